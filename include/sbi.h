@@ -365,9 +365,8 @@ int32_t sbi_last_stats(const sbi_ctx* ctx, double* out, int32_t n);
  *                compile without register spills): sbi_plan_variants().
  *   row_rows     rows of the grid per row-pass workgroup (a power of two; 0:
  *                as many as fill 256 threads, the default).
- *   col_split    workgroups a column pass should reach by splitting its
- *                products over workgroups along y (0: no split, the default;
- *                only 2D grids split).
+ *   col_split    kept with the plan (>= 0; 0 the default) and without effect:
+ *                a column pass deals its products to its own wavefronts.
  *   us           time of the tuned unit under this plan in microseconds (one
  *                sweep in iteration mode, one W solve in SA mode), 0 when the
  *                plan was set rather than measured.
@@ -393,9 +392,8 @@ sbi_status sbi_plan_get(const sbi_ctx* ctx, sbi_plan* out);
 sbi_status sbi_plan_set(sbi_ctx* ctx, const sbi_plan* plan);
 
 /*
- * Autotuner: times every built row variant, rows per workgroup from the
- * launch bound down to a quarter of it, and column splits {0, 1024, 2048,
- * 4096} (2D grids), each on the context's own kernels and workspace (5 units
+ * Autotuner: times every built row variant and rows per workgroup from the
+ * launch bound down to a quarter of it, each on the context's own kernels and workspace (5 units
  * after 2 of warm-up, best of two rounds, HIP events on the context's
  * stream), and keeps the fastest.  The plan cache, a process-wide table keyed
  * by device (name and architecture), grid size, batch, precision, mode,

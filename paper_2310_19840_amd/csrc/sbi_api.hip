@@ -40,7 +40,7 @@ enum {
     C_EH, C_PH,          // state u_n
     C_ES, C_PS,          // stage state
     C_AE, C_AP,          // Runge-Kutta accumulator
-    C_VH,                // W spectrum (SA sum)
+    C_VH,                // W spectrum (SA: V_1, then the sum of the orders)
     C_BV, C_BB,          // constant parts of the summed operator
     C_VN, C_BN,          // current iterate (V, phi_b)
     C_VP,                // T(V_n): candidate answer of the iteration
@@ -57,8 +57,10 @@ enum {
     C_HB0 = C_HV0 + kHistTaps,  //   (phi_b)
     C_PV = C_HB0 + kHistTaps,   // its prediction for the current solve (V, phi_b)
     C_PB,
-    C_COUNT
+    C_COUNT,
+    C_SAV0 = C_AFV0      // SA orders V_2 .. V_6 (that mode has no residual history)
 };
+static_assert(4 * kAASlots >= 11, "the SA orders take the history ring's slots");
 // half-form buffers
 enum {
     H_ETA, H_EX, H_EY, H_PX, H_PY,  // state and its gradients
@@ -75,8 +77,6 @@ enum {
     P_BY0 = P_BX0 + 7,
     P_COUNT = P_BY0 + 7
 };
-
-constexpr int kAABlocks = 256;  // workgroups per member of the Anderson inner products
 
 struct Stats {
     double launches = 0, syncs = 0, sweeps = 0;
@@ -124,11 +124,8 @@ struct sbi_ctx {
     double* href_dev = nullptr;
     Ctl* ctl = nullptr;
     double* diag_partial = nullptr;
-    double* aa_partial = nullptr;   // [batch][kAABlocks][kAASlots] inner-product partials
-    void* part = nullptr;    // partial sums of grouped column passes
-    int* cnt = nullptr;      // tile tickets of grouped column passes
-    int col_C = 1;
-    int group_target = 0;    // workgroups a column pass should reach by splitting products (0: never split)
+    double* aa_partial = nullptr;   // [batch][column tiles][kAASlots] inner-product partials
+    int group_target = 0;    // the plan's col_split (kept; the column pass has no use for it)
     int diag_nblk = 64;
     std::vector<double> href;
     bool vd = false;         // some member has a non-flat bed
@@ -230,7 +227,7 @@ static sbi_status hip_ok(hipError_t e) { return e == hipSuccess ? SBI_OK : SBI_E
 // sizes and layout
 // ---------------------------------------------------------------------------
 struct Layout {
-    int Mx, My, Kx, Kxp, Ky, C, qb, ldh;
+    int Mx, My, Kx, Kxp, Ky, C, ldh;
     size_t rsz, csz;
     long long s_phys, s_half, s_cmp;
     size_t bytes_comp, bytes_half, bytes_phys, bytes_tw, bytes_misc, bytes_net, bytes_full, bytes_inner, total;
@@ -285,8 +282,7 @@ static Layout layout(const sbi_grid* g, int batch) {
     L.Mx = (int)std::ceil(g->dealias * g->nx / 2.0 - 1e-9) - 1;
     L.My = g->ny == 1 ? 0 : (int)std::ceil(g->dealias * g->ny / 2.0 - 1e-9) - 1;
     L.Kx = L.Mx + 1;
-    L.qb = col_quarter_band(g->ny, L.My);
-    L.C = col_tile(g->ny, f64, L.qb);
+    L.C = col_tile(g->ny);
     L.Kxp = (L.Kx + L.C - 1) / L.C * L.C;
     L.Ky = g->ny == 1 ? 1 : 2 * L.My + 1;
     L.s_phys = (long long)g->nx * g->ny;
@@ -299,9 +295,7 @@ static Layout layout(const sbi_grid* g, int batch) {
     L.bytes_phys = al((size_t)L.s_phys * L.rsz * batch) * P_COUNT;
     L.bytes_tw = al((size_t)g->nx * L.csz) + al((size_t)(g->nx / 2) * L.csz) + al((size_t)g->ny * L.csz);
     L.bytes_misc = al(sizeof(double) * batch) + al(sizeof(Ctl) * batch) + al(sizeof(CtlSlots) * batch) +
-                   al(sizeof(double) * 2 * 64 * batch) + al(sizeof(double) * kAASlots * kAABlocks * batch) +
-                   al(sizeof(double) * kAASlots * batch) +
-                   al((size_t)L.s_cmp * L.csz * batch * kMaxGroups * 4) + al(sizeof(int) * (size_t)kMaxTiles * batch);
+                   al(sizeof(double) * 2 * 64 * batch) + al(sizeof(double) * kAASlots * (size_t)(L.Kxp / L.C) * batch);
     // learned warm start: packed weights, and the feature field when it seeds the iteration
     L.bytes_net = al(sizeof(NetPacked)) +
                   ((g->seed == SBI_SEED_NET && g->ny > 1) ? al((size_t)L.s_phys * 8 * sizeof(float) * batch) : 0) +
@@ -530,11 +524,7 @@ static sbi_status ctx_setup(sbi_ctx* c, const sbi_grid* g, int32_t batch, const 
     c->diag_partial = reinterpret_cast<double*>(p);
     p += al(sizeof(double) * 2 * 64 * batch);
     c->aa_partial = reinterpret_cast<double*>(p);
-    p += al(sizeof(double) * kAASlots * kAABlocks * batch);
-    c->part = p;
-    p += al((size_t)L.s_cmp * L.csz * batch * kMaxGroups * 4);
-    c->cnt = reinterpret_cast<int*>(p);
-    p += al(sizeof(int) * (size_t)kMaxTiles * batch);
+    p += al(sizeof(double) * kAASlots * (size_t)(L.Kxp / L.C) * batch);
     c->net = reinterpret_cast<NetPacked*>(p);
     p += al(sizeof(NetPacked));
     if (g->seed == SBI_SEED_NET && g->ny > 1) {
@@ -568,9 +558,7 @@ static sbi_status ctx_setup(sbi_ctx* c, const sbi_grid* g, int32_t batch, const 
         c->full_part = p + 16 * tb;
         c->full_bed = reinterpret_cast<int*>(p + 16 * tb + al((size_t)full_slices(g->nx) * g->nx * 8 * batch));
     }
-    c->col_C = L.C;
     gd.col_C = L.C;
-    gd.qb = L.qb;
     gd.href = c->href_dev;
     if (transient) {
         c->head_host.assign(batch, Ctl{});
@@ -586,10 +574,6 @@ static sbi_status ctx_setup(sbi_ctx* c, const sbi_grid* g, int32_t batch, const 
             return SBI_ERR_HIP;
         }
     }
-    // SBI_COL_GROUP_TARGET: workgroups a column pass aims for by splitting its
-    // products over workgroups (tuning knob; 0 = one workgroup per tile)
-    if (const char* e = std::getenv("SBI_COL_GROUP_TARGET")) c->group_target = std::atoi(e);
-
     sbi_status st = hip_ok(launch_fill_zero(c->ws, L.total, c->stream));
     if (st == SBI_OK) {
         auto up = [&](void* dst, int n) -> sbi_status {
@@ -703,76 +687,109 @@ extern "C" int32_t sbi_last_stats(const sbi_ctx* c, double* out, int32_t n) {
 // ---------------------------------------------------------------------------
 // column-pass builder
 // ---------------------------------------------------------------------------
+// Inputs and outputs belong to the sub-pass they were added in (next_sub()
+// starts another; sub-passes run side by side with accumulators of their own).
 struct ColBuilder {
     ColParams p{};
-    std::vector<ColTerm> terms;
-    std::vector<const void*> prods, cins;
-    std::vector<int> cin_w;
-    std::vector<long long> prod_stride;
+    bool ok = true;
+    std::vector<int> cin_of;   // compact input -> its entry in p.csrc
+    int np = 0, nc = 0, no = 0, ni = 0;
     explicit ColBuilder(const GridDev& g) {
         p.g = g;
-        p.relax_prev[0] = p.relax_prev[1] = -1;
         p.nacc = 1;
+        p.nsub = 1;
+        p.sub[0] = ColSub{};
     }
-    int prod(const void* h, long long stride = 0) {
-        prods.push_back(h);
-        prod_stride.push_back(stride);
-        return (int)prods.size() - 1;
+    static ColSrc empty(const void* ptr, int widx) {
+        ColSrc s{};
+        s.ptr = ptr;
+        s.acc[0] = s.acc[1] = -1;
+        s.widx = (signed char)widx;
+        return s;
+    }
+    int prod(const void* h) {
+        if (np >= kMaxProd) {
+            ok = false;
+            return 0;
+        }
+        p.src[np] = empty(h, -1);
+        return np++;
     }
     // widx >= 0: the input is scaled by the Anderson weight of history slot
     // widx, which the pass solves for itself (p.aa_partial must be set)
     int cin(const void* c, int widx = -1) {
-        cins.push_back(c);
-        cin_w.push_back(widx);
-        return -(int)cins.size();  // resolved at build: nprod + index
+        if (nc >= kMaxCin) {
+            ok = false;
+            return -1;
+        }
+        p.src[kMaxProd + nc] = empty(c, widx);
+        cin_of.push_back(nc++);
+        return -(int)cin_of.size();
     }
+    // src: what prod() or cin() returned.  A compact input with a third term
+    // or another derivative is entered once more (its owner reads it again)
     void term(int src, int acc, double coef, int fn, int pw, int dv) {
-        ColTerm t{};
-        t.coef = coef;
-        t.src = (short)src;
-        t.acc = (signed char)acc;
-        t.fn = (signed char)fn;
-        t.pw = (signed char)pw;
-        t.dv = (signed char)dv;
-        terms.push_back(t);
+        if (!ok) return;
+        if (pw > 6 || pw < -1) {  // the column pass forms k^-1 .. k^6
+            ok = false;
+            return;
+        }
+        ColSrc* s = src >= 0 ? &p.src[src] : &p.src[kMaxProd + cin_of[-src - 1]];
+        if (s->acc[0] >= 0 && (s->acc[1] >= 0 || s->dv != dv)) {
+            if (src >= 0 || nc >= kMaxCin) {
+                ok = false;
+                return;
+            }
+            p.src[kMaxProd + nc] = empty(s->ptr, s->widx);
+            s = &p.src[kMaxProd + nc];
+            cin_of[-src - 1] = nc++;
+        }
+        const int t = s->acc[0] < 0 ? 0 : 1;
+        s->acc[t] = (signed char)acc;
+        s->coef[t] = coef;
+        s->fn[t] = (signed char)fn;
+        s->pw[t] = (signed char)pw;
+        s->dv = (signed char)dv;
+        if (fn != FN_ONE) p.hyper = 1;
         p.nacc = std::max(p.nacc, acc + 1);
     }
     void cout(int src, void* dst) {
-        p.cout_src[p.ncout] = src;
-        p.cout[p.ncout++] = dst;
+        if (no >= kMaxCout) {
+            ok = false;
+            return;
+        }
+        p.cout_src[no] = src;
+        p.cout[no++] = dst;
     }
     void inv(int src, int dv, void* dst) {
-        p.inv_src[p.ninv] = src;
-        p.inv_dv[p.ninv] = dv;
-        p.inv[p.ninv++] = dst;
+        if (ni >= kMaxInv) {
+            ok = false;
+            return;
+        }
+        p.inv_src[ni] = src;
+        p.inv_dv[ni] = dv;
+        p.inv[ni++] = dst;
+    }
+    void close() {
+        ColSub& s = p.sub[p.nsub - 1];
+        s.p1 = (short)np;
+        s.c1 = (short)nc;
+        s.o1 = (short)no;
+        s.i1 = (short)ni;
+    }
+    void next_sub() {
+        close();
+        if (p.nsub >= kMaxSub) {
+            ok = false;
+            return;
+        }
+        p.sub[p.nsub++] = ColSub{(short)np, (short)np, (short)nc, (short)nc, (short)no, (short)no, (short)ni, (short)ni};
     }
     bool build() {
-        p.nprod = (int)prods.size();
-        p.ncin = (int)cins.size();
-        if (p.nprod > kMaxProd || p.ncin > kMaxCin || (int)terms.size() > kMaxTerms) return false;
-        for (auto& t : terms)
-            if (t.pw > 6 || t.pw < -1) return false;  // the column pass forms k^-1 .. k^6
-        for (int i = 0; i < p.nprod; ++i) {
-            p.hin[i] = prods[i];
-            p.hin_stride[i] = prod_stride[i];
-        }
-        for (int i = 0; i < p.ncin; ++i) p.cin[i] = cins[i];
-        for (int i = 0; i < kMaxCin; ++i) {
-            p.cin_widx[i] = (signed char)(i < p.ncin ? cin_w[i] : -1);
-            if (p.cin_widx[i] >= kAASlots || (p.cin_widx[i] >= 0 && !p.aa_partial)) return false;
-        }
-        for (auto& t : terms)
-            if (t.src < 0) t.src = (short)(p.nprod + (-t.src - 1));
-        std::stable_sort(terms.begin(), terms.end(), [](const ColTerm& a, const ColTerm& b) { return a.src < b.src; });
-        const int nsrc = p.nprod + p.ncin;
-        int k = 0;
-        for (int s = 0; s <= nsrc; ++s) {
-            while (k < (int)terms.size() && terms[k].src < s) ++k;
-            p.toff[s] = (short)k;
-        }
-        p.nterm = (int)terms.size();
-        for (int i = 0; i < p.nterm; ++i) p.term[i] = terms[i];
-        return true;
+        close();
+        for (int i = 0; i < nc; ++i)
+            if (p.src[kMaxProd + i].widx >= kAASlots || (p.src[kMaxProd + i].widx >= 0 && !p.aa_partial)) return false;
+        return ok;
     }
 };
 
@@ -838,24 +855,8 @@ static Twiddles tw_of(const sbi_ctx* c) {
 #define HALF(i) (c->half[(i)])
 #define PHYS(i) (c->phys[(i)])
 
-// Split the products of a column pass over workgroups along y when the tiles
-// alone cannot fill the GPU (~512 workgroups wanted).
-static void set_groups(sbi_ctx* c, ColParams& p) {
-    p.ngroup = 1;
-    p.part = c->part;
-    p.cnt = c->cnt;
-    const int np = p.nprod;
-    if (np <= 1 || c->grid.ny == 1 || c->group_target <= 0) return;
-    const int tiles = c->gd.Kxp / c->col_C;
-    int want = (c->group_target + tiles * c->batch - 1) / (tiles * c->batch);
-    want = std::max(1, std::min(want, std::min(np, kMaxGroups)));
-    p.ngroup = want;
-    for (int g = 0; g <= want; ++g) p.gstart[g] = (g * np) / want;
-}
-
 static sbi_status run_col(sbi_ctx* c, ColBuilder& b, int cls = K_COL_OTHER) {
     if (!b.build()) return SBI_ERR_UNSUPPORTED;
-    set_groups(c, b.p);
     c->st.launches += 1;
     ProfScope ps(c, cls);
     return hip_ok(launch_col(c->fp64, b.p, c->batch, tw_of(c), c->stream));
@@ -932,7 +933,6 @@ static sbi_status stage_state_pass(sbi_ctx* c, bool need_eta, bool allow_prev = 
         b.cout(SRC_ACC2, CMP(C_VN));
         if (c->vd) b.cout(SRC_ACC3, CMP(C_BN));
     }
-    if (!c->vd && b.p.nacc < 3) b.p.nacc = 3;
     return run_col(c, b, K_COL_STATE);
 }
 
@@ -992,29 +992,13 @@ static sbi_status col_forcing(sbi_ctx* c) {
 }
 
 // Anderson mixing after the column pass of sweep n (which stored f_n and g_n
-// in the history ring): partial inner products, then one column pass whose
-// workgroups each solve for the weights w_i of the next iterate and form
+// in the history ring and left the partial inner products <F_i, f_n> of its
+// workgroups): one column pass whose workgroups each solve for the weights w_i of the next iterate and form
 // x_(n+1) = sum_i w_i g_i from the history (compact) and its inverse column
 // transforms (V, grad phi_b) for the next row pass
 static sbi_status anderson_mix(sbi_ctx* c, int n) {
     const bool two_d = c->grid.ny > 1;
     const int k = std::min(n, kAADepth);
-    AaParams ap{};
-    ap.g = c->gd;
-    ap.ctl = c->ctl;
-    ap.sweep = n;
-    ap.vd = c->vd;
-    for (int i = 0; i < kAASlots; ++i) {
-        ap.fv[i] = CMP(C_AFV0 + i);
-        ap.fb[i] = CMP(C_AFB0 + i);
-    }
-    ap.partial = c->aa_partial;
-    ap.nblk = kAABlocks;
-    c->st.launches += 1;
-    {
-        ProfScope ps_(c, K_COL_OTHER);
-        SBI_TRY(hip_ok(launch_aa_dot(c->fp64, ap, c->batch, c->stream)));
-    }
     ColBuilder b(c->gd);
     for (int a = 0; a <= k; ++a) {
         const int si = (n - k + a) % kAASlots;
@@ -1027,7 +1011,7 @@ static sbi_status anderson_mix(sbi_ctx* c, int n) {
     }
     // every workgroup of the pass adds the partials and solves for the weights
     b.p.aa_partial = c->aa_partial;
-    b.p.aa_nblk = kAABlocks;
+    b.p.aa_nblk = c->gd.Kxp / c->gd.col_C;
     b.p.aa_sweep = n;
     b.cout(SRC_ACC0, CMP(C_VN));
     b.inv(SRC_ACC0, DV_NONE, HALF(H_GV));
@@ -1078,9 +1062,9 @@ static sbi_status run_row_sweep(sbi_ctx* c, const RowSweepParams& rp) {
 }
 
 // terms of T(x) = b + A x in a column pass: the forcing (C_BV, C_BB) and, with
-// products, the summed operator applied to the iterate's products; *cvn and
-// *cbn are the inputs that hold the iterate x itself (C_VN, C_BN)
-static void sweep_col_terms(sbi_ctx* c, ColBuilder& b, bool products, int* cvn, int* cbn) {
+// products, the summed operator applied to the iterate's products; the
+// previous iterate x itself (C_VN, C_BN) is the pass's prev
+static void sweep_col_terms(sbi_ctx* c, ColBuilder& b, bool products) {
     const bool two_d = c->grid.ny > 1;
     const int J = c->grid.order - 1;
     std::vector<int> se(J + 1), sbx(J + 1), sby(J + 1);
@@ -1093,16 +1077,10 @@ static void sweep_col_terms(sbi_ctx* c, ColBuilder& b, bool products, int* cvn, 
                 for (int j = 1; j <= J; ++j) sby[j] = b.prod(HALF(H_PROD0 + idx++));
         }
     }
-    int cbv = b.cin(CMP(C_BV));
-    *cvn = b.cin(CMP(C_VN));
-    int cbb = -1;
-    *cbn = -1;
-    if (c->vd) {
-        cbb = b.cin(CMP(C_BB));
-        *cbn = b.cin(CMP(C_BN));
-    }
-    b.term(cbv, 0, 1.0, FN_ONE, 0, DV_NONE);
-    if (c->vd) b.term(cbb, 1, 1.0, FN_ONE, 0, DV_NONE);
+    b.term(b.cin(CMP(C_BV)), 0, 1.0, FN_ONE, 0, DV_NONE);
+    if (c->vd) b.term(b.cin(CMP(C_BB)), 1, 1.0, FN_ONE, 0, DV_NONE);
+    b.p.prev[0] = CMP(C_VN);
+    if (c->vd) b.p.prev[1] = CMP(C_BN);
     if (products) {
         for (int j = 1; j <= J; ++j) {
             const double f = 1.0 / fact(j);
@@ -1131,16 +1109,18 @@ static sbi_status launch_sweep(sbi_ctx* c, const void* eta_phys, int n, double t
     SBI_TRY(run_row_sweep(c, rp));
 
     ColBuilder b(c->gd);
-    int cvn, cbn;
-    sweep_col_terms(c, b, rp.products, &cvn, &cbn);
+    sweep_col_terms(c, b, rp.products);
     if (aa) {
         // T_V(x_n); the residual f_n and the relaxed sweep g_n into the history
         // ring; the half forms of the residual test (f_n and T_V(x_n)).  The
         // next iterate follows once the inner products over the whole spectrum
         // are known.
         const int s = n % kAASlots;
-        b.p.relax_prev[0] = -cvn - 1;
-        if (c->vd) b.p.relax_prev[1] = -cbn - 1;
+        b.p.aa_dots = c->aa_partial;
+        for (int i = 0; i < kAASlots; ++i) {
+            b.p.aa_f[0][i] = CMP(C_AFV0 + i);
+            b.p.aa_f[1][i] = c->vd ? CMP(C_AFB0 + i) : nullptr;
+        }
         b.cout(SRC_ACC0, CMP(C_VP));
         b.cout(SRC_DIFF0, CMP(C_AFV0 + s));
         b.cout(SRC_NEW0, CMP(C_AGV0 + s));
@@ -1151,8 +1131,6 @@ static sbi_status launch_sweep(sbi_ctx* c, const void* eta_phys, int n, double t
         b.inv(SRC_DIFF0, DV_NONE, HALF(H_GD));
         b.inv(SRC_ACC0, DV_NONE, HALF(H_GT));
     } else {
-        b.p.relax_prev[0] = -cvn - 1;  // resolved in build(): encoded as cin index
-        if (c->vd) b.p.relax_prev[1] = -cbn - 1;
         b.cout(SRC_ACC0, CMP(C_VP));
         b.cout(SRC_NEW0, CMP(C_VN));
         if (c->vd) b.cout(SRC_NEW1, CMP(C_BN));
@@ -1283,10 +1261,7 @@ static sbi_status iterate_half_forms(sbi_ctx* c) {
 static sbi_status refine_sweep(sbi_ctx* c, const void* eta_phys, int k) {
     SBI_TRY(run_row_sweep(c, sweep_row_params(c, eta_phys, false, true, 0, false)));
     ColBuilder b(c->gd);
-    int cvn, cbn;
-    sweep_col_terms(c, b, c->grid.order > 1, &cvn, &cbn);
-    b.p.relax_prev[0] = -cvn - 1;
-    if (c->vd) b.p.relax_prev[1] = -cbn - 1;
+    sweep_col_terms(c, b, c->grid.order > 1);
     b.cout(SRC_ACC0, CMP(C_VP));
     b.cout(SRC_DIFF0, CMP(C_AFV0));
     if (c->vd) b.cout(SRC_DIFF1, CMP(C_AFB0));
@@ -1408,21 +1383,16 @@ static sbi_status run_sa(sbi_ctx* c, const void* eta_phys) {
         }
         int fx = b.prod(HALF(H_PROD0 + idx++));
         int fy = two_d ? b.prod(HALF(H_PROD0 + idx++)) : -1;
-        int cvh = b.cin(CMP(C_VH));
         const bool want_b = c->vd && l <= L - 1;
-        // acc0 = V_l, acc1 = phi_b,l, acc2 = running sum of V
-        auto both = [&](int src, double coef, int fn, int pw, int dv) {
-            b.term(src, 0, coef, fn, pw, dv);
-            b.term(src, 2, coef, fn, pw, dv);
-        };
+        // acc0 = V_l (kept until the last order adds them all), acc1 = phi_b,l
         for (int j = 1; j <= l - 1; ++j) {
             const double f = 1.0 / fact(j);
-            both(se[j], -f, Tfn(j), j, DV_NONE);
+            b.term(se[j], 0, -f, Tfn(j), j, DV_NONE);
             if (want_b && (j & 1)) b.term(se[j], 1, -f, FN_S, j - 1, DV_NONE);
             if (c->vd) {
                 if (j & 1) {
-                    both(sbx[j], f, FN_S, j - 1, DV_X);
-                    if (two_d) both(sby[j], f, FN_S, j - 1, DV_Y);
+                    b.term(sbx[j], 0, f, FN_S, j - 1, DV_X);
+                    if (two_d) b.term(sby[j], 0, f, FN_S, j - 1, DV_Y);
                 }
                 if (want_b) {
                     const double sg = (j & 1) ? -f : f;
@@ -1432,23 +1402,25 @@ static sbi_status run_sa(sbi_ctx* c, const void* eta_phys) {
             }
         }
         const double fl = -1.0 / fact(l - 1);
-        both(fx, fl, Tfn(l), l - 2, DV_X);
-        if (two_d) both(fy, fl, Tfn(l), l - 2, DV_Y);
+        b.term(fx, 0, fl, Tfn(l), l - 2, DV_X);
+        if (two_d) b.term(fy, 0, fl, Tfn(l), l - 2, DV_Y);
         if (want_b && (l & 1)) {
             b.term(fx, 1, fl, FN_S, l - 3, DV_X);
             if (two_d) b.term(fy, 1, fl, FN_S, l - 3, DV_Y);
         }
-        b.term(cvh, 2, 1.0, FN_ONE, 0, DV_NONE);
-        b.p.nacc = 3;
-        b.cout(SRC_ACC2, CMP(C_VH));
         if (l < L) {
+            b.cout(SRC_ACC0, CMP(C_SAV0 + l - 2));
             b.inv(SRC_ACC0, DV_NONE, HALF(H_GV));
             if (want_b) {
                 b.inv(SRC_ACC1, DV_X, HALF(H_GBX));
                 if (two_d) b.inv(SRC_ACC1, DV_Y, HALF(H_GBY));
             }
         } else {
-            b.inv(SRC_ACC2, DV_NONE, HALF(H_GV));
+            // W = V_1 + ... + V_L
+            b.term(b.cin(CMP(C_VH)), 0, 1.0, FN_ONE, 0, DV_NONE);
+            for (int m = 2; m < L; ++m) b.term(b.cin(CMP(C_SAV0 + m - 2)), 0, 1.0, FN_ONE, 0, DV_NONE);
+            b.cout(SRC_ACC0, CMP(C_VH));
+            b.inv(SRC_ACC0, DV_NONE, HALF(H_GV));
         }
         SBI_TRY(run_col(c, b, K_COL_SA));
     }
@@ -2747,17 +2719,15 @@ static sbi_status tune_key(const sbi_ctx* c, std::string* key) {
 }
 
 // the plans the tuner tries: every built row variant, rows per workgroup from
-// the launch bound down to a quarter of it, column splits of 2D grids
+// the launch bound down to a quarter of it
 static std::vector<sbi_plan> plan_candidates(const sbi_ctx* c) {
     std::vector<sbi_plan> out;
     const int mask = plan_variants(c);
-    std::vector<int> splits = {0};
-    if (c->grid.ny > 1) splits = {0, 1024, 2048, 4096};
     for (int v = 0; v < 4; ++v) {
         if (!((mask >> v) & 1)) continue;
         const int cap = std::min(row_rows_cap(c->fp64, c->grid.nx, v), c->grid.ny);
         for (int rows = cap; rows >= 1 && rows * 4 >= cap; rows /= 2)
-            for (int sp : splits) out.push_back(sbi_plan{v, rows, sp, 0.f, 0});
+            out.push_back(sbi_plan{v, rows, 0, 0.f, 0});
     }
     return out;
 }

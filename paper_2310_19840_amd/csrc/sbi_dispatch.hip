@@ -6,18 +6,12 @@
 
 namespace sbi {
 
-// columns per column-pass workgroup (equals ColCfg<R, NY, QB, NACC>::C of the kernels;
-// the launcher checks it)
-int col_tile(int ny, int fp64, int qb) {
+// columns per column-pass workgroup (equals ColShape<R, NY>::CW of the kernels, 64
+// modes of a 1D grid; the launcher checks it): the columns of one wavefront
+int col_tile(int ny) {
     if (ny == 1) return 64;
-    if (qb && ny == 1024) return 1;  // one wavefront per column transform
-    int e = (fp64 && !qb) ? 4 : 8;
-    if (e > ny) e = ny;
-    const int P = ny / e;
-    return P >= 128 ? 1 : 256 / P;
+    return ny >= 512 ? 1 : 512 / ny;
 }
-
-int col_quarter_band(int ny, int My) { return (ny >= 128 && 4 * My < ny) ? 1 : 0; }
 
 __global__ void k_ctl_reset(Ctl* ctl, int slots) {
     Ctl* c = ctl + blockIdx.x;
@@ -268,9 +262,6 @@ hipError_t launch_rk(int fp64, const RkParams& p, int batch, hipStream_t s) {
 }
 hipError_t launch_rk54(int fp64, const Rk54Params& p, int batch, hipStream_t s) {
     return fp64 ? launch_rk54_t<double>(p, batch, s) : launch_rk54_t<float>(p, batch, s);
-}
-hipError_t launch_aa_dot(int fp64, const AaParams& p, int batch, hipStream_t s) {
-    return fp64 ? launch_aa_dot_t<double>(p, batch, s) : launch_aa_dot_t<float>(p, batch, s);
 }
 hipError_t launch_diag(int fp64, const DiagParams& p, int batch, hipStream_t s) {
     return fp64 ? launch_diag_t<double>(p, batch, s) : launch_diag_t<float>(p, batch, s);

@@ -22,12 +22,10 @@ namespace sbi {
 
 constexpr int kMaxSweepSlots = 1024;   // max_sweeps <= 1000
 constexpr int kMaxProd = 24;           // forward inputs of one column pass
-constexpr int kMaxCin = 8;             // compact inputs of one column pass
-constexpr int kMaxTerms = 48;
-constexpr int kMaxCout = 6;
+constexpr int kMaxCin = 16;            // compact inputs of one column pass
+constexpr int kMaxCout = 16;
 constexpr int kMaxInv = 8;
-constexpr int kMaxGroups = 8;          // product groups of one column pass
-constexpr int kMaxTiles = 4096;        // column tiles per member (ticket counters)
+constexpr int kMaxSub = 6;             // sub-passes of one column pass
 constexpr size_t kMaxLdsBytes = 160 * 1024;  // LDS of one gfx950 workgroup
 
 // Per-member control block in device memory: a small header the host reads
@@ -39,7 +37,6 @@ struct CtlSlots {
 };
 constexpr int kAADepth = 2;              // residual differences kept by the Anderson mixing
 constexpr int kAASlots = kAADepth + 1;   // history ring of residuals and relaxed sweeps
-constexpr int kAADotThreads = 512;       // threads of an inner-product workgroup (<= 1024)
 
 // Learned history seed (a spectral layer of the learned warm start): the
 // nonlinear part of a fixed-step solve at RK stage s is predicted from the
@@ -100,7 +97,6 @@ struct GridDev {
     long long s_cmp;    // complex per member of a compact field
     const double* href; // [batch] reference depth
     int relax;
-    int qb;             // kept band below ny/4 and ny >= 128: the quarter-band column pass
     int col_C;          // columns per column-pass workgroup (Kxp is a multiple)
     // launch plan of the row sweep and SA kernels (the autotuner's choice):
     // row_var 0 radix-8 with twiddle recurrence, 1 radix-8 with every twiddle
@@ -109,14 +105,25 @@ struct GridDev {
     int row_var, row_rpw;
 };
 
-// Multiplier of one contribution to a column-pass accumulator:
+// One input of a column pass (a half form to transform, or a compact field) and
+// what it adds to the accumulators: at most two terms
 //   coef * fn(k) * k^pw * dv,  fn in {1, tanh(kh), sech(kh)}, dv in {1, i kx, i ky}
 // (k^-1 and i k terms vanish at k = 0).
-struct ColTerm {
-    double coef;
-    short src;      // product index (< nprod) or nprod + compact-input index
-    signed char acc, fn, pw, dv;
-    signed char pad[2];
+struct ColSrc {
+    double coef[2];
+    const void* ptr;
+    signed char acc[2];   // accumulator of each term, -1: none
+    signed char fn[2], pw[2];
+    signed char dv;
+    signed char widx;     // Anderson weight (history slot) scaling a compact input, -1: none
+};
+
+// a sub-pass (blockIdx.y) of a column pass: its own inputs, accumulators and outputs
+struct ColSub {
+    short p0, p1;   // products
+    short c0, c1;   // compact inputs
+    short o0, o1;   // compact outputs
+    short i0, i1;   // inverse transforms
 };
 
 enum { FN_ONE = 0, FN_T = 1, FN_S = 2 };
@@ -129,24 +136,24 @@ enum { CTL_NONE = 0, CTL_OMEGA = 1, CTL_SWEEP = 2, CTL_SKIP = 3 };  // CTL_SKIP:
 
 struct ColParams {
     GridDev g;
-    int nprod, ncin, nterm, nacc;
-    const void* hin[kMaxProd];
-    long long hin_stride[kMaxProd];   // per-member stride override (0 = g.s_half)
-    const void* cin[kMaxCin];
-    signed char cin_widx[kMaxCin];     // Anderson weight (history slot) scaling each compact input, -1: none
+    int nacc, nsub;
+    int hyper;                         // some term uses tanh(kh) or sech(kh)
+    ColSub sub[kMaxSub];
+    ColSrc src[kMaxProd + kMaxCin];    // products (half forms), then from kMaxProd on compact inputs
     // Anderson weights formed in the pass itself: when aa_partial is set, each
     // workgroup adds the inner-product partials of sweep aa_sweep
     // ([batch][aa_nblk][kAASlots]) and solves for the weights of the history
     // slots; the first workgroup of a member stores the new Gram entries
     const double* aa_partial;
     int aa_nblk, aa_sweep;
-    short toff[kMaxProd + kMaxCin + 1]; // terms sorted by source: [toff[s], toff[s+1])
-    ColTerm term[kMaxTerms];
-    int relax_prev[2];                 // compact-input index of the previous iterate of acc0/acc1, -1 none
-    int ncout;
+    // inner products <F_i, f_n> of the residual history formed by a sweep's
+    // pass (f_n the differences of its accumulators to prev, the older ones
+    // the ring aa_f[V, phi_b part][slot]): one partial per workgroup
+    double* aa_dots;
+    const void* aa_f[2][kAASlots];
+    const void* prev[2];               // previous iterate of acc0 / acc1 (compact), null: none
     int cout_src[kMaxCout];
     void* cout[kMaxCout];
-    int ninv;
     int inv_src[kMaxInv];
     int inv_dv[kMaxInv];
     void* inv[kMaxInv];
@@ -155,13 +162,7 @@ struct ColParams {
     int sweep;        // sweep index n of this pass (CTL_SWEEP)
     int max_sweeps;
     double tol;
-    // products split over workgroups along y: group g transforms products
-    // [gstart[g], gstart[g+1]); partial sums go to `part` and the last
-    // workgroup of a tile (ticket in `cnt`) adds them in group order.
-    int ngroup;
-    int gstart[kMaxGroups + 1];
-    void* part;       // [batch][kMaxGroups][4][Ky][Kxp] complex
-    int* cnt;         // [batch][kMaxTiles]
 };
+static_assert(sizeof(ColParams) <= 4096, "a kernel's arguments");
 
 }  // namespace sbi

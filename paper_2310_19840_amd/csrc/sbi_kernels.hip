@@ -10,6 +10,7 @@
 // iterate directly from registers.  Only kept modes are ever written, so the
 // spectra in memory are 1/4 (2D) of the full size.
 #include <math.h>
+#include <algorithm>
 #include <type_traits>
 #include "sbi_device.hpp"
 #include "sbi_fft.hpp"
@@ -784,51 +785,55 @@ __global__ void __launch_bounds__(row_threads<NX>()) k_row_feat(const RowFeatPar
 // ---------------------------------------------------------------------------
 // Column pass: forward column transforms of the products, multiplier sums,
 // relaxation, compact outputs, inverse column transforms of the results.
+//
+// A workgroup owns the columns of one wavefront's transform (ColShape::CW of
+// them; a single one from 512 rows on) and the kept modes in them.  Its
+// wavefronts take the products as jobs, one column transform each, which never
+// leave the wavefront; after a round of transforms the kept values stand in
+// the wavefronts' LDS areas, and each thread -- the owner of one kept mode --
+// adds the round's products to its mode's sums, the multipliers formed once
+// per mode and product with the term's exponents in scalar registers.  The
+// next round's columns are requested before the sums, so the loads run under
+// them.  The owners read and write the compact fields themselves (one
+// contiguous run per column) and hand the wavefronts the spectra of the
+// inverse transforms through the same areas.
+//
+// What bounds it: at 1024 rows the transforms' issue and LDS exchanges, on
+// small grids the chain of dependent loads and barriers of one workgroup.
+// Measured per launch, against one whose transform threads also formed the sums
+// of the modes they held: FP64 1024 x 1024 sweep 36 us (37, and 5.6 for the
+// inner products in a kernel of their own), its inverse pass 16.6 (17.5); FP32
+// 512 x 512 SA order 8.5 (21.7); FP64 128 x 64 sweep 20 (31); a single product
+// without inverse at 1024 rows 6.9 (11.8).
+//
+// S ("classes"): columns of more than 512 rows are split by decimation in
+// frequency into S = ny / 512 transforms of 512 points, one wavefront each:
+// wave h forms u_h[n] = sum_p x[n + 512 p] W_S^(h p) W^(h n), W = exp(-2 pi i /
+// ny), whose transform holds the modes S k + h.  All S waves read the whole
+// column (the repeated reads are served by the cache).  The inverse runs the
+// other way: each wave inverts its class of modes, multiplies by W^(-h n), and
+// the S waves form x[n + 512 p] = sum_h W_S^(-h p) e_h[n] through LDS.
 // ---------------------------------------------------------------------------
-// Shape of a column pass.  QB ("quarter band"): the kept band |m_y| <= My lies
-// below NY/4, so of the E values a thread transforms (modes j + qP) only the
-// first and last E/4 can be kept; the accumulators of the others are never
-// formed.  Elements per thread: 8, or 4 in FP64 without QB (the accumulators of
-// all E modes then share the registers); columns of 128 or more threads get a
-// workgroup of their own, shorter ones are packed to 256 threads per lane (half
-// forms are column-major, so each column is one contiguous run); product
-// lanes (threads transforming different products of the same columns) fill up
-// to 512 threads, at most 2 in FP64 without QB and 4 otherwise.
-// WV ("wave lanes", QB at NY = 1024 with at most 2 accumulators in FP64):
-// 16 elements per thread, so a single wavefront owns a whole column
-// transform; one column per workgroup and up to 8 product lanes of one
-// wavefront each, which never wait on one another until their sums are
-// combined.  (Four FP64 accumulators of 16 elements do not fit in registers.)
-// WAVE: every column transform lies within one wavefront, so its exchanges
-// order only that wavefront.
-template <typename R, int NY, bool QB, int NACC> struct ColCfg {
-    static constexpr bool WV = QB && NY == 1024 && (sizeof(R) == 4 || NACC <= 2);
-    static constexpr int CE = WV ? 16 : ((sizeof(R) == 8 && !QB) ? 4 : 8);
-    static constexpr int E = FftShape<NY, CE>::E;
-    static constexpr int P = FftShape<NY, CE>::P;
-    static constexpr int C = NY == 1 ? 64 : ((WV || P >= 128) ? 1 : 256 / P);
-    static constexpr int LMAX = WV ? 8 : ((sizeof(R) == 8 && !QB) ? 2 : 4);
-    static constexpr int FIT = 512 / (C * P);
-    // 1D grids: eight wavefront lanes share a tile's products (each "column"
-    // is one value, so a lane's rounds are one dependent load each)
-    static constexpr int PL = NY == 1 ? 8 : (FIT < 1 ? 1 : (FIT < LMAX ? FIT : LMAX));
-    static constexpr int THREADS = PL * C * P;
-    static constexpr bool WAVE = P <= 64;
-    // the next round's column is loaded during the current transform, except
-    // in FP64 wave lanes, whose registers cannot hold a second column (the
-    // other wavefront of the SIMD covers the load instead)
-    static constexpr bool PREFETCH = !(WV && sizeof(R) == 8);
-    // LDS: the transform exchange area of every lane and column (for 1D
-    // grids, whose "columns" are single values, one value per lane and column
-    // to combine the lanes' sums), then the mode-geometry table of C * Ky
-    // entries of 4 reals
-    static constexpr int XFORM = PL * C * fft_lds_elems<NY, E>();
-    static constexpr size_t lds_bytes(int Ky) {
-        return (size_t)XFORM * sizeof(typename cplx_of<R>::type) + (size_t)C * Ky * 4 * sizeof(R);
-    }
-    static constexpr bool keepable(int q) { return !QB || q < E / 4 || q >= E - E / 4; }
+template <typename R, int NY> struct ColShape {
+    using V = typename cplx_of<R>::type;
+    static constexpr int S = NY <= 512 ? 1 : NY / 512;
+    static constexpr int NH = NY / S;
+    static constexpr int E = FftShape<NH>::E;
+    static constexpr int P = NH / E;
+    static constexpr int CW = 64 / P;   // columns per workgroup
+    static constexpr int REG = fft_lds_elems<NH, E>();
+    // a wavefront's LDS area; the areas of the S classes of a column start
+    // 256 / S bytes apart modulo the banks, so that consecutive modes, which
+    // alternate between the classes, are read without conflicts
+    static constexpr int AREA = CW * REG + (S > 1 ? 256 / S / (int)sizeof(V) : 0);
+    // wavefronts of a workgroup at most: twelve leave each thread 168 registers,
+    // enough to hold the next round's column in FP64
+    static constexpr int WMAX = 12;
+    // kept modes per owner thread when all of a column's are kept (1 below 1024
+    // rows; quarter bands of 1024 rows take 1 as well)
+    static constexpr int ITMAX = (CW * (NY - 1) + 64 * WMAX - 1) / (64 * WMAX);
+    static_assert(WMAX % S == 0 && WMAX * AREA * sizeof(V) + 4096 <= kMaxLdsBytes, "the workgroup's LDS");
 };
-
 
 // Sweep control of a column pass: decides the solve from the previous
 // sweep's residual (false: this launch has nothing to do) and gives the
@@ -876,88 +881,95 @@ __device__ __forceinline__ bool col_control(const ColParams& p, Ctl* ctl, bool l
     return true;
 }
 
-// Stage a column pass's term table and the geometry of its C columns' kept
-// modes in LDS: geo[(c * Ky + r) * 4 + {0, 1, 2, 3}] = {k, tanh(k h), sech(k h),
-// k_y} (the caller synchronises).
+// geometry of one kept mode
+template <typename R> struct ColGeo {
+    R k, T, S, kx, ky;
+};
+// (mx, r): column and compact row; T = tanh(kh) and S = sech(kh) only when
+// the pass uses them
 template <typename R>
-__device__ __forceinline__ void col_stage_tables(const ColParams& p, int x0, int C, double href, R* geo_all,
-                                                 ColTerm* s_term, short* s_toff) {
+__device__ __forceinline__ ColGeo<R> col_geo(const ColParams& p, int mx, int r, double href) {
     const GridDev& g = p.g;
-    const int t = threadIdx.x;
-    for (int i = t; i < p.nterm; i += blockDim.x) s_term[i] = p.term[i];
-    for (int i = t; i <= p.nprod + p.ncin; i += blockDim.x) s_toff[i] = p.toff[i];
-    for (int idx = t; idx < C * g.Ky; idx += blockDim.x) {
-        const int c2 = idx / g.Ky, r2 = idx % g.Ky;
-        const int my = r2 <= g.My ? r2 : r2 - g.Ky;
-        const double kx2 = 2.0 * M_PI * (double)(x0 + c2) / g.lx;
-        const double ky = (g.ny == 1) ? 0.0 : 2.0 * M_PI * (double)my / g.ly;
-        const double k = sqrt(kx2 * kx2 + ky * ky);
-        R* gq = geo_all + idx * 4;
-        gq[0] = R(k);
-        gq[1] = R(tanh(k * href));
-        gq[2] = R(sech_d(k * href));
-        gq[3] = R(ky);
+    const int my = r <= g.My ? r : r - g.Ky;
+    const double kx = 2.0 * M_PI * (double)mx / g.lx;
+    const double ky = (g.ny == 1) ? 0.0 : 2.0 * M_PI * (double)my / g.ly;
+    const double k = sqrt(kx * kx + ky * ky);
+    ColGeo<R> o;
+    o.k = R(k);
+    o.T = o.S = R(1);
+    if (p.hyper) {
+        o.T = R(tanh(k * href));
+        o.S = R(sech_d(k * href));
     }
+    o.kx = R(kx);
+    o.ky = R(ky);
+    return o;
 }
 
-// multiplier sum of one source into the accumulators (kept modes only)
-// toff, term: the pass's term table, staged in LDS; geo: the column's mode
-// geometry (col_stage_tables)
-template <typename R, typename V, int E, int NACC>
-__device__ __forceinline__ void col_apply_terms(const short* toff, const ColTerm* term, int src, const V (&v)[E],
-                                                V (&acc)[NACC][E], const int (&crow)[E], const R* __restrict__ geo,
-                                                R kxr) {
-    // modes outer, terms inner: only one mode's geometry is live at a time
-    // (each accumulator still sums its terms in table order)
-    const int t0 = toff[src], t1 = toff[src + 1];
+// A pass's parameters are staged in LDS by one parallel load: read where they
+// are needed, each source's description would cost a dependent miss of the
+// scalar cache (the kernel arguments are new to it in every launch).
+__device__ __forceinline__ void col_stage(const ColParams& p, ColParams* sp) {
+    const int* src = reinterpret_cast<const int*>(&p);
+    int* dst = reinterpret_cast<int*>(sp);
+    for (int i = threadIdx.x; i < (int)(sizeof(ColParams) / 4); i += blockDim.x) dst[i] = src[i];
+}
+// a source's description; every thread reads the same one, so what steers
+// branches goes to scalar registers
+__device__ __forceinline__ ColSrc col_src(const ColSrc* s) {
+    ColSrc o = *s;
+    int ctl[2];
+    __builtin_memcpy(ctl, o.acc, 8);
+    ctl[0] = __builtin_amdgcn_readfirstlane(ctl[0]);
+    ctl[1] = __builtin_amdgcn_readfirstlane(ctl[1]);
+    __builtin_memcpy(o.acc, ctl, 8);
+    return o;
+}
+__device__ __forceinline__ int col_uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T> __device__ __forceinline__ T* col_uni(T* ptr) {
+    const unsigned long long a = (unsigned long long)ptr;
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32));
+    return reinterpret_cast<T*>(((unsigned long long)hi << 32) | lo);
+}
+
+// Adds a source's terms to the sums of one mode: acc[t.acc] += coef fn(k) k^pw
+// (i kx or i ky) val for its at most two terms (the branches are uniform).
+template <typename R, typename V, int NACC>
+__device__ __forceinline__ void col_add(const ColSrc& s, V val, V (&acc)[NACC], const ColGeo<R>& q) {
+    if (s.dv == DV_X) val = mul_i(cscale(val, q.kx));
+    else if (s.dv == DV_Y) val = mul_i(cscale(val, q.ky));
 #pragma unroll
-    for (int q = 0; q < E; ++q) {
-        if (crow[q] < 0) continue;
-        const R* gq = geo + crow[q] * 4;
-        const R kq = gq[0];
-        for (int ti = t0; ti < t1; ++ti) {
-            const ColTerm tm = term[ti];
-            R m = R(tm.coef);
-            if (tm.fn == FN_T) m *= gq[1];
-            else if (tm.fn == FN_S) m *= gq[2];
-            if (tm.pw >= 0) {
-                for (int e = 0; e < tm.pw; ++e) m *= kq;
-            } else {
-                m = kq > R(0) ? m / kq : R(0);
-            }
-            V val = cscale(v[q], m);
-            if (tm.dv == DV_X) val = mul_i(cscale(val, kxr));
-            else if (tm.dv == DV_Y) val = mul_i(cscale(val, gq[3]));
-#pragma unroll
-            for (int a = 0; a < NACC; ++a)
-                if (a == tm.acc) acc[a][q] = cadd(acc[a][q], val);
+    for (int t = 0; t < 2; ++t) {
+        if (s.acc[t] < 0) continue;
+        R m = R(s.coef[t]);
+        if (s.fn[t] == FN_T) m *= q.T;
+        else if (s.fn[t] == FN_S) m *= q.S;
+        const int pw = s.pw[t];
+        if (pw >= 0) {
+            for (int e = 0; e < pw; ++e) m *= q.k;
+        } else {
+            m = q.k > R(0) ? m / q.k : R(0);
         }
-    }
-}
-
-// value of output source `src` at the thread's mode q (crow >= 0)
-template <typename R, typename V, int E, int NACC>
-__device__ __forceinline__ V col_source(const ColParams& p, int src, int q, const V (&acc)[NACC][E], int crow,
-                                        int mem, int mx, double omega) {
-    if (src <= SRC_ACC3) {
-        V r = cx<V>(R(0), R(0));
 #pragma unroll
         for (int a = 0; a < NACC; ++a)
-            if (a == src) r = acc[a][q];
-        return r;
+            if (a == s.acc[t]) acc[a] = cx<V>(acc[a].x + val.x * m, acc[a].y + val.y * m);
     }
-    const int a = (src == SRC_NEW0 || src == SRC_DIFF0) ? 0 : 1;
-    V cur = cx<V>(R(0), R(0));
+}
+
+// value of output source `src` of one mode; pv: the previous iterates
+template <typename V, int NACC>
+__device__ __forceinline__ V col_source(int src, const V (&acc)[NACC], const V (&pv)[2], decltype(V::x) omega) {
+    const bool relaxed = src >= SRC_NEW0;
+    const int a = relaxed ? ((src == SRC_NEW0 || src == SRC_DIFF0) ? 0 : 1) : src;
+    V cur = cx<V>(0, 0);
 #pragma unroll
     for (int k = 0; k < NACC; ++k)
-        if (k == a) cur = acc[k][q];
-    V pv = cx<V>(R(0), R(0));
-    const int pi = p.relax_prev[a];
-    if (pi >= 0)
-        pv = static_cast<const V*>(p.cin[pi])[mem * p.g.s_cmp + (long long)mx * p.g.Ky + crow];
-    const V d = csub(cur, pv);
-    if (src == SRC_DIFF0 || src == SRC_DIFF1) return d;
-    return cadd(pv, cscale(d, R(omega)));
+        if (k == a) cur = acc[k];
+    if (!relaxed) return cur;
+    const V pq = a == 0 ? pv[0] : pv[1];
+    const V d = csub(cur, pq);
+    return src >= SRC_DIFF0 ? d : cadd(pq, cscale(d, omega));
 }
 
 // entry i of a register array, with i known only at run time: a chain of
@@ -1088,539 +1100,374 @@ static __device__ void aa_block_weights(const ColParams& p, Ctl* ctl, int mem, b
     __syncthreads();
 }
 
-// product lanes of a column-pass workgroup: independent thread groups that
-// transform alternate products of the same columns (more waves per CU to hide
-// memory latency); their partial sums are combined through LDS
-template <typename R, int NY, int NACC, bool QB>
-__global__ void __launch_bounds__((ColCfg<R, NY, QB, NACC>::THREADS))
-k_col(const ColParams p, const typename cplx_of<R>::type* __restrict__ twY) {
-    using V = typename cplx_of<R>::type;
-    using CF = ColCfg<R, NY, QB, NACC>;
-    constexpr int N = NY;
-    constexpr int CE = CF::CE;
-    constexpr int E = CF::E;
-    constexpr int P = CF::P;
-    constexpr int C = CF::C;
-    constexpr int PL = CF::PL;
-    constexpr int REG = fft_lds_elems<N, E>();  // LDS elements of one column transform
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    const int t = threadIdx.x;
-    // a lane is a whole number of wavefronts: make its index wave-uniform, so
-    // that the per-product parameters it selects are scalar loads (a vector
-    // load would also wait for the next product's prefetched column)
-    const int lane = (C * P) % 64 == 0 ? __builtin_amdgcn_readfirstlane(t / (C * P)) : t / (C * P);
-    const int tl = t % (C * P);
-    const int c = tl / P;  // column of the tile
-    const int j = tl % P;  // thread within the column
-    V* lds = reinterpret_cast<V*>(smem_raw) + (lane * C + c) * REG;
-    const int mem = blockIdx.z;
-    const int grp = blockIdx.y;
-    const int x0 = blockIdx.x * C;
-    const int mx = x0 + c;
-    const GridDev& g = p.g;
-    Ctl* ctl = p.ctl ? p.ctl + mem : nullptr;
-
-    double omega = 1.0;
-    if (!col_control(p, ctl, blockIdx.x == 0 && grp == 0 && t == 0, &omega)) return;
-    __shared__ double s_aa[(16 + 1) * kAASlots];  // wavefront sums, then the Anderson weights
-    if (p.aa_partial) aa_block_weights(p, ctl, mem, blockIdx.x == 0 && grp == 0, s_aa, s_aa + 16 * kAASlots);
-
-    Twid<V, N, E> twc;
-    twc.load(twY, j);
-
-    // mode geometry: the compact row of each value this thread owns (m_y index
-    // n = j + q P) and an LDS table of k, tanh(kh), sech(kh), k_y per kept mode
-    const double href = g.href[mem];
-    const double kx = 2.0 * M_PI * (double)mx / g.lx;
-    int crow[E];  // compact row, -1 if not kept
+// inner products of the residual history for the Anderson mixing, formed by
+// the sweep's own owners: d[i] += wt <F_i, f_n> of one mode over the ring slots
+// of sweep n (f: f_n's V and phi_b parts; the older ones are read back)
+template <typename V>
+__device__ __forceinline__ void col_aa_dots(const ColParams& p, const V (&f)[2], long long o, double wt,
+                                            double (&d)[kAASlots]) {
+    const int n = p.sweep, k = n < kAADepth ? n : kAADepth;
 #pragma unroll
-    for (int q = 0; q < E; ++q) {
-        const int n = j + q * P;
-        const int my = (n <= N / 2) ? n : n - N;
-        const bool keep = CF::keepable(q) && (mx < g.Kx) && (my <= g.My) && (my >= -g.My);
-        crow[q] = keep ? (my >= 0 ? my : my + g.Ky) : -1;
-    }
-    // the pass's term table in LDS: its per-product reads then wait on LDS
-    // only, never on the prefetched column in flight
-    __shared__ ColTerm s_term[kMaxTerms];
-    __shared__ short s_toff[kMaxProd + kMaxCin + 1];
-    R* geo_all = reinterpret_cast<R*>(reinterpret_cast<V*>(smem_raw) + CF::XFORM);
-    col_stage_tables<R>(p, x0, C, href, geo_all, s_term, s_toff);
-    __syncthreads();
-    const R* geo = geo_all + c * g.Ky * 4;
-    const R kxr = R(kx);
-
-    V acc[NACC][E];  // entries of modes that cannot be kept are never used
+    for (int part = 0; part < 2; ++part) {
+        if (part == 1 && !p.aa_f[1][0]) break;
+        const V f0 = f[part];
 #pragma unroll
-    for (int a = 0; a < NACC; ++a)
+        for (int j = 0; j <= kAADepth; ++j) {
+            if (j > k) break;
+            const int si = (n - j) % kAASlots;
+            const V fj = j == 0 ? f0 : static_cast<const V*>(p.aa_f[part][si])[o];
+            const double v = wt * ((double)fj.x * (double)f0.x + (double)fj.y * (double)f0.y);
 #pragma unroll
-        for (int q = 0; q < E; ++q) acc[a][q] = cx<V>(R(0), R(0));
-
-    // jobs of this workgroup: its products (forward column transforms), then,
-    // in the first product group only, the compact inputs, whose kept values
-    // enter the same multiplier sums without a transform.  Lane L takes jobs
-    // L, L + PL, ...; every lane runs the same number of rounds (slots that
-    // are not products transform zeros so that workgroup barriers line up,
-    // or skip the transform when it synchronises per wavefront).  The next
-    // round's column is loaded before the current transform runs.
-    const int s0 = p.ngroup > 1 ? p.gstart[grp] : 0;
-    const int s1 = p.ngroup > 1 ? p.gstart[grp + 1] : p.nprod;
-    const int nps = s1 - s0;
-    const int njob = nps + (grp == 0 ? p.ncin : 0);
-    const int rounds = (njob + PL - 1) / PL;
-    auto load_col = [&](int jb, V (&dst)[E]) __attribute__((always_inline)) {
-        if (jb < nps) {
-            const int s = s0 + jb;
-            const long long st = p.hin_stride[s] ? p.hin_stride[s] : g.s_half;
-            const V* H = static_cast<const V*>(p.hin[s]) + mem * st + (long long)mx * g.ldh;
-#pragma unroll
-            for (int q = 0; q < E; ++q) dst[q] = H[j + q * P];
-        } else {
-#pragma unroll
-            for (int q = 0; q < E; ++q) dst[q] = cx<V>(R(0), R(0));
-        }
-    };
-    V v[E];
-    if constexpr (CF::PREFETCH) {
-        if (rounds > 0) load_col(lane, v);
-    }
-    for (int rd = 0; rd < rounds; ++rd) {
-        const int jb = rd * PL + lane;
-        const bool prod = jb < nps;
-        const int src = prod ? s0 + jb : p.nprod + (jb - nps);  // row of the term table
-        const bool live = jb < njob && s_toff[src] < s_toff[src + 1];
-        V vn[E];
-        if constexpr (CF::PREFETCH) {
-            if (rd + 1 < rounds) load_col(jb + PL, vn);
-        } else {
-            if (CF::WAVE && jb >= njob) break;
-            load_col(jb, v);
-        }
-        if (prod || !CF::WAVE) fft<V, N, false, 1, CE, CF::WAVE>(v, lds, 0, j, twc);
-        if (live && !prod) {
-            const V* Ci = static_cast<const V*>(p.cin[jb - nps]) + mem * g.s_cmp + (long long)mx * g.Ky;
-            const int wi = p.cin_widx[jb - nps];
-            const R cw = wi >= 0 ? R(s_aa[16 * kAASlots + wi]) : R(1);
-#pragma unroll
-            for (int q = 0; q < E; ++q) v[q] = crow[q] >= 0 ? cscale(Ci[crow[q]], cw) : cx<V>(R(0), R(0));
-        }
-        if (live) col_apply_terms<R, V, E, NACC>(s_toff, s_term, src, v, acc, crow, geo, kxr);
-        if constexpr (CF::PREFETCH) {
-#pragma unroll
-            for (int q = 0; q < E; ++q) v[q] = vn[q];
-        }
-    }
-    // combine the lanes' partial sums into lane 0
-    if (PL > 1 && rounds > 0) {
-#pragma unroll
-        for (int a = 0; a < NACC; ++a) {
-            lds_sync();
-            if (lane > 0) {
-#pragma unroll
-                for (int q = 0; q < E; ++q)
-                    if (CF::keepable(q)) lds[j + q * P] = acc[a][q];
-            }
-            lds_sync();
-            if (lane == 0) {
-#pragma unroll
-                for (int l2 = 1; l2 < PL; ++l2) {
-                    const V* o = reinterpret_cast<const V*>(smem_raw) + (l2 * C + c) * REG;
-#pragma unroll
-                    for (int q = 0; q < E; ++q)
-                        if (CF::keepable(q)) acc[a][q] = cadd(acc[a][q], o[j + q * P]);
-                }
-            }
-        }
-    }
-    if (p.ngroup > 1) {
-        // publish this group's partial sums; the last workgroup of the tile
-        // continues with their sum in group order (deterministic)
-        V* part = static_cast<V*>(p.part);
-        const long long gs = (long long)g.Ky * g.Kxp;
-        if (lane == 0) {
-#pragma unroll
-            for (int a = 0; a < NACC; ++a)
-#pragma unroll
-                for (int q = 0; q < E; ++q)
-                    if (crow[q] >= 0)
-                        part[(((long long)mem * kMaxGroups + grp) * 4 + a) * gs + (long long)mx * g.Ky + crow[q]] =
-                            acc[a][q];
-        }
-        __shared__ int last_flag;
-        __threadfence();
-        __syncthreads();
-        if (t == 0) {
-            const int old = atomicAdd(&p.cnt[(long long)mem * kMaxTiles + blockIdx.x], 1);
-            last_flag = (old == p.ngroup - 1);
-        }
-        __syncthreads();
-        if (!last_flag) return;
-        __threadfence();
-        if (t == 0) p.cnt[(long long)mem * kMaxTiles + blockIdx.x] = 0;
-        if (lane == 0) {
-#pragma unroll
-            for (int a = 0; a < NACC; ++a)
-#pragma unroll
-                for (int q = 0; q < E; ++q) {
-                    if (!CF::keepable(q)) continue;
-                    V sum = cx<V>(R(0), R(0));
-                    if (crow[q] >= 0) {
-                        for (int gg = 0; gg < p.ngroup; ++gg) {
-                            const R* ps = reinterpret_cast<const R*>(
-                                part + (((long long)mem * kMaxGroups + gg) * 4 + a) * gs + (long long)mx * g.Ky +
-                                crow[q]);
-                            sum = cadd(sum,
-                                       cx<V>(__builtin_nontemporal_load(ps), __builtin_nontemporal_load(ps + 1)));
-                        }
-                    }
-                    acc[a][q] = sum;
-                }
-        }
-    }
-    // broadcast the final sums to every lane
-    if (PL > 1 && p.ninv > 1) {
-#pragma unroll
-        for (int a = 0; a < NACC; ++a) {
-            lds_sync();
-            if (lane == 0) {
-#pragma unroll
-                for (int q = 0; q < E; ++q)
-                    if (CF::keepable(q)) lds[j + q * P] = acc[a][q];
-            }
-            lds_sync();
-            if (lane > 0) {
-                const V* o = reinterpret_cast<const V*>(smem_raw) + c * REG;
-#pragma unroll
-                for (int q = 0; q < E; ++q)
-                    if (CF::keepable(q)) acc[a][q] = o[j + q * P];
-            }
-        }
-    }
-    // the exchange areas were last read across lanes (sums combined or
-    // broadcast): every lane is past those reads before it transforms again
-    if (PL > 1) lds_sync();
-    // inverse column transforms, spread over the lanes (before any compact
-    // output is written: NEW/DIFF sources re-read the previous iterate)
-    const int lanes_used = (PL > 1 && p.ninv > 1) ? PL : 1;
-    const int irounds = (p.ninv + lanes_used - 1) / lanes_used;
-    for (int rd = 0; rd < irounds; ++rd) {
-        const int o = rd * lanes_used + (lanes_used > 1 ? lane : 0);
-        const bool mine = (lanes_used > 1 || lane == 0) && o < p.ninv;
-        if (CF::WAVE && !mine) continue;
-        V vi[E];
-        const int src = mine ? p.inv_src[o] : 0;
-        const int dv = mine ? p.inv_dv[o] : 0;
-#pragma unroll
-        for (int q = 0; q < E; ++q) {
-            V sv = cx<V>(R(0), R(0));
-            if (mine && crow[q] >= 0) sv = col_source<R, V, E, NACC>(p, src, q, acc, crow[q], mem, mx, omega);
-            if (crow[q] >= 0) {
-                if (dv == DV_X) sv = mul_i(cscale(sv, kxr));
-                else if (dv == DV_Y) sv = mul_i(cscale(sv, geo[crow[q] * 4 + 3]));
-            }
-            vi[q] = sv;
-        }
-        fft<V, N, true, 1, CE, CF::WAVE>(vi, lds, 0, j, twc);
-        if (mine) {
-            V* G = static_cast<V*>(p.inv[o]) + mem * g.s_half + (long long)mx * g.ldh;
-#pragma unroll
-            for (int q = 0; q < E; ++q) G[j + q * P] = vi[q];
-        }
-    }
-    if (PL > 1) __syncthreads();  // inverse outputs (read prev) before compact outputs (write)
-    // compact outputs: the previous iterates the relaxed sources need are read
-    // before any output is written, so an output may overwrite an input of
-    // the same pass in place
-    if (lane == 0) {
-        V pv[2][E];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            const int pi = p.relax_prev[a];
-            const V* Pp = pi >= 0 ? static_cast<const V*>(p.cin[pi]) + mem * p.g.s_cmp + (long long)mx * p.g.Ky
-                                  : nullptr;
-#pragma unroll
-            for (int q = 0; q < E; ++q)
-                pv[a][q] = (Pp && crow[q] >= 0) ? Pp[crow[q]] : cx<V>(R(0), R(0));
-        }
-        for (int o = 0; o < p.ncout; ++o) {
-            const int src = p.cout_src[o];
-            const bool relaxed = src >= SRC_NEW0;
-            const int a = relaxed ? ((src == SRC_NEW0 || src == SRC_DIFF0) ? 0 : 1) : src;
-            const bool diff = src >= SRC_DIFF0;
-            V* out = static_cast<V*>(p.cout[o]) + mem * g.s_cmp + (long long)mx * g.Ky;
-#pragma unroll
-            for (int q = 0; q < E; ++q) {
-                if (crow[q] < 0) continue;
-                V cur = cx<V>(R(0), R(0));
-#pragma unroll
-                for (int k = 0; k < NACC; ++k)
-                    if (k == a) cur = acc[k][q];
-                V val = cur;
-                if (relaxed) {
-                    const V pq = a == 0 ? pv[0][q] : pv[1][q];
-                    const V d = csub(cur, pq);
-                    val = diff ? d : cadd(pq, cscale(d, R(omega)));
-                }
-                out[crow[q]] = val;
-            }
+            for (int i = 0; i < kAASlots; ++i)
+                if (i == si) d[i] += v;
         }
     }
 }
 
-// ---------------------------------------------------------------------------
-// Column pass in wave pairs (1024 rows, quarter band, at most two
-// accumulators, one product group).  Decimation in frequency splits a
-// 1024-point column transform into the 512-point transforms of its even and
-// odd outputs: wave 0 of a pair transforms u0[n] = x[n] + x[n + 512] and
-// wave 1 u1[n] = (x[n] - x[n + 512]) W^n, W = exp(-2 pi i / 1024), so that
-// X[2k] = U0[k] and X[2k + 1] = U1[k].  Both waves read the whole column (the
-// second read is served by the cache) and transform with wave-level
-// ordering only; a thread of wave h holds the modes 2 (j + 64 q) + h.  The
-// inverse runs the other way: each wave inverts its half of the modes, the
-// odd half is multiplied by W^-n, and the pair forms x[n] = e[n] + o[n] and
-// x[n + 512] = e[n] - o[n] through LDS.  Seven pairs (14 wavefronts, at most
-// 128 registers each) share the workgroup of one column.
-// ---------------------------------------------------------------------------
-struct ColPairCfg {
-    static constexpr int N = 1024, NH = 512, E = 8, P = 64;
-    static constexpr int PL = 7;
-    static constexpr int THREADS = PL * 2 * P;
-    static constexpr int REG = fft_lds_elems<NH, E>();  // LDS elements of one wave's exchange area
-    static constexpr bool keepable(int q) { return q < E / 4 || q >= E - E / 4; }
-    template <typename R> static constexpr size_t lds_bytes(int Ky) {
-        return (size_t)PL * 2 * REG * sizeof(typename cplx_of<R>::type) + (size_t)Ky * 4 * sizeof(R);
-    }
-};
-
-template <typename R, int NACC>
-__global__ void __launch_bounds__(ColPairCfg::THREADS)
-k_colp(const ColParams p, const typename cplx_of<R>::type* __restrict__ twY) {
-    using V = typename cplx_of<R>::type;
-    using CF = ColPairCfg;
-    constexpr int N = CF::N, NH = CF::NH, E = CF::E, P = CF::P, PL = CF::PL, REG = CF::REG;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    const int t = threadIdx.x;
-    const int wv = __builtin_amdgcn_readfirstlane(t / P);
-    const int lane = wv >> 1;  // pair
-    const int h = wv & 1;      // 0: even outputs, 1: odd outputs
-    const int j = t % P;
-    V* const xch = reinterpret_cast<V*>(smem_raw);
-    V* lds = xch + wv * REG;
-    const int mem = blockIdx.z;
-    const int mx = blockIdx.x;
-    const GridDev& g = p.g;
-    Ctl* ctl = p.ctl ? p.ctl + mem : nullptr;
-
-    // tables and twiddles are requested before the sweep decision, whose
-    // chain of dependent control reads then overlaps them; a launch after
-    // the member's solve was decided returns before any table work
-    Twid<V, NH, E> twc;
-    twc.load(twY, j, 2);  // the 512-point twiddles are every other 1024-point one
-    if (p.ctl_mode == CTL_SWEEP && ctl->done) return;
-    const double href = g.href[mem];
-    const double kx = 2.0 * M_PI * (double)mx / g.lx;
-    int crow[E];  // compact row of mode 2 (j + qP) + h, -1 if not kept
+// block sums of d -> out[0 .. kAASlots) (fixed order; s_red: kAASlots per wavefront)
+__device__ __forceinline__ void col_aa_reduce(double (&d)[kAASlots], double* s_red, double* out) {
 #pragma unroll
-    for (int q = 0; q < E; ++q) {
-        const int n = 2 * (j + q * P) + h;
-        const int my = (n <= N / 2) ? n : n - N;
-        const bool keep = CF::keepable(q) && (mx < g.Kx) && (my <= g.My) && (my >= -g.My);
-        crow[q] = keep ? (my >= 0 ? my : my + g.Ky) : -1;
+    for (int i = 0; i < kAASlots; ++i)
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) d[i] += __shfl_xor(d[i], off, 64);
+    const int wv = threadIdx.x / 64, nw = blockDim.x / 64;
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int i = 0; i < kAASlots; ++i) s_red[wv * kAASlots + i] = d[i];
+    lds_sync();
+    if (threadIdx.x < kAASlots) {
+        double v = 0.0;
+        for (int w = 0; w < nw; ++w) v += s_red[w * kAASlots + threadIdx.x];
+        out[threadIdx.x] = v;
     }
-    __shared__ ColTerm s_term[kMaxTerms];
-    __shared__ short s_toff[kMaxProd + kMaxCin + 1];
-    R* geo = reinterpret_cast<R*>(xch + PL * 2 * REG);
-    col_stage_tables<R>(p, mx, 1, href, geo, s_term, s_toff);
-    const V wj = twY[j], wP = twY[P];  // W^(j + qP) = W^j (W^P)^q
+}
+
+template <typename R, int NY, int NACC, int IT>
+__global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColParams p, const typename cplx_of<R>::type* __restrict__ twY) {
+    using CS = ColShape<R, NY>;
+    using V = typename CS::V;
+    constexpr int S = CS::S, NH = CS::NH, E = CS::E, P = CS::P, CW = CS::CW, REG = CS::REG, AREA = CS::AREA;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    __shared__ double s_aa[(16 + 1) * kAASlots];  // wavefront sums, then the Anderson weights
+    __shared__ ColParams sp;
+    V* const areas = reinterpret_cast<V*>(smem_raw);
+    const int t = threadIdx.x;
+    const int W = blockDim.x >> 6;                             // a multiple of S
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int ln = t & 63;
+    const int c = ln / P, j = ln % P;                          // column of the workgroup, thread of the column
+    const int h = S > 1 ? wv % S : 0;                          // class of modes of this wavefront
+    const int mem = blockIdx.z;
+    const int x0 = blockIdx.x * CW;
+    const GridDev& g = p.g;
+    const ColSub& sub = p.sub[blockIdx.y];
+    Ctl* ctl = p.ctl ? p.ctl + mem : nullptr;
+    if ((p.ctl_mode == CTL_SWEEP || p.ctl_mode == CTL_SKIP) && ctl->done) return;
+    col_stage(p, &sp);
+
+    const int np = sub.p1 - sub.p0;
+    const int njob = np * S;
+    const int rounds = (njob + W - 1) / W;
+    const int per = W / S;                                     // products per round
+    // column of job jb (product jb / S): the raw values of its thread
+    // (not for the largest columns in FP64: their registers hold a thread's several modes)
+    constexpr bool AHEAD = S == 1 || (S == 2 && IT == 1) || (S == 2 && sizeof(R) == 4);
+    V raw[AHEAD ? S : 1][E];
+    auto column = [&](int jb) __attribute__((always_inline)) {
+        return static_cast<const V*>(jb < W ? p.src[sub.p0 + jb / S].ptr : col_uni(sp.src[sub.p0 + jb / S].ptr)) + mem * g.s_half + (long long)(x0 + c) * g.ldh + j;
+    };
+    auto request = [&](int jb) __attribute__((always_inline)) {
+        if constexpr (AHEAD) {
+            const V* H = column(jb);
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int q = 0; q < E; ++q) raw[s][q] = H[q * P + s * NH];
+        }
+    };
+    if (wv < njob) request(wv);
+    Twid<V, NH, E> twc;
+    twc.load(twY, j, S);                                       // the NH-point twiddles: every S-th entry
+    V wn = cx<V>(R(1), R(0)), wq = wn;                         // W^(h j), W^(h P)
+    if constexpr (S > 1) {
+        wn = twY[h * j];
+        wq = twY[h * P];
+    }
+    // the owner's mode(s): entry i = t + it T of the workgroup's compact modes
+    const double href = g.href[mem];
+    ColGeo<R> geo[IT];
+    int slot[IT];          // element of the areas holding the mode: class area, column, transform index
+    int co[IT];            // compact offset from the workgroup's first column, -1: no mode
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int i = t + it * (int)blockDim.x;
+        const int c2 = i / g.Ky, r = i - c2 * g.Ky;
+        const bool on = c2 < CW && x0 + c2 < g.Kx;
+        const int n = r <= g.My ? r : r + NY - g.Ky;
+        co[it] = on ? i : -1;
+        slot[it] = (n % S) * AREA + c2 * REG + n / S;
+        geo[it] = col_geo<R>(p, x0 + c2, r, href);
+    }
+    const long long cb = mem * g.s_cmp + (long long)x0 * g.Ky;  // compact base of the workgroup
     double omega = 1.0;
     // the decision is the same in every thread (the leader's header updates
     // cannot change it), so the workgroup returns as a whole
-    if (!col_control(p, ctl, blockIdx.x == 0 && t == 0, &omega)) return;
-    __shared__ double s_aa[(16 + 1) * kAASlots];  // wavefront sums, then the Anderson weights
+    if (!col_control(p, ctl, blockIdx.x == 0 && blockIdx.y == 0 && t == 0, &omega)) return;
     if (p.aa_partial) aa_block_weights(p, ctl, mem, blockIdx.x == 0, s_aa, s_aa + 16 * kAASlots);
-    __syncthreads();
-    const R kxr = R(kx);
 
-    V acc[NACC][E];  // entries of modes that cannot be kept are never used
+    V acc[IT][NACC];
 #pragma unroll
-    for (int a = 0; a < NACC; ++a)
+    for (int it = 0; it < IT; ++it)
 #pragma unroll
-        for (int q = 0; q < E; ++q) acc[a][q] = cx<V>(R(0), R(0));
+        for (int a = 0; a < NACC; ++a) acc[it][a] = cx<V>(R(0), R(0));
+    V pv[IT][2];
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+            pv[it][a] = (p.prev[a] && co[it] >= 0) ? static_cast<const V*>(p.prev[a])[cb + co[it]] : cx<V>(R(0), R(0));
 
-    // jobs: the products (forward transforms), then the compact inputs; job
-    // jb is row jb of the term table.  Round rd deals jobs rd PL .. rd PL +
-    // PL - 1 to the pairs in alternating direction, so the cheap compact-input
-    // jobs of the last rounds go to pairs with fewer transforms.
-    const int nps = p.nprod;
-    const int njob = nps + p.ncin;
-    const int rounds = (njob + PL - 1) / PL;
+    V* const area = areas + wv * AREA;
+    lds_sync();  // the staged parameters: every wavefront's part of them is written
     for (int rd = 0; rd < rounds; ++rd) {
-        const int jb = rd * PL + ((rd & 1) ? PL - 1 - lane : lane);
-        if (jb >= njob) continue;
-        if (s_toff[jb] == s_toff[jb + 1]) continue;  // no term reads it
-        V v[E];
-        if (jb < nps) {
-            const long long st = p.hin_stride[jb] ? p.hin_stride[jb] : g.s_half;
-            const V* H = static_cast<const V*>(p.hin[jb]) + mem * st + (long long)mx * g.ldh;
-            if (h == 0) {
+        const int jb = rd * W + wv;
+        if (jb < njob) {
+            V v[E];
+            if constexpr (S == 1) {
 #pragma unroll
-                for (int q = 0; q < E; ++q) v[q] = cadd(H[j + q * P], H[j + q * P + NH]);
+                for (int q = 0; q < E; ++q) v[q] = raw[0][q];
             } else {
-                V w = wj;
-                asm volatile("" : "+v"(w.x), "+v"(w.y));  // powers formed here, not held across rounds
+                if constexpr (AHEAD) {
+                    if (h == 0) {
 #pragma unroll
-                for (int q = 0; q < E; ++q) {
-                    v[q] = cmul(csub(H[j + q * P], H[j + q * P + NH]), w);
-                    w = cmul(w, wP);
+                        for (int q = 0; q < E; ++q) v[q] = cadd(raw[0][q], raw[1][q]);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < E; ++q) v[q] = csub(raw[0][q], raw[1][q]);
+                    }
+                } else {
+                    const V* H = column(jb);
+#pragma unroll
+                    for (int q = 0; q < E; ++q) v[q] = H[q * P];
+#pragma unroll 1
+                    for (int s = 1; s < S; ++s) {
+                        const int rot = S == 2 ? 2 * (h * s) : (h * s) & 3;  // times (-i)^(...)
+#pragma unroll
+                        for (int q = 0; q < E; ++q) {
+                            const V x = H[q * P + s * NH];
+                            const V y = rot == 0 ? x : (rot == 1 ? mul_mi<false>(x)
+                                                                 : (rot == 2 ? cx<V>(-x.x, -x.y) : mul_i(x)));
+                            v[q] = cadd(v[q], y);
+                        }
+                    }
+                }
+                if (h > 0) {
+                    V w = wn;
+                    asm volatile("" : "+v"(w.x), "+v"(w.y));  // powers formed here, not held across rounds
+#pragma unroll
+                    for (int q = 0; q < E; ++q) {
+                        v[q] = cmul(v[q], w);
+                        w = cmul(w, wq);
+                    }
                 }
             }
-            fft<V, NH, false, 1, E, true>(v, lds, 0, j, twc);
-        } else {
-            const V* Ci = static_cast<const V*>(p.cin[jb - nps]) + mem * g.s_cmp + (long long)mx * g.Ky;
-            const int wi = p.cin_widx[jb - nps];
-            const R cw = wi >= 0 ? R(s_aa[16 * kAASlots + wi]) : R(1);
+            fft<V, NH, false, 1, E, true>(v, area + c * REG, 0, j, twc);
+            wave_lds_sync();
 #pragma unroll
-            for (int q = 0; q < E; ++q) v[q] = crow[q] >= 0 ? cscale(Ci[crow[q]], cw) : cx<V>(R(0), R(0));
+            for (int q = 0; q < E; ++q) area[c * REG + j + q * P] = v[q];
         }
-        col_apply_terms<R, V, E, NACC>(s_toff, s_term, jb, v, acc, crow, geo, kxr);
+        if (jb + W < njob) request(jb + W);
+        lds_sync();
+        const int s0 = rd * per, s1 = min(np, s0 + per);
+#pragma unroll 2
+        for (int s = s0; s < s1; ++s) {
+            const ColSrc src = col_src(&sp.src[sub.p0 + s]);
+#pragma unroll
+            for (int it = 0; it < IT; ++it)
+                if (co[it] >= 0) col_add<R, V, NACC>(src, areas[(s - s0) * S * AREA + slot[it]], acc[it], geo[it]);
+        }
+        lds_sync();
     }
-    // combine the pairs' partial sums into pair 0 (the same half of every pair
-    // holds the same modes), every accumulator in one exchange: the kept slots
-    // of NACC <= 2 accumulators fill NACC * E/2 * P <= 512 of an area's slots
-    static_assert(NACC * (E / 2) * P <= REG, "the accumulators exceed an exchange area");
-    auto slot = [&](int a, int q) { return (a * (E / 2) + (q < E / 4 ? q : q - E / 2)) * P + j; };
-    if (rounds > 0) {
-        lds_sync();
-        if (lane > 0) {
+#pragma unroll 2
+    for (int s = sub.c0; s < sub.c1; ++s) {
+        const ColSrc src = col_src(&sp.src[kMaxProd + s]);
+        const R cw = src.widx >= 0 ? R(s_aa[16 * kAASlots + src.widx]) : R(1);
 #pragma unroll
-            for (int a = 0; a < NACC; ++a)
+        for (int it = 0; it < IT; ++it)
+            if (co[it] >= 0)
+                col_add<R, V, NACC>(src, cscale(static_cast<const V*>(col_uni(src.ptr))[cb + co[it]], cw), acc[it],
+                                    geo[it]);
+    }
+
+    // inverse column transforms, W / S outputs a round
+    V* const ownarea = areas;
+    const int ninv = sub.i1 - sub.i0;
+    for (int o0 = 0; o0 < ninv; o0 += per) {
+        if (o0 > 0) lds_sync();  // the last round's areas have been read
+        const int on = min(per, ninv - o0);
+        for (int o = 0; o < on; ++o) {
+            const int isrc = col_uni(sp.inv_src[sub.i0 + o0 + o]), dv = col_uni(sp.inv_dv[sub.i0 + o0 + o]);
 #pragma unroll
-                for (int q = 0; q < E; ++q)
-                    if (CF::keepable(q)) lds[slot(a, q)] = acc[a][q];
-        }
-        lds_sync();
-        if (lane == 0) {
-#pragma unroll
-            for (int l2 = 1; l2 < PL; ++l2) {
-                const V* o = xch + (2 * l2 + h) * REG;
-#pragma unroll
-                for (int a = 0; a < NACC; ++a)
-#pragma unroll
-                    for (int q = 0; q < E; ++q)
-                        if (CF::keepable(q)) acc[a][q] = cadd(acc[a][q], o[slot(a, q)]);
+            for (int it = 0; it < IT; ++it) {
+                if (co[it] < 0) continue;
+                V sv = col_source<V, NACC>(isrc, acc[it], pv[it], R(omega));
+                if (dv == DV_X) sv = mul_i(cscale(sv, geo[it].kx));
+                else if (dv == DV_Y) sv = mul_i(cscale(sv, geo[it].ky));
+                ownarea[o * S * AREA + slot[it]] = sv;
             }
         }
-    }
-    // broadcast the final sums to every pair
-    if (p.ninv > 1) {
         lds_sync();
-        if (lane == 0) {
-#pragma unroll
-            for (int a = 0; a < NACC; ++a)
-#pragma unroll
-                for (int q = 0; q < E; ++q)
-                    if (CF::keepable(q)) lds[slot(a, q)] = acc[a][q];
-        }
-        lds_sync();
-        if (lane > 0) {
-            const V* o = xch + h * REG;
-#pragma unroll
-            for (int a = 0; a < NACC; ++a)
-#pragma unroll
-                for (int q = 0; q < E; ++q)
-                    if (CF::keepable(q)) acc[a][q] = o[slot(a, q)];
-        }
-    }
-    lds_sync();  // every pair is past the reads above before the areas are reused
-    // compact outputs, mode by mode: a mode's previous iterates are read before
-    // any output of that mode is written, so an output may overwrite an input
-    // of the same pass in place
-    auto compact_outputs = [&]() __attribute__((always_inline)) {
-        const long long co = mem * g.s_cmp + (long long)mx * g.Ky;
-        const V* P0 = p.relax_prev[0] >= 0 ? static_cast<const V*>(p.cin[p.relax_prev[0]]) + co : nullptr;
-        const V* P1 = p.relax_prev[1] >= 0 ? static_cast<const V*>(p.cin[p.relax_prev[1]]) + co : nullptr;
-#pragma unroll
-        for (int q = 0; q < E; ++q) {
-            if (crow[q] < 0) continue;
-            const V pv0 = P0 ? P0[crow[q]] : cx<V>(R(0), R(0));
-            const V pv1 = P1 ? P1[crow[q]] : cx<V>(R(0), R(0));
-            for (int o = 0; o < p.ncout; ++o) {
-                const int src = p.cout_src[o];
-                const bool relaxed = src >= SRC_NEW0;
-                const int a = relaxed ? ((src == SRC_NEW0 || src == SRC_DIFF0) ? 0 : 1) : src;
-                V cur = cx<V>(R(0), R(0));
-#pragma unroll
-                for (int k = 0; k < NACC; ++k)
-                    if (k == a) cur = acc[k][q];
-                V val = cur;
-                if (relaxed) {
-                    const V pq = a == 0 ? pv0 : pv1;
-                    const V d = csub(cur, pq);
-                    val = src >= SRC_DIFF0 ? d : cadd(pq, cscale(d, R(omega)));
-                }
-                static_cast<V*>(p.cout[o])[co + crow[q]] = val;
-            }
-        }
-    };
-    // inverse column transforms of the outputs, one per pair and round.  When
-    // they take a single round and leave a pair idle (which then holds the
-    // broadcast sums too), that pair writes the compact outputs while the
-    // others transform, once every pair has read the previous iterates its
-    // sources need; otherwise pair 0 writes them at the end.
-    const int lanes_used = p.ninv > 1 ? PL : 1;
-    const int irounds = (p.ninv + lanes_used - 1) / lanes_used;
-    const bool overlap = p.ninv > 1 && irounds == 1 && p.ninv < PL;
-    for (int rd = 0; rd < irounds; ++rd) {
-        const int o = rd * lanes_used + (lanes_used > 1 ? lane : 0);
-        const bool mine = (lanes_used > 1 || lane == 0) && o < p.ninv;
+        const int o = wv / S;
         V v[E];
-        if (mine) {
-            const int isrc = p.inv_src[o], dv = p.inv_dv[o];
+        if (o < on) {
 #pragma unroll
             for (int q = 0; q < E; ++q) {
-                V sv = cx<V>(R(0), R(0));
-                if (crow[q] >= 0) {
-                    sv = col_source<R, V, E, NACC>(p, isrc, q, acc, crow[q], mem, mx, omega);
-                    if (dv == DV_X) sv = mul_i(cscale(sv, kxr));
-                    else if (dv == DV_Y) sv = mul_i(cscale(sv, geo[crow[q] * 4 + 3]));
+                const int n = S * (j + q * P) + h;
+                const int my = n <= NY / 2 ? n : n - NY;
+                const bool keep = x0 + c < g.Kx && my <= g.My && my >= -g.My;
+                v[q] = keep ? area[c * REG + j + q * P] : cx<V>(R(0), R(0));
+            }
+            wave_lds_sync();
+            fft<V, NH, true, 1, E, true>(v, area + c * REG, 0, j, twc);
+            if constexpr (S > 1) {
+                if (h > 0) {
+                    V w = cconj(wn);
+                    asm volatile("" : "+v"(w.x), "+v"(w.y));
+                    const V wc = cconj(wq);
+#pragma unroll
+                    for (int q = 0; q < E; ++q) {
+                        v[q] = cmul(v[q], w);
+                        w = cmul(w, wc);
+                    }
                 }
-                v[q] = sv;
+                wave_lds_sync();
+#pragma unroll
+                for (int q = 0; q < E; ++q) area[j + q * P] = v[q];
             }
         }
-        if (overlap) {
-            __syncthreads();  // every source above has been formed from the previous iterates
-            if (lane == PL - 1) compact_outputs();
-        }
-        if (mine) {
-            fft<V, NH, true, 1, E, true>(v, lds, 0, j, twc);
-            if (h == 1) {
-                V w = cconj(wj);
-                asm volatile("" : "+v"(w.x), "+v"(w.y));
-                const V wPc = cconj(wP);
+        if constexpr (S > 1) {
+            lds_sync();
+            if (o < on) {
+                const V* const e = areas + o * S * AREA;
 #pragma unroll
                 for (int q = 0; q < E; ++q) {
-                    v[q] = cmul(v[q], w);
-                    w = cmul(w, wPc);
+                    const int n = j + q * P;
+                    V x = e[n];
+#pragma unroll
+                    for (int s = 1; s < S; ++s) {
+                        const int rot = S == 2 ? 2 * ((h * s) & 1) : (h * s) & 3;  // times i^(...)
+                        const V y = e[s * AREA + n];
+                        x = cadd(x, rot == 0 ? y : (rot == 1 ? mul_i(y) : (rot == 2 ? cx<V>(-y.x, -y.y) : mul_mi<false>(y))));
+                    }
+                    v[q] = x;
                 }
             }
-#pragma unroll
-            for (int q = 0; q < E; ++q) lds[j + q * P] = v[q];
         }
-        lds_sync();
-        if (mine) {
-            const V* ev = xch + (2 * lane) * REG;
-            const V* od = xch + (2 * lane + 1) * REG;
-            V* G = static_cast<V*>(p.inv[o]) + mem * g.s_half + (long long)mx * g.ldh + h * NH;
+        if (o < on) {
+            V* G = static_cast<V*>(col_uni(sp.inv[sub.i0 + o0 + o])) + mem * g.s_half + (long long)(x0 + c) * g.ldh + h * NH + j;
 #pragma unroll
-            for (int q = 0; q < E; ++q) {
-                const int n = j + q * P;
-                G[n] = h == 0 ? cadd(ev[n], od[n]) : csub(ev[n], od[n]);
-            }
+            for (int q = 0; q < E; ++q) G[q * P] = v[q];
         }
-        lds_sync();
     }
-    // every inverse transform above has read its sources (the last barrier)
-    if (!overlap && lane == 0) compact_outputs();
+    // compact outputs: a mode's inputs were all read by its owner, so an output
+    // may overwrite an input of the same pass
+    for (int o = sub.o0; o < sub.o1; ++o) {
+        V* const out = static_cast<V*>(col_uni(sp.cout[o])) + cb;
+        const int src = col_uni(sp.cout_src[o]);
+#pragma unroll
+        for (int it = 0; it < IT; ++it)
+            if (co[it] >= 0) out[co[it]] = col_source<V, NACC>(src, acc[it], pv[it], R(omega));
+    }
+    if (p.aa_dots) {
+        double d[kAASlots];
+#pragma unroll
+        for (int i = 0; i < kAASlots; ++i) d[i] = 0.0;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            if (co[it] < 0) continue;
+            const V f[2] = {col_source<V, NACC>(SRC_DIFF0, acc[it], pv[it], R(1)),
+                            col_source<V, NACC>(SRC_DIFF1, acc[it], pv[it], R(1))};
+            const int mx = x0 + co[it] / g.Ky;
+            col_aa_dots<V>(p, f, cb + co[it], mx == 0 ? 1.0 : 2.0, d);
+        }
+        col_aa_reduce(d, s_aa, p.aa_dots + ((long long)mem * gridDim.x + blockIdx.x) * kAASlots);
+    }
+}
+
+// Column pass of one-dimensional grids: a "column" is one mode, so a thread
+// reads its mode of a source itself.  Bound by the latency of one chain (control
+// header, parameters, loads, sums, store); the sources are shared by up to
+// eight wavefronts whose partial sums meet in LDS.
+constexpr int kCol1Waves = 8;
+template <typename R, int NACC>
+__global__ void __launch_bounds__(64 * kCol1Waves) k_col1(const ColParams p) {
+    using V = typename cplx_of<R>::type;
+    __shared__ double s_aa[(16 + 1) * kAASlots];
+    __shared__ ColParams sp;
+    __shared__ V sums[kCol1Waves - 1][NACC][64];
+    const int t = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
+    const int mem = blockIdx.z;
+    const int mx = blockIdx.x * 64 + t;
+    const GridDev& g = p.g;
+    const ColSub& sub = p.sub[blockIdx.y];
+    Ctl* ctl = p.ctl ? p.ctl + mem : nullptr;
+    if ((p.ctl_mode == CTL_SWEEP || p.ctl_mode == CTL_SKIP) && ctl->done) return;
+    col_stage(p, &sp);
+    const bool on = mx < g.Kx;
+    const long long cb = mem * g.s_cmp + mx, hb = mem * g.s_half + mx;
+    const V zero = cx<V>(R(0), R(0));
+    V pv[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) pv[a] = (p.prev[a] && on) ? static_cast<const V*>(p.prev[a])[cb] : zero;
+    const ColGeo<R> geo = col_geo<R>(p, mx, 0, g.href[mem]);
+    double omega = 1.0;
+    if (!col_control(p, ctl, blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0, &omega)) return;
+    if (p.aa_partial) aa_block_weights(p, ctl, mem, blockIdx.x == 0, s_aa, s_aa + 16 * kAASlots);
+    lds_sync();
+    V acc[NACC];
+#pragma unroll
+    for (int a = 0; a < NACC; ++a) acc[a] = zero;
+    const int np = sub.p1 - sub.p0, ns = np + sub.c1 - sub.c0;
+#pragma unroll 2
+    for (int s = wv; s < ns; s += W) {
+        const bool prod = s < np;
+        const ColSrc src = col_src(&sp.src[prod ? sub.p0 + s : kMaxProd + sub.c0 + s - np]);
+        V val = on ? static_cast<const V*>(col_uni(src.ptr))[prod ? hb : cb] : zero;
+        if (src.widx >= 0) val = cscale(val, R(s_aa[16 * kAASlots + src.widx]));
+        col_add<R, V, NACC>(src, val, acc, geo);
+    }
+    if (W > 1) {
+        if (wv > 0)
+#pragma unroll
+            for (int a = 0; a < NACC; ++a) sums[wv - 1][a][t] = acc[a];
+        lds_sync();
+        if (wv == 0)
+            for (int w = 1; w < W; ++w)
+#pragma unroll
+                for (int a = 0; a < NACC; ++a) acc[a] = cadd(acc[a], sums[w - 1][a][t]);
+    }
+    if (wv == 0 && on) {
+        for (int o = sub.i0; o < sub.i1; ++o) {
+            V sv = col_source<V, NACC>(col_uni(sp.inv_src[o]), acc, pv, R(omega));
+            const int dv = col_uni(sp.inv_dv[o]);
+            if (dv == DV_X) sv = mul_i(cscale(sv, geo.kx));
+            else if (dv == DV_Y) sv = zero;
+            static_cast<V*>(col_uni(sp.inv[o]))[hb] = sv;
+        }
+        for (int o = sub.o0; o < sub.o1; ++o)
+            static_cast<V*>(col_uni(sp.cout[o]))[cb] = col_source<V, NACC>(col_uni(sp.cout_src[o]), acc, pv, R(omega));
+    }
+    if (p.aa_dots) {
+        double d[kAASlots];
+#pragma unroll
+        for (int i = 0; i < kAASlots; ++i) d[i] = 0.0;
+        if (wv == 0 && on) {
+            const V f[2] = {col_source<V, NACC>(SRC_DIFF0, acc, pv, R(1)), col_source<V, NACC>(SRC_DIFF1, acc, pv, R(1))};
+            col_aa_dots<V>(p, f, cb, mx == 0 ? 1.0 : 2.0, d);
+        }
+        col_aa_reduce(d, s_aa, p.aa_dots + ((long long)mem * gridDim.x + blockIdx.x) * kAASlots);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1856,71 +1703,6 @@ __global__ void k_rk54(const Rk54Params p) {
     }
 }
 
-// ---------------------------------------------------------------------------
-// Anderson mixing of the relaxed sweep (iteration mode)
-// ---------------------------------------------------------------------------
-// The sweep's column pass stores f_n = T(x_n) - x_n and g_n = x_n + omega f_n
-// in ring slot n mod kAASlots; k_aa_dot forms per-workgroup partial sums of
-// <F_i, f_n> over the k + 1 = min(n, kAADepth) + 1 history slots (real inner
-// product of the real fields: half-spectrum modes weighted 2 for m_x > 0).
-// The column pass that forms the next iterate adds them and solves for its
-// weights in every workgroup (aa_block_weights).
-template <typename R>
-__global__ void __launch_bounds__(kAADotThreads) k_aa_dot(const AaParams p) {
-    using V = typename cplx_of<R>::type;
-    __shared__ double red[kAASlots][16];
-    const int mem = blockIdx.y;
-    const Ctl* ctl = p.ctl + mem;
-    if (ctl->done) return;
-    const GridDev& g = p.g;
-    const int n = p.sweep, k = n < kAADepth ? n : kAADepth;
-    const int ncmp = (int)g.s_cmp;
-    double d[kAASlots];
-#pragma unroll
-    for (int i = 0; i < kAASlots; ++i) d[i] = 0.0;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < ncmp; idx += gridDim.x * blockDim.x) {
-        const int mx = idx / g.Ky;
-        if (mx >= g.Kx) continue;
-        const long long o = mem * g.s_cmp + idx;
-        const double wt = mx == 0 ? 1.0 : 2.0;
-#pragma unroll
-        for (int part = 0; part < 2; ++part) {
-            if (part == 1 && !p.vd) break;
-            V fo[kAASlots];
-#pragma unroll
-            for (int j = 0; j <= kAADepth; ++j)
-                if (j <= k) {
-                    const int si = (n - j) % kAASlots;
-                    fo[j] = static_cast<const V*>(part ? p.fb[si] : p.fv[si])[o];
-                }
-#pragma unroll
-            for (int j = 0; j <= kAADepth; ++j) {
-                if (j > k) break;
-                const int si = (n - j) % kAASlots;
-                const double v = wt * ((double)fo[j].x * (double)fo[0].x + (double)fo[j].y * (double)fo[0].y);
-#pragma unroll
-                for (int i = 0; i < kAASlots; ++i)
-                    if (i == si) d[i] += v;
-            }
-        }
-    }
-    // across the wavefront, then wavefront by wavefront (<= 16 of them)
-#pragma unroll
-    for (int i = 0; i < kAASlots; ++i)
-        for (int off = 32; off > 0; off >>= 1) d[i] += __shfl_xor(d[i], off, 64);
-    const int wv = threadIdx.x / 64;
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-        for (int i = 0; i < kAASlots; ++i) red[i][wv] = d[i];
-    __syncthreads();
-    if (threadIdx.x < kAASlots) {
-        double v = 0.0;
-        const int nw = (blockDim.x + 63) / 64;
-        for (int w = 0; w < nw; ++w) v += red[threadIdx.x][w];
-        p.partial[((long long)mem * p.nblk + blockIdx.x) * kAASlots + threadIdx.x] = v;
-    }
-}
-
 template <typename R>
 __global__ void k_diag(const DiagParams p) {
     using V = typename cplx_of<R>::type;
@@ -2067,41 +1849,65 @@ SBI_ROW_LAUNCH(k_row_nphi_tank, RowNphiParams)
 SBI_ROW_LAUNCH(k_row_blend, RowBlendParams)
 SBI_ROW_LAUNCH(k_row_feat, RowFeatParams)
 
-template <typename R, int NY, int NACC, bool QB>
-static hipError_t col_go(const ColParams& p, int batch, const Twiddles& tw, hipStream_t s) {
-    using V = typename cplx_of<R>::type;
-    using CF = ColCfg<R, NY, QB, NACC>;
-    if (p.g.col_C != CF::C) return hipErrorInvalidValue;  // the layout was made for another tile
-    dim3 block(CF::THREADS);
-    dim3 grid(p.g.Kxp / CF::C, p.ngroup > 0 ? p.ngroup : 1, batch);
-    const size_t lds = CF::lds_bytes(p.g.Ky);
-    if (lds > kMaxLdsBytes) return hipErrorInvalidValue;
-    if constexpr (NY == 1024 && QB && NACC <= 2) {
-        if (p.ngroup <= 1) {
-            const size_t lp = ColPairCfg::lds_bytes<R>(p.g.Ky);
-            if (lp > kMaxLdsBytes) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((k_colp<R, NACC>), dim3(p.g.Kxp, 1, batch), dim3(ColPairCfg::THREADS), lp, s, p,
-                               (const V*)tw.ty);
-            return hipGetLastError();
-        }
+// Wavefronts of a column-pass workgroup: one per column transform of a round,
+// as few as the same number of rounds takes, and enough to own every kept
+// mode.  Few workgroups (up to one per CU) take up to twelve, so that a
+// workgroup's chain is short; more of them hide each other's barriers, and
+// smaller workgroups then pack the CU better.  Measured with at most 4 / 8 / 12
+// wavefronts: 96 ragged FP32 members (6656 workgroups a pass) 7.9 / 8.8 / 9.3 ms
+// per step; two 1024 x 1024 FP64 members (512) 5.9 / 5.7 / 6.0; one 512 x 512
+// member (128) 0.67 / 0.65 / 0.65.
+template <typename R, int NY> static int col_waves(const ColParams& p, int batch) {
+    using CS = ColShape<R, NY>;
+    int np = 0, ni = 0;
+    for (int s = 0; s < p.nsub; ++s) {
+        np = std::max(np, (int)(p.sub[s].p1 - p.sub[s].p0));
+        ni = std::max(ni, (int)(p.sub[s].i1 - p.sub[s].i0));
     }
-    hipLaunchKernelGGL((k_col<R, NY, NACC, QB>), grid, block, lds, s, p, (const V*)tw.ty);
+    const long long groups = (long long)(p.g.Kxp / CS::CW) * p.nsub * batch;
+    const int cap = groups <= 256 ? CS::WMAX : (groups <= 1024 ? 8 : 4);
+    const int jobs = np * CS::S;
+    const int rounds = (jobs + cap - 1) / cap;
+    int w = rounds > 0 ? (jobs + rounds - 1) / rounds : 1;
+    w = std::max(w, std::min(ni * CS::S, cap));
+    const int it = CS::CW * p.g.Ky <= 64 * CS::WMAX ? 1 : CS::ITMAX;
+    w = std::max(w, (CS::CW * p.g.Ky + 64 * it - 1) / (64 * it));
+    w = (w + CS::S - 1) / CS::S * CS::S;
+    return std::min(w, CS::WMAX);
+}
+template <typename R, int NY, int NACC, int IT>
+static hipError_t col_it(const ColParams& p, int W, int batch, const Twiddles& tw, hipStream_t s) {
+    using CS = ColShape<R, NY>;
+    using V = typename CS::V;
+    if (CS::CW * p.g.Ky > W * 64 * IT) return hipErrorInvalidValue;  // a mode without an owner
+    hipLaunchKernelGGL((k_col<R, NY, NACC, IT>), dim3(p.g.Kxp / CS::CW, p.nsub, batch), dim3(64 * W),
+                       (size_t)W * CS::AREA * sizeof(V), s, p, (const V*)tw.ty);
     return hipGetLastError();
 }
-template <typename R, int NY, bool QB>
-static hipError_t col_acc_qb(const ColParams& p, int batch, const Twiddles& tw, hipStream_t s) {
-    if (p.nacc <= 1) return col_go<R, NY, 1, QB>(p, batch, tw, s);
-    if (p.nacc <= 2) return col_go<R, NY, 2, QB>(p, batch, tw, s);
-    return col_go<R, NY, 4, QB>(p, batch, tw, s);
+template <typename R, int NY, int NACC>
+static hipError_t col_go(const ColParams& p, int batch, const Twiddles& tw, hipStream_t s) {
+    if constexpr (NY == 1) {
+        if (p.g.col_C != 64) return hipErrorInvalidValue;
+        int ns = 0;
+        for (int i = 0; i < p.nsub; ++i)
+            ns = std::max(ns, p.sub[i].p1 - p.sub[i].p0 + p.sub[i].c1 - p.sub[i].c0);
+        const int W = std::min(kCol1Waves, std::max(1, (ns + 1) / 2));
+        hipLaunchKernelGGL((k_col1<R, NACC>), dim3(p.g.Kxp / 64, p.nsub, batch), dim3(64 * W), 0, s, p);
+        return hipGetLastError();
+    } else {
+        using CS = ColShape<R, NY>;
+        if (p.g.col_C != CS::CW) return hipErrorInvalidValue;  // the layout was made for another tile
+        const int W = col_waves<R, NY>(p, batch);
+        if constexpr (CS::ITMAX > 1)
+            if (CS::CW * p.g.Ky > 64 * CS::WMAX) return col_it<R, NY, NACC, CS::ITMAX>(p, W, batch, tw, s);
+        return col_it<R, NY, NACC, 1>(p, W, batch, tw, s);
+    }
 }
-// the quarter-band variant serves grids of 128 or more rows whose kept band
-// lies below NY/4
 template <typename R, int NY>
 static hipError_t col_acc(const ColParams& p, int batch, const Twiddles& tw, hipStream_t s) {
-    if constexpr (NY >= 128) {
-        if (p.g.qb) return col_acc_qb<R, NY, true>(p, batch, tw, s);
-    }
-    return col_acc_qb<R, NY, false>(p, batch, tw, s);
+    if (p.nacc <= 1) return col_go<R, NY, 1>(p, batch, tw, s);
+    if (p.nacc <= 2) return col_go<R, NY, 2>(p, batch, tw, s);
+    return col_go<R, NY, 4>(p, batch, tw, s);
 }
 template <typename R>
 static hipError_t col_ny(const ColParams& p, int batch, const Twiddles& tw, hipStream_t s) {
@@ -2331,11 +2137,6 @@ template <> hipError_t launch_rk54_t<Real>(const Rk54Params& p, int batch, hipSt
     const unsigned nb = p.stage == 5 ? (unsigned)p.nblk : (unsigned)((p.g.s_cmp + 255) / 256);
     dim3 block(256), grid(nb, batch);
     hipLaunchKernelGGL(k_rk54<Real>, grid, block, 0, s, p);
-    return hipGetLastError();
-}
-template <> hipError_t launch_aa_dot_t<Real>(const AaParams& p, int batch, hipStream_t s) {
-    dim3 block(kAADotThreads), grid((unsigned)p.nblk, batch);
-    hipLaunchKernelGGL(k_aa_dot<Real>, grid, block, 0, s, p);
     return hipGetLastError();
 }
 template <> hipError_t launch_hist_seed_t<Real>(const HistParams& p, int batch, hipStream_t s) {

@@ -159,20 +159,6 @@ struct Rk54Params {
     int nblk;
 };
 
-// Anderson mixing of the relaxed sweep (iteration mode): partial inner
-// products of the residual history (k_aa_dot), which the next column pass
-// turns into the weights of the next iterate
-struct AaParams {
-    GridDev g;
-    Ctl* ctl;
-    int sweep;                 // n
-    int vd;                    // phi_b is iterated too (variable bed)
-    const void* fv[kAASlots];  // residual history f_i = T(x_i) - x_i (V and phi_b parts)
-    const void* fb[kAASlots];
-    double* partial;           // [batch][nblk][kAASlots]
-    int nblk;
-};
-
 // learned history seed: prediction, history push, loss gradient, reduction, Adam
 struct HistParams {
     GridDev g;
@@ -205,8 +191,7 @@ struct Twiddles {
     const void* ty;   // length ny
 };
 
-int col_tile(int ny, int fp64, int qb);   // column-tile width C for a grid
-int col_quarter_band(int ny, int My);     // 1 if the quarter-band column pass applies
+int col_tile(int ny);   // columns of a column-pass workgroup (ColShape::CW; 64 modes in 1D)
 
 // per-precision launchers (defined in sbi_kernels.hip, one object per precision)
 template <typename R> hipError_t launch_row_fwd_t(const RowFwdParams&, int, const Twiddles&, hipStream_t);
@@ -220,7 +205,6 @@ template <typename R> hipError_t launch_row_feat_t(const RowFeatParams&, int, co
 template <typename R> hipError_t launch_col_t(const ColParams&, int, const Twiddles&, hipStream_t);
 template <typename R> hipError_t launch_rk_t(const RkParams&, int, hipStream_t);
 template <typename R> hipError_t launch_rk54_t(const Rk54Params&, int, hipStream_t);
-template <typename R> hipError_t launch_aa_dot_t(const AaParams&, int, hipStream_t);
 template <typename R> hipError_t launch_diag_t(const DiagParams&, int, hipStream_t);
 template <typename R> hipError_t launch_hist_seed_t(const HistParams&, int, hipStream_t);
 template <typename R> hipError_t launch_hist_push_t(const HistParams&, int, hipStream_t);
@@ -244,7 +228,6 @@ hipError_t launch_row_feat(int fp64, const RowFeatParams& p, int batch, const Tw
 hipError_t launch_col(int fp64, const ColParams& p, int batch, const Twiddles& tw, hipStream_t s);
 hipError_t launch_rk(int fp64, const RkParams& p, int batch, hipStream_t s);
 hipError_t launch_rk54(int fp64, const Rk54Params& p, int batch, hipStream_t s);
-hipError_t launch_aa_dot(int fp64, const AaParams& p, int batch, hipStream_t s);
 hipError_t launch_diag(int fp64, const DiagParams& p, int batch, hipStream_t s);
 hipError_t launch_hist_seed(int fp64, const HistParams& p, int batch, hipStream_t s);
 hipError_t launch_hist_push(int fp64, const HistParams& p, int batch, hipStream_t s);
