@@ -58,7 +58,8 @@ enum {
     C_PV = C_HB0 + kHistTaps,   // its prediction for the current solve (V, phi_b)
     C_PB,
     C_COUNT,
-    C_SAV0 = C_AFV0      // SA orders V_2 .. V_6 (that mode has no residual history)
+    C_SAV0 = C_AFV0,     // SA orders V_2 .. V_7 (that mode has no residual history)
+    C_SAB0 = C_SAV0 + 6  //   phi_b,2 .. phi_b,6
 };
 static_assert(4 * kAASlots >= 11, "the SA orders take the history ring's slots");
 // half-form buffers
@@ -71,11 +72,9 @@ enum {
 };
 // physical buffers
 enum {
-    P_ETA, P_DELTA, P_PX, P_PY,
-    P_V0,                 // SA orders V_1..V_7 at P_V0 + (l-1)
-    P_BX0 = P_V0 + 7,     // SA orders grad phi_b,1..6 (x)
-    P_BY0 = P_BX0 + 7,
-    P_COUNT = P_BY0 + 7
+    P_ETA, P_DELTA,
+    P_WORK0,              // work fields of the learned seed and of the fully nonlinear solve
+    P_COUNT = P_WORK0 + 6
 };
 
 struct Stats {
@@ -936,29 +935,53 @@ static sbi_status stage_state_pass(sbi_ctx* c, bool need_eta, bool allow_prev = 
     return run_col(c, b, K_COL_STATE);
 }
 
+// Products per workgroup of a row pass of nfam families of J products.  A
+// workgroup is a chain of transforms (the family's inverse one, then its
+// products); with fewer than two workgroups per CU the chip idles along it, so
+// the chains are cut, each piece repeating the inverse, until 512 workgroups
+// run or each holds one product.  Measured, uncut -> cut: 128 x 64 FP64
+// iteration 4160 -> 2870 us a step, 512 x 512 FP32 SA 642 -> 580, 1D 256-point
+// solve 1008 -> 770.  From 512 on the repeated transforms cost more: 1024 x 1024
+// (768 workgroups) 7.0 ms uncut, 7.5 in halves, 8.5 in single products.
+static int row_chunk(const sbi_ctx* c, int nfam, int J) {
+    constexpr long long kWant = 512;
+    const int cap = std::min(row_rows_cap(c->fp64, c->grid.nx, c->gd.row_var), c->grid.ny);
+    const int rpw = c->gd.row_rpw > 0 ? std::min(c->gd.row_rpw, cap) : cap;
+    const long long groups = (long long)((c->grid.ny + rpw - 1) / rpw) * nfam * c->batch;
+    int pc = std::max(J, 1);
+    for (int parts = 2; parts <= J && groups * ((J + pc - 1) / pc) < kWant; ++parts) pc = (J + parts - 1) / parts;
+    return pc;
+}
+
+static sbi_status run_row_prod(sbi_ctx* c, RowProdParams& rp, int cls) {
+    rp.g = c->gd;
+    rp.delta = PHYS(P_DELTA);
+    rp.ctl = c->ctl;
+    rp.pc = row_chunk(c, rp.nfam, rp.J);
+    rp.nch = rp.J > 0 ? (rp.J + rp.pc - 1) / rp.pc : 1;
+    if (rp.nfam * rp.J > kMaxProd) return SBI_ERR_UNSUPPORTED;
+    for (int i = 0; i < rp.nfam * rp.J; ++i) rp.h[i] = HALF(H_PROD0 + i);
+    c->st.launches += 1;
+    ProfScope ps_(c, cls);
+    return hip_ok(launch_row_prod(c->fp64, rp, c->batch, tw_of(c), c->stream));
+}
+
+// physical eta (stored unless the caller gave it), its extrema and, in
+// iteration mode, the forcing products eta^(l-1) grad phi_s of every order
 static sbi_status row_setup(sbi_ctx* c, const void* eta_user) {
     const bool two_d = c->grid.ny > 1;
-    const bool sa = c->grid.mode == SBI_MODE_SA;
     const bool iter = c->grid.mode == SBI_MODE_ITER;
-    RowSetupParams rp{};
-    rp.g = c->gd;
+    RowProdParams rp{};
+    rp.nfam = two_d ? 2 : 1;
+    rp.J = iter ? c->grid.order - 1 : 0;
+    rp.check = rp.nfam == 2 ? 3 : 1;
+    rp.extrema = 1;
+    rp.src[0] = HALF(H_PX);
+    rp.src[1] = HALF(H_PY);
     rp.g_eta = eta_user ? nullptr : HALF(H_ETA);
     rp.eta_in = eta_user;
     rp.eta_out = eta_user ? nullptr : PHYS(P_ETA);
-    rp.g_px = HALF(H_PX);
-    rp.g_py = HALF(H_PY);
-    rp.px_out = sa ? PHYS(P_PX) : nullptr;
-    rp.py_out = (sa && two_d) ? PHYS(P_PY) : nullptr;
-    rp.nprod = iter ? (c->grid.order - 1) * (two_d ? 2 : 1) : 0;
-    for (int i = 0; i < rp.nprod; ++i) rp.h[i] = HALF(H_PROD0 + i);
-    rp.ctl = c->ctl;
-    // the two components' product chains in workgroups of their own
-    rp.nfam = (two_d && rp.nprod > 0) ? 2 : 1;
-    c->st.launches += 1;
-    {
-        ProfScope ps_(c, K_ROW_SETUP);
-        return hip_ok(launch_row_setup(c->fp64, rp, c->batch, tw_of(c), c->stream));
-    }
+    return run_row_prod(c, rp, K_ROW_SETUP);
 }
 
 // constant parts b_V, b_phi of the summed operator; also fixes omega (CTL_OMEGA)
@@ -966,11 +989,10 @@ static sbi_status col_forcing(sbi_ctx* c) {
     const bool two_d = c->grid.ny > 1;
     const int L = c->grid.order;
     ColBuilder b(c->gd);
-    int idx = 0;
     std::vector<int> sx(L + 1, -1), sy(L + 1, -1);
     for (int l = 2; l <= L; ++l) {
-        sx[l] = b.prod(HALF(H_PROD0 + idx++));
-        if (two_d) sy[l] = b.prod(HALF(H_PROD0 + idx++));
+        sx[l] = b.prod(HALF(H_PROD0 + l - 2));
+        if (two_d) sy[l] = b.prod(HALF(H_PROD0 + L - 1 + l - 2));
     }
     int sp = b.cin(CMP(C_PS));
     b.term(sp, 0, 1.0, FN_T, 1, DV_NONE);
@@ -1047,6 +1069,8 @@ static RowSweepParams sweep_row_params(sbi_ctx* c, const void* eta_phys, bool re
     rp.vd = c->vd;
     rp.slot = slot;
     rp.nfam = rp.products ? 1 + (c->vd ? (two_d ? 2 : 1) : 0) : 1;
+    rp.pc = rp.products ? row_chunk(c, rp.nfam, J) : 1;
+    rp.nch = rp.products ? (J + rp.pc - 1) / rp.pc : 1;
     if (rp.products) {
         const int np = J * (1 + (c->vd ? (two_d ? 2 : 1) : 0));
         for (int i = 0; i < np; ++i) rp.h[i] = HALF(H_PROD0 + i);
@@ -1336,91 +1360,85 @@ static sbi_status iterate_mixed(sbi_ctx* c, const void* eta_phys, double tol) {
     return SBI_OK;
 }
 
-static sbi_status run_sa(sbi_ctx* c, const void* eta_phys) {
+// Successive approximation by forward scatter: once order m is known, the
+// products eta^j V_m and delta^j grad phi_b,m, j = 1 .. L - m, add their terms to
+// the orders m + j, whose partial sums stay in the compact fields; order m + 1
+// is then complete.  The first pass also carries the forcing eta^(l-1) grad
+// phi_s of every order.  An order's fields are read once, as half forms, and
+// never kept at the points.  The column pass takes the orders m + j side by side
+// as sub-passes.  Runs after stage_state_pass; sets what row_setup does.
+static sbi_status run_sa(sbi_ctx* c, const void* eta_user) {
     const bool two_d = c->grid.ny > 1;
     const int L = c->grid.order;
-    for (int l = 2; l <= L; ++l) {
-        RowSaParams rp{};
-        rp.g = c->gd;
-        rp.l = l;
-        rp.vd = c->vd;
-        rp.gV = HALF(H_GV);
-        rp.gbx = HALF(H_GBX);
-        rp.gby = HALF(H_GBY);
-        rp.V_out = PHYS(P_V0 + (l - 2));      // V_(l-1)
-        rp.bx_out = c->vd ? PHYS(P_BX0 + (l - 2)) : nullptr;
-        rp.by_out = (c->vd && two_d) ? PHYS(P_BY0 + (l - 2)) : nullptr;
-        for (int m = 1; m < l; ++m) {
-            rp.Vphys[m] = PHYS(P_V0 + (m - 1));
-            rp.bxphys[m] = PHYS(P_BX0 + (m - 1));
-            rp.byphys[m] = PHYS(P_BY0 + (m - 1));
+    const int nbed = c->vd ? (two_d ? 2 : 1) : 0, nfor = two_d ? 2 : 1;
+    for (int m = 1; m < std::max(L, 2); ++m) {
+        const int J = L - m;
+        const bool first = m == 1;
+        RowProdParams rp{};
+        rp.J = J;
+        if (J > 0) {
+            rp.src[rp.nfam++] = HALF(H_GV);
+            for (int d = 0; d < nbed; ++d) {
+                rp.bed |= 1 << rp.nfam;
+                rp.src[rp.nfam++] = HALF(d == 0 ? H_GBX : H_GBY);
+            }
         }
-        rp.eta = eta_phys;
-        rp.delta = PHYS(P_DELTA);
-        rp.phx = PHYS(P_PX);
-        rp.phy = PHYS(P_PY);
-        const int np = (l - 1) * (1 + (c->vd ? (two_d ? 2 : 1) : 0)) + (two_d ? 2 : 1);
-        if (np > kMaxProd) return SBI_ERR_UNSUPPORTED;
-        for (int i = 0; i < np; ++i) rp.h[i] = HALF(H_PROD0 + i);
-        // few rows (a 1D grid, or up to 1024 rows over all members): one
-        // workgroup per product, so that the pass is not one long chain of
-        // transforms per row block
-        rp.split = (!two_d || (long long)c->grid.ny * c->batch <= 1024) ? np : 0;
-        c->st.launches += 1;
-        {
-        ProfScope ps_(c, K_ROW_SA);
-        SBI_TRY(hip_ok(launch_row_sa(c->fp64, rp, c->batch, tw_of(c), c->stream)));
-    }
+        rp.lead = -1;
+        if (first) {
+            rp.lead = rp.nfam;
+            for (int d = 0; d < nfor; ++d) {
+                rp.check |= 1 << rp.nfam;
+                rp.src[rp.nfam++] = HALF(d == 0 ? H_PX : H_PY);
+            }
+        }
+        rp.g_eta = first && !eta_user ? HALF(H_ETA) : nullptr;
+        rp.eta_in = eta_user ? eta_user : PHYS(P_ETA);
+        rp.eta_out = first && !eta_user ? PHYS(P_ETA) : nullptr;
+        SBI_TRY(run_row_prod(c, rp, K_ROW_SA));
+        if (J == 0) break;
 
         ColBuilder b(c->gd);
-        int idx = 0;
-        std::vector<int> se(l), sbx(l), sby(l);
-        for (int j = 1; j <= l - 1; ++j) se[j] = b.prod(HALF(H_PROD0 + idx++));
-        if (c->vd) {
-            for (int j = 1; j <= l - 1; ++j) sbx[j] = b.prod(HALF(H_PROD0 + idx++));
-            if (two_d)
-                for (int j = 1; j <= l - 1; ++j) sby[j] = b.prod(HALF(H_PROD0 + idx++));
-        }
-        int fx = b.prod(HALF(H_PROD0 + idx++));
-        int fy = two_d ? b.prod(HALF(H_PROD0 + idx++)) : -1;
-        const bool want_b = c->vd && l <= L - 1;
-        // acc0 = V_l (kept until the last order adds them all), acc1 = phi_b,l
-        for (int j = 1; j <= l - 1; ++j) {
-            const double f = 1.0 / fact(j);
-            b.term(se[j], 0, -f, Tfn(j), j, DV_NONE);
-            if (want_b && (j & 1)) b.term(se[j], 1, -f, FN_S, j - 1, DV_NONE);
-            if (c->vd) {
-                if (j & 1) {
-                    b.term(sbx[j], 0, f, FN_S, j - 1, DV_X);
-                    if (two_d) b.term(sby[j], 0, f, FN_S, j - 1, DV_Y);
+        for (int j = 1; j <= J; ++j) {
+            const int l = m + j;  // the order this sub-pass adds to
+            const bool last = l == L, done = j == 1;
+            const bool want_b = c->vd && !last;
+            const double f = 1.0 / fact(j), sg = (j & 1) ? -f : f;
+            if (j > 1) b.next_sub();
+            auto prod = [&](int fam) { return b.prod(HALF(H_PROD0 + fam * J + j - 1)); };
+            const int sv = prod(0);
+            b.term(sv, 0, -f, Tfn(j), j, DV_NONE);
+            if (want_b && (j & 1)) b.term(sv, 1, -f, FN_S, j - 1, DV_NONE);
+            for (int d = 0; d < nbed; ++d) {
+                const int sb = prod(1 + d), dv = d == 0 ? DV_X : DV_Y;
+                if (j & 1) b.term(sb, 0, f, FN_S, j - 1, dv);
+                if (want_b) b.term(sb, 1, sg, Tfn(j), j - 2, dv);
+            }
+            if (first) {
+                for (int d = 0; d < nfor; ++d) {
+                    const int sf = prod(1 + nbed + d), dv = d == 0 ? DV_X : DV_Y;
+                    b.term(sf, 0, -f, Tfn(l), l - 2, dv);
+                    if (want_b && (l & 1)) b.term(sf, 1, -f, FN_S, l - 3, dv);
                 }
+            } else {
+                b.term(b.cin(CMP(C_SAV0 + l - 2)), 0, 1.0, FN_ONE, 0, DV_NONE);
+                if (want_b) b.term(b.cin(CMP(C_SAB0 + l - 2)), 1, 1.0, FN_ONE, 0, DV_NONE);
+            }
+            if (done && last) {
+                // W = V_1 + ... + V_L
+                b.term(b.cin(CMP(C_VH)), 0, 1.0, FN_ONE, 0, DV_NONE);
+                for (int i = 2; i < L; ++i) b.term(b.cin(CMP(C_SAV0 + i - 2)), 0, 1.0, FN_ONE, 0, DV_NONE);
+                b.cout(SRC_ACC0, CMP(C_VH));
+            } else {
+                b.cout(SRC_ACC0, CMP(C_SAV0 + l - 2));
+                if (want_b && !done) b.cout(SRC_ACC1, CMP(C_SAB0 + l - 2));
+            }
+            if (done) {
+                b.inv(SRC_ACC0, DV_NONE, HALF(H_GV));
                 if (want_b) {
-                    const double sg = (j & 1) ? -f : f;
-                    b.term(sbx[j], 1, sg, Tfn(j), j - 2, DV_X);
-                    if (two_d) b.term(sby[j], 1, sg, Tfn(j), j - 2, DV_Y);
+                    b.inv(SRC_ACC1, DV_X, HALF(H_GBX));
+                    if (two_d) b.inv(SRC_ACC1, DV_Y, HALF(H_GBY));
                 }
             }
-        }
-        const double fl = -1.0 / fact(l - 1);
-        b.term(fx, 0, fl, Tfn(l), l - 2, DV_X);
-        if (two_d) b.term(fy, 0, fl, Tfn(l), l - 2, DV_Y);
-        if (want_b && (l & 1)) {
-            b.term(fx, 1, fl, FN_S, l - 3, DV_X);
-            if (two_d) b.term(fy, 1, fl, FN_S, l - 3, DV_Y);
-        }
-        if (l < L) {
-            b.cout(SRC_ACC0, CMP(C_SAV0 + l - 2));
-            b.inv(SRC_ACC0, DV_NONE, HALF(H_GV));
-            if (want_b) {
-                b.inv(SRC_ACC1, DV_X, HALF(H_GBX));
-                if (two_d) b.inv(SRC_ACC1, DV_Y, HALF(H_GBY));
-            }
-        } else {
-            // W = V_1 + ... + V_L
-            b.term(b.cin(CMP(C_VH)), 0, 1.0, FN_ONE, 0, DV_NONE);
-            for (int m = 2; m < L; ++m) b.term(b.cin(CMP(C_SAV0 + m - 2)), 0, 1.0, FN_ONE, 0, DV_NONE);
-            b.cout(SRC_ACC0, CMP(C_VH));
-            b.inv(SRC_ACC0, DV_NONE, HALF(H_GV));
         }
         SBI_TRY(run_col(c, b, K_COL_SA));
     }
@@ -1489,14 +1507,14 @@ static sbi_status net_infer(sbi_ctx* c, const float* feat, const void* wlin, voi
 // which left the linear guesses in C_VN / C_BN)
 static sbi_status net_seed(sbi_ctx* c, const void* eta_phys) {
     if (!c->net_loaded || !c->feat) return SBI_ERR_INVALID_ARG;
-    SBI_TRY(row_features(c, eta_phys, c->feat, PHYS(P_V0)));
-    SBI_TRY(net_infer(c, c->feat, PHYS(P_V0), PHYS(P_V0 + 1), PHYS(P_V0 + 2)));
+    SBI_TRY(row_features(c, eta_phys, c->feat, PHYS(P_WORK0)));
+    SBI_TRY(net_infer(c, c->feat, PHYS(P_WORK0), PHYS(P_WORK0 + 1), PHYS(P_WORK0 + 2)));
     RowFwdParams rp{};
     rp.g = c->gd;
     rp.nf = c->vd ? 2 : 1;
-    rp.in[0] = PHYS(P_V0 + 1);
+    rp.in[0] = PHYS(P_WORK0 + 1);
     rp.out[0] = HALF(H_PROD0);
-    rp.in[1] = PHYS(P_V0 + 2);
+    rp.in[1] = PHYS(P_WORK0 + 2);
     rp.out[1] = HALF(H_PROD0 + 1);
     c->st.launches += 1;
     {
@@ -1593,8 +1611,8 @@ static sbi_status hist_after_solve(sbi_ctx* c, int stage, bool capture_safe) {
 // equations with the remaining integrals kept (sbi_full.hip) -- over a flat
 // bed by its image, over a variable bed with the bed as a second boundary
 // ---------------------------------------------------------------------------
-// physical work fields of the solve (the SA order slots, unused in this mode)
-enum { PF_PHI = P_V0, PF_EX, PF_EXX, PF_V, PF_B0, PF_B1 };
+// physical work fields of the solve
+enum { PF_PHI = P_WORK0, PF_EX, PF_EXX, PF_V, PF_B0, PF_B1 };
 
 static FullParams full_params(sbi_ctx* c) {
     FullParams p{};
@@ -1762,10 +1780,10 @@ static sbi_status solve_stage(sbi_ctx* c, const void* eta_user, double tol, bool
         SBI_TRY(hip_ok(launch_hist_seed(c->fp64, hist_params(c, stage), c->batch, c->stream)));
     }
     SBI_TRY(stage_state_pass(c, need_eta_grad || !eta_user || net, true, hist));
-    SBI_TRY(row_setup(c, eta_user));
+    if (c->grid.mode != SBI_MODE_SA) SBI_TRY(row_setup(c, eta_user));
     const void* eta_phys = eta_user ? eta_user : PHYS(P_ETA);
     if (c->grid.mode == SBI_MODE_SA) {
-        SBI_TRY(run_sa(c, eta_phys));
+        SBI_TRY(run_sa(c, eta_user));
         *vh_buf = C_VH;
     } else if (c->grid.mode == SBI_MODE_FULL) {
         SBI_TRY(full_solve(c, eta_phys, tol));

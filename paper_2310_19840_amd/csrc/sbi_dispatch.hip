@@ -239,9 +239,8 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t s) {
     }
 SBI_DISPATCH(launch_row_fwd, RowFwdParams)
 SBI_DISPATCH(launch_row_inv, RowInvParams)
-SBI_DISPATCH(launch_row_setup, RowSetupParams)
 SBI_DISPATCH(launch_row_sweep, RowSweepParams)
-SBI_DISPATCH(launch_row_sa, RowSaParams)
+SBI_DISPATCH(launch_row_prod, RowProdParams)
 SBI_DISPATCH(launch_row_nphi, RowNphiParams)
 SBI_DISPATCH(launch_row_blend, RowBlendParams)
 SBI_DISPATCH(launch_row_feat, RowFeatParams)

@@ -21,7 +21,7 @@
 namespace sbi {
 
 constexpr int kMaxSweepSlots = 1024;   // max_sweeps <= 1000
-constexpr int kMaxProd = 24;           // forward inputs of one column pass
+constexpr int kMaxProd = 30;           // forward inputs of one column pass (SA's first: 5 families of 6)
 constexpr int kMaxCin = 16;            // compact inputs of one column pass
 constexpr int kMaxCout = 16;
 constexpr int kMaxInv = 8;

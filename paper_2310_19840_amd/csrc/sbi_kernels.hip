@@ -274,90 +274,84 @@ __global__ void __launch_bounds__(row_threads<NX>()) k_row_inv(const RowInvParam
     }
 }
 
-template <typename R, int NX>
-__global__ void __launch_bounds__(row_threads<NX>()) k_row_setup(const RowSetupParams p, const typename cplx_of<R>::type* twN_tab,
-                            const typename cplx_of<R>::type* twX_tab) {
-    ROW_PROLOGUE(R, NX)
-    const bool two_d = p.g.ny > 1;
-    // with two families (p.nfam = 2, 2D iteration) workgroup row y = 1 takes
-    // the y component: its own copy of eta, d_y phi and their products, formed
-    // by the same operations as in one family
-    const int fam = blockIdx.y;
-    const bool want_x = fam == 0;
-    const bool want_y = two_d && (p.nfam < 2 || fam == 1);
-    V e[E];
-    if (p.g_eta) {
-        RW::inverse(e, static_cast<const V*>(p.g_eta) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
+// Forward half forms of the running products v w^j, j = j0 + 1 .. j1, of a row
+// (v is destroyed; every chunk of a chain forms the same products).
+template <typename RW, typename V, int E>
+__device__ __forceinline__ void row_chain(V (&v)[E], const V (&w)[E], int j0, int j1, void* const* h, long long hb,
+                                          const RowCtx& rc, V* lds_all, const typename RW::TW& twN, const V* twX) {
+    for (int jj = 1; jj <= j1; ++jj) {
+#pragma unroll
+        for (int q = 0; q < E; ++q) v[q] = rmul(v[q], w[q]);
+        if (jj <= j0) continue;
+        V o[E];
+#pragma unroll
+        for (int q = 0; q < E; ++q) o[q] = v[q];
+        RW::forward(o, static_cast<V*>(h[jj - 1]) + hb, rc, lds_all, twN, twX);
+    }
+}
+
+// Product families of a W solve: src w^j, j = 1 .. J, for each family's half
+// form src and its weight w (eta, or delta for the bed's gradients) -- the
+// forcing eta^j grad phi_s of every order, and in SA mode the products of the
+// order last formed.  Workgroup row y takes products pc ch + 1 .. pc (ch + 1) of
+// family y / nch.  The lead family also serves the stage: it stores eta, its
+// extrema (relaxation weight) and the checks for non-finite values.
+//
+// A workgroup is one chain of transforms, so few rows leave the chip idle
+// however short the rows: there each product takes a workgroup of its own and
+// the inverse transform before it is repeated (row_chunk).
+template <typename R, int NX, int VAR>
+__global__ void __launch_bounds__((row_threads<NX, RowVar<R, NX, VAR>::E>()))
+    k_row_prod(const RowProdParams p, const typename cplx_of<R>::type* twN_tab,
+               const typename cplx_of<R>::type* twX_tab) {
+    ROW_PROLOGUE_T(RowVar<R, NX, VAR>)
+    const int fam = blockIdx.y / p.nch, ch = blockIdx.y % p.nch;
+    const bool bed = (p.bed >> fam) & 1;
+    const bool check = ch == 0 && ((p.check >> fam) & 1);
+    const bool lead = ch == 0 && fam == p.lead;
+    V w[E];
+    if (bed) {
+        RW::load(w, static_cast<const R*>(p.delta) + po, ri.j, ri.valid);
+    } else if (p.g_eta) {
+        RW::inverse(w, static_cast<const V*>(p.g_eta) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
     } else {
-        RW::load(e, static_cast<const R*>(p.eta_in) + po, ri.j, ri.valid);
+        RW::load(w, static_cast<const R*>(p.eta_in) + po, ri.j, ri.valid);
     }
     int bad = 0;
-    if (fam == 0) {
-        if (p.eta_out) RW::store(e, static_cast<R*>(p.eta_out) + po, ri.j, ri.valid);
-        // extrema of eta (relaxation weight)
-        unsigned long long mx = 0ull, mn = ~0ull;
+    if (lead) {
+        if (p.eta_out) RW::store(w, static_cast<R*>(p.eta_out) + po, ri.j, ri.valid);
+        if (p.extrema) {
+            unsigned long long mx = 0ull, mn = ~0ull;
+            if (ri.valid) {
+#pragma unroll
+                for (int q = 0; q < E; ++q) {
+                    unsigned long long a = ord_bits((double)w[q].x), b = ord_bits((double)w[q].y);
+                    mx = a > mx ? a : mx;
+                    mx = b > mx ? b : mx;
+                    mn = a < mn ? a : mn;
+                    mn = b < mn ? b : mn;
+                }
+            }
+            mx = block_reduce_u64<true>(mx);
+            mn = block_reduce_u64<false>(mn);
+            if (threadIdx.x == 0) {
+                atomicMax(&p.ctl[ri.mem].eta_max, mx);
+                atomicMin(&p.ctl[ri.mem].eta_min, mn);
+            }
+        }
         if (ri.valid) {
 #pragma unroll
-            for (int q = 0; q < E; ++q) {
-                unsigned long long a = ord_bits((double)e[q].x), b = ord_bits((double)e[q].y);
-                mx = a > mx ? a : mx;
-                mx = b > mx ? b : mx;
-                mn = a < mn ? a : mn;
-                mn = b < mn ? b : mn;
-            }
-        }
-        mx = block_reduce_u64<true>(mx);
-        mn = block_reduce_u64<false>(mn);
-        if (threadIdx.x == 0 && p.ctl) {
-            atomicMax(&p.ctl[ri.mem].eta_max, mx);
-            atomicMin(&p.ctl[ri.mem].eta_min, mn);
-        }
-        if (ri.valid) {
-#pragma unroll
-            for (int q = 0; q < E; ++q) bad |= !isfinite((double)e[q].x) || !isfinite((double)e[q].y);
+            for (int q = 0; q < E; ++q) bad |= !isfinite((double)w[q].x) || !isfinite((double)w[q].y);
         }
     }
-    V px[E], py[E];
-    if (want_x) {
-        RW::inverse(px, static_cast<const V*>(p.g_px) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
-        if (p.px_out) RW::store(px, static_cast<R*>(p.px_out) + po, ri.j, ri.valid);
+    V v[E];
+    RW::inverse(v, static_cast<const V*>(p.src[fam]) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
+    if (check && ri.valid) {
+#pragma unroll
+        for (int q = 0; q < E; ++q) bad |= !isfinite((double)v[q].x) || !isfinite((double)v[q].y);
     }
-    if (want_y) {
-        RW::inverse(py, static_cast<const V*>(p.g_py) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
-        if (p.py_out) RW::store(py, static_cast<R*>(p.py_out) + po, ri.j, ri.valid);
-    }
-    if (ri.valid) {
-#pragma unroll
-        for (int q = 0; q < E; ++q) {
-            if (want_x) bad |= !isfinite((double)px[q].x) || !isfinite((double)px[q].y);
-            if (want_y) bad |= !isfinite((double)py[q].x) || !isfinite((double)py[q].y);
-        }
-    }
-    if (bad && p.ctl) atomicOr(&p.ctl[ri.mem].nonfinite, 1);
-    if (p.nprod > 0) {
-        V ep[E];
-#pragma unroll
-        for (int q = 0; q < E; ++q) ep[q] = e[q];
-        for (int l = 2; l <= p.g.order; ++l) {
-            if (l > 2) {
-#pragma unroll
-                for (int q = 0; q < E; ++q) ep[q] = rmul(ep[q], e[q]);
-            }
-            // products of order l: x at 2 (l - 2), y at 2 (l - 2) + 1 (1D: l - 2)
-            const int idx = two_d ? 2 * (l - 2) : l - 2;
-            V w[E];
-            if (want_x) {
-#pragma unroll
-                for (int q = 0; q < E; ++q) w[q] = rmul(ep[q], px[q]);
-                RW::forward(w, static_cast<V*>(p.h[idx]) + hb, rc, lds_all, twN, twX);
-            }
-            if (want_y) {
-#pragma unroll
-                for (int q = 0; q < E; ++q) w[q] = rmul(ep[q], py[q]);
-                RW::forward(w, static_cast<V*>(p.h[idx + 1]) + hb, rc, lds_all, twN, twX);
-            }
-        }
-    }
+    if (bad) atomicOr(&p.ctl[ri.mem].nonfinite, 1);
+    row_chain<RW, V, E>(v, w, ch * p.pc, min(p.J, (ch + 1) * p.pc), p.h + fam * p.J, hb, rc, lds_all, twN, twX);
 }
 
 template <typename R, int NX, bool AA, int VAR>
@@ -366,12 +360,16 @@ __device__ __forceinline__ void row_sweep_body(const RowSweepParams& p, const ty
     Ctl* ctl = p.ctl + blockIdx.z;
     if (ctl->done) return;  // block-uniform: the member's solve is decided
     ROW_PROLOGUE_T(RowVar<R, NX, VAR>)
-    const int fam = blockIdx.y;  // product family of this workgroup
-    if (fam == 0) {
+    // product family and chunk of this workgroup; with several chunks the
+    // residual test has a workgroup row of its own after them
+    const int fam = blockIdx.y / p.nch, ch = blockIdx.y % p.nch;
+    const bool rest = fam == p.nfam;
+    if (rest || (fam == 0 && p.nch == 1)) {
         V vv[E];
+        const bool products = p.products && !rest;
         // the iterate: for its products, and for the residual's denominator
         // of the relaxed update (a residual-only Anderson pass needs neither)
-        if (!AA || p.products)
+        if (!AA || products)
             RW::inverse(vv, static_cast<const V*>(p.gV) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
         if (p.residual) {
             V dd[E];
@@ -412,37 +410,20 @@ __device__ __forceinline__ void row_sweep_body(const RowSweepParams& p, const ty
                 atomicMax(&ctl->slots->den[p.slot], de);
             }
         }
-        if (!p.products) return;
-        // eta^j V as a running product (vv <- vv eta before each transform)
+        if (!products) return;
+        // eta^j V as a running product
         V ev[E];
         RW::load(ev, static_cast<const R*>(p.eta) + po, ri.j, ri.valid);
-        for (int jj = 1; jj <= p.J; ++jj) {
-            V w[E];
-#pragma unroll
-            for (int q = 0; q < E; ++q) {
-                vv[q] = rmul(vv[q], ev[q]);
-                w[q] = vv[q];
-            }
-            RW::forward(w, static_cast<V*>(p.h[jj - 1]) + hb, rc, lds_all, twN, twX);
-        }
+        row_chain<RW, V, E>(vv, ev, 0, p.J, p.h, hb, rc, lds_all, twN, twX);
         return;
     }
-    // families 1, 2: delta^j d_x phi_b, delta^j d_y phi_b
-    if (!p.products || !p.vd) return;
-    const int comp = fam - 1;
-    V gb[E];
-    RW::inverse(gb, static_cast<const V*>(comp == 0 ? p.gbx : p.gby) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
-    V dv[E];
-    RW::load(dv, static_cast<const R*>(p.delta) + po, ri.j, ri.valid);
-    for (int jj = 1; jj <= p.J; ++jj) {
-        V w[E];
-#pragma unroll
-        for (int q = 0; q < E; ++q) {
-            gb[q] = rmul(gb[q], dv[q]);  // running product delta^j d phi_b
-            w[q] = gb[q];
-        }
-        RW::forward(w, static_cast<V*>(p.h[fam * p.J + jj - 1]) + hb, rc, lds_all, twN, twX);
-    }
+    // eta^j V, delta^j d_x phi_b, delta^j d_y phi_b
+    if (!p.products) return;
+    V v[E], w[E];
+    RW::inverse(v, static_cast<const V*>(fam == 0 ? p.gV : (fam == 1 ? p.gbx : p.gby)) + hb, nullptr, R(0), rc, lds_all,
+                twN, twX, iscale);
+    RW::load(w, static_cast<const R*>(fam == 0 ? p.eta : p.delta) + po, ri.j, ri.valid);
+    row_chain<RW, V, E>(v, w, ch * p.pc, min(p.J, (ch + 1) * p.pc), p.h + fam * p.J, hb, rc, lds_all, twN, twX);
 }
 
 template <typename R, int NX, int VAR>
@@ -458,128 +439,6 @@ __global__ void __launch_bounds__((row_threads<NX, RowVar<R, NX, VAR>::E>()), 3)
     k_row_sweep_aa(const RowSweepParams p, const typename cplx_of<R>::type* twN_tab,
                    const typename cplx_of<R>::type* twX_tab) {
     row_sweep_body<R, NX, true, VAR>(p, twN_tab, twX_tab);
-}
-
-template <typename R, int NX, int VAR>
-__global__ void __launch_bounds__((row_threads<NX, RowVar<R, NX, VAR>::E>()))
-    k_row_sa(const RowSaParams p, const typename cplx_of<R>::type* twN_tab,
-             const typename cplx_of<R>::type* twX_tab) {
-    ROW_PROLOGUE_T(RowVar<R, NX, VAR>)
-    const int l = p.l;
-    if (p.split > 0) {
-        // few rows (a 1D grid, a small 2D one): each product of the order in a
-        // workgroup of its own (blockIdx.y), in the order of the sequential
-        // form below and formed by the same operations: eta^j V_(l-j) for
-        // j < l; over a variable bed delta^j d_x phi_b,(l-j), then (2D)
-        // delta^j d_y phi_b,(l-j); then eta^(l-1) d_x phi_s (and d_y phi_s)
-        const int nv = l - 1;
-        const int ncomp = p.g.ny > 1 ? 2 : 1;
-        const int nb = p.vd ? ncomp * nv : 0;
-        const int part = blockIdx.y;
-        // fam 0: V; 1: bed component comp; 2: forcing component comp
-        const int fam = part < nv ? 0 : (part < nv + nb ? 1 : 2);
-        const int comp = fam == 1 ? (part - nv) / nv : (fam == 2 ? part - nv - nb : 0);
-        V base[E], pw[E], src[E];
-        RW::load(base, static_cast<const R*>(fam == 1 ? p.delta : p.eta) + po, ri.j, ri.valid);
-#pragma unroll
-        for (int q = 0; q < E; ++q) pw[q] = base[q];
-        if (fam < 2) {
-            const int jj = (fam == 0 ? part : (part - nv) % nv) + 1;
-            if (jj == 1) {
-                const void* g = fam == 0 ? p.gV : (comp == 0 ? p.gbx : p.gby);
-                RW::inverse(src, static_cast<const V*>(g) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
-                void* outp = fam == 0 ? p.V_out : (comp == 0 ? p.bx_out : p.by_out);
-                if (outp) RW::store(src, static_cast<R*>(outp) + po, ri.j, ri.valid);
-            } else {
-                for (int i = 2; i <= jj; ++i) {
-#pragma unroll
-                    for (int q = 0; q < E; ++q) pw[q] = rmul(pw[q], base[q]);
-                }
-                const void* const* phys = fam == 0 ? p.Vphys : (comp == 0 ? p.bxphys : p.byphys);
-                RW::load(src, static_cast<const R*>(phys[l - jj]) + po, ri.j, ri.valid);
-            }
-#pragma unroll
-            for (int q = 0; q < E; ++q) src[q] = rmul(pw[q], src[q]);
-            const int idx = fam == 0 ? jj - 1 : nv + comp * nv + jj - 1;
-            RW::forward(src, static_cast<V*>(p.h[idx]) + hb, rc, lds_all, twN, twX);
-        } else {
-            for (int i = 2; i <= nv; ++i) {
-#pragma unroll
-                for (int q = 0; q < E; ++q) pw[q] = rmul(pw[q], base[q]);
-            }
-            RW::load(src, static_cast<const R*>(comp == 0 ? p.phx : p.phy) + po, ri.j, ri.valid);
-#pragma unroll
-            for (int q = 0; q < E; ++q) src[q] = rmul(pw[q], src[q]);
-            RW::forward(src, static_cast<V*>(p.h[nv + nb + comp]) + hb, rc, lds_all, twN, twX);
-        }
-        return;
-    }
-    int idx = 0;
-    V a[E], base[E], pw[E];
-    // eta^j V_(l-j)
-    RW::inverse(a, static_cast<const V*>(p.gV) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
-    if (p.V_out) RW::store(a, static_cast<R*>(p.V_out) + po, ri.j, ri.valid);
-    RW::load(base, static_cast<const R*>(p.eta) + po, ri.j, ri.valid);
-#pragma unroll
-    for (int q = 0; q < E; ++q) pw[q] = base[q];
-    for (int jj = 1; jj <= l - 1; ++jj) {
-        V src[E], w[E];
-        if (jj == 1) {
-#pragma unroll
-            for (int q = 0; q < E; ++q) src[q] = a[q];
-        } else {
-#pragma unroll
-            for (int q = 0; q < E; ++q) pw[q] = rmul(pw[q], base[q]);
-            RW::load(src, static_cast<const R*>(p.Vphys[l - jj]) + po, ri.j, ri.valid);
-        }
-#pragma unroll
-        for (int q = 0; q < E; ++q) w[q] = rmul(pw[q], src[q]);
-        RW::forward(w, static_cast<V*>(p.h[idx++]) + hb, rc, lds_all, twN, twX);
-    }
-    // delta^j grad phi_b,(l-j)
-    if (p.vd) {
-        const int ncomp = p.g.ny > 1 ? 2 : 1;
-        for (int comp = 0; comp < ncomp; ++comp) {
-            const void* gsrc = comp == 0 ? p.gbx : p.gby;
-            void* outp = comp == 0 ? p.bx_out : p.by_out;
-            const void* const* phys = comp == 0 ? p.bxphys : p.byphys;
-            RW::inverse(a, static_cast<const V*>(gsrc) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
-            if (outp) RW::store(a, static_cast<R*>(outp) + po, ri.j, ri.valid);
-            RW::load(base, static_cast<const R*>(p.delta) + po, ri.j, ri.valid);
-#pragma unroll
-            for (int q = 0; q < E; ++q) pw[q] = base[q];
-            for (int jj = 1; jj <= l - 1; ++jj) {
-                V src[E], w[E];
-                if (jj == 1) {
-#pragma unroll
-                    for (int q = 0; q < E; ++q) src[q] = a[q];
-                } else {
-#pragma unroll
-                    for (int q = 0; q < E; ++q) pw[q] = rmul(pw[q], base[q]);
-                    RW::load(src, static_cast<const R*>(phys[l - jj]) + po, ri.j, ri.valid);
-                }
-#pragma unroll
-                for (int q = 0; q < E; ++q) w[q] = rmul(pw[q], src[q]);
-                RW::forward(w, static_cast<V*>(p.h[idx++]) + hb, rc, lds_all, twN, twX);
-            }
-        }
-    }
-    // forcing eta^(l-1) grad phi_s
-    RW::load(base, static_cast<const R*>(p.eta) + po, ri.j, ri.valid);
-#pragma unroll
-    for (int q = 0; q < E; ++q) pw[q] = base[q];
-    for (int jj = 2; jj <= l - 1; ++jj) {
-#pragma unroll
-        for (int q = 0; q < E; ++q) pw[q] = rmul(pw[q], base[q]);
-    }
-    const int ncomp = p.g.ny > 1 ? 2 : 1;
-    for (int comp = 0; comp < ncomp; ++comp) {
-        V w[E];
-        RW::load(a, static_cast<const R*>(comp == 0 ? p.phx : p.phy) + po, ri.j, ri.valid);
-#pragma unroll
-        for (int q = 0; q < E; ++q) w[q] = rmul(pw[q], a[q]);
-        RW::forward(w, static_cast<V*>(p.h[idx++]) + hb, rc, lds_all, twN, twX);
-    }
 }
 
 // nonlinear term of the potential equation; TANK adds the wave tank's surface
@@ -1743,9 +1602,8 @@ __global__ void k_diag(const DiagParams p) {
 // ---------------------------------------------------------------------------
 // workgroups along y of a row pass: the sweep splits its product families
 template <typename PT> static int row_families(const PT&) { return 1; }
-static int row_families(const RowSweepParams& p) { return p.nfam > 0 ? p.nfam : 1; }
-static int row_families(const RowSaParams& p) { return p.split > 0 ? p.split : 1; }
-static int row_families(const RowSetupParams& p) { return p.nfam > 1 ? p.nfam : 1; }
+static int row_families(const RowSweepParams& p) { return p.nfam * p.nch + (p.nch > 1 && p.residual ? 1 : 0); }
+static int row_families(const RowProdParams& p) { return p.nfam * p.nch; }
 
 template <typename RWT> struct RowLaunch {
     using V = typename RWT::V;
@@ -1840,10 +1698,9 @@ template <typename R, int NX, int VAR, bool SWEEP> constexpr bool row_var_built(
 
 SBI_ROW_LAUNCH(k_row_fwd, RowFwdParams)
 SBI_ROW_LAUNCH(k_row_inv, RowInvParams)
-SBI_ROW_LAUNCH(k_row_setup, RowSetupParams)
 SBI_ROW_LAUNCH_VAR(k_row_sweep, RowSweepParams, true)
 SBI_ROW_LAUNCH_VAR(k_row_sweep_aa, RowSweepParams, true)
-SBI_ROW_LAUNCH_VAR(k_row_sa, RowSaParams, false)
+SBI_ROW_LAUNCH_VAR(k_row_prod, RowProdParams, false)
 SBI_ROW_LAUNCH(k_row_nphi, RowNphiParams)
 SBI_ROW_LAUNCH(k_row_nphi_tank, RowNphiParams)
 SBI_ROW_LAUNCH(k_row_blend, RowBlendParams)
@@ -2076,9 +1933,6 @@ template <> hipError_t launch_row_fwd_t<Real>(const RowFwdParams& p, int b, cons
 template <> hipError_t launch_row_inv_t<Real>(const RowInvParams& p, int b, const Twiddles& tw, hipStream_t s) {
     return k_row_inv_nx<Real>(p, b, tw, s);
 }
-template <> hipError_t launch_row_setup_t<Real>(const RowSetupParams& p, int b, const Twiddles& tw, hipStream_t s) {
-    return k_row_setup_nx<Real>(p, b, tw, s);
-}
 template <typename R, int NX, bool SWEEP> static int row_var_mask_nx() {
     return (row_var_built<R, NX, 0, SWEEP>() ? 1 : 0) | (row_var_built<R, NX, 1, SWEEP>() ? 2 : 0) |
            (row_var_built<R, NX, 2, SWEEP>() ? 4 : 0) | (row_var_built<R, NX, 3, SWEEP>() ? 8 : 0);
@@ -2112,8 +1966,8 @@ template <> int row_rows_cap_t<Real>(int nx, int var) {
 template <> hipError_t launch_row_sweep_t<Real>(const RowSweepParams& p, int b, const Twiddles& tw, hipStream_t s) {
     return p.gT ? k_row_sweep_aa_nx<Real>(p, b, tw, s) : k_row_sweep_nx<Real>(p, b, tw, s);
 }
-template <> hipError_t launch_row_sa_t<Real>(const RowSaParams& p, int b, const Twiddles& tw, hipStream_t s) {
-    return k_row_sa_nx<Real>(p, b, tw, s);
+template <> hipError_t launch_row_prod_t<Real>(const RowProdParams& p, int b, const Twiddles& tw, hipStream_t s) {
+    return k_row_prod_nx<Real>(p, b, tw, s);
 }
 template <> hipError_t launch_row_nphi_t<Real>(const RowNphiParams& p, int b, const Twiddles& tw, hipStream_t s) {
     return (p.wm_n > 0 || p.dmp_w > 0.0) ? k_row_nphi_tank_nx<Real>(p, b, tw, s) : k_row_nphi_nx<Real>(p, b, tw, s);

@@ -22,19 +22,22 @@ struct RowInvParams {
     Ctl* ctl;
 };
 
-struct RowSetupParams {
+struct RowProdParams {
     GridDev g;
+    int nfam;                 // families src w^j, j = 1..J
+    int J;
+    int pc, nch;              // products per workgroup, workgroups per family (along y)
+    int bed;                  // bit f: family f is weighted with delta, else with eta
+    int check;                // bit f: flag non-finite values of family f's source
+    int lead;                 // family whose first workgroup serves eta (-1: none)
+    int extrema;              // the lead reduces max and min of eta
+    const void* src[5];       // half forms
     const void* g_eta;        // half form of eta (or null when eta_in is given)
-    const void* eta_in;       // physical eta given by the caller (or null)
-    void* eta_out;            // physical eta written (may be null when eta_in)
-    const void* g_px;         // half forms of the potential gradient
-    const void* g_py;
-    void* px_out;             // physical gradient (SA mode), may be null
-    void* py_out;
-    int nprod;                // forcing products eta^(l-1) grad phi, l = 2..L
-    void* h[kMaxProd];
+    const void* eta_in;       // physical eta
+    void* eta_out;            // physical eta written by the lead, may be null
+    const void* delta;        // physical
+    void* h[kMaxProd];        // [family][j - 1]
     Ctl* ctl;
-    int nfam;                 // 2: the x and y components in workgroups of their own (blockIdx.y)
 };
 
 struct RowSweepParams {
@@ -51,30 +54,10 @@ struct RowSweepParams {
     int products;       // form the products of this sweep
     int vd;             // variable depth
     int slot;
-    int nfam;           // workgroups along y: 0 eta^j V (+ residual), 1/2 delta^j d_x/d_y phi_b
+    int nfam;           // families along y: 0 eta^j V (+ residual), 1/2 delta^j d_x/d_y phi_b
+    int pc, nch;        // products per workgroup, workgroups per family (nch > 1: the residual has its own)
     void* h[kMaxProd];
     Ctl* ctl;
-};
-
-struct RowSaParams {
-    GridDev g;
-    int l;              // order being formed
-    int vd;
-    const void* gV;     // half form of V_(l-1)
-    const void* gbx;    // half forms of grad phi_b,(l-1) (vd and l-1 <= L-1)
-    const void* gby;
-    void* V_out;        // physical V_(l-1) (kept for higher orders), may be null
-    void* bx_out;
-    void* by_out;
-    const void* Vphys[8];   // physical V_m, m < l-1
-    const void* bxphys[8];
-    const void* byphys[8];
-    const void* eta;
-    const void* delta;
-    const void* phx;    // physical grad phi_s
-    const void* phy;
-    void* h[kMaxProd];
-    int split;          // > 0: workgroups per row block, one product each (blockIdx.y)
 };
 
 constexpr int kMaxWavemaker = 8;   // pneumatic wavemaker components
@@ -196,9 +179,8 @@ int col_tile(int ny);   // columns of a column-pass workgroup (ColShape::CW; 64 
 // per-precision launchers (defined in sbi_kernels.hip, one object per precision)
 template <typename R> hipError_t launch_row_fwd_t(const RowFwdParams&, int, const Twiddles&, hipStream_t);
 template <typename R> hipError_t launch_row_inv_t(const RowInvParams&, int, const Twiddles&, hipStream_t);
-template <typename R> hipError_t launch_row_setup_t(const RowSetupParams&, int, const Twiddles&, hipStream_t);
 template <typename R> hipError_t launch_row_sweep_t(const RowSweepParams&, int, const Twiddles&, hipStream_t);
-template <typename R> hipError_t launch_row_sa_t(const RowSaParams&, int, const Twiddles&, hipStream_t);
+template <typename R> hipError_t launch_row_prod_t(const RowProdParams&, int, const Twiddles&, hipStream_t);
 template <typename R> hipError_t launch_row_nphi_t(const RowNphiParams&, int, const Twiddles&, hipStream_t);
 template <typename R> hipError_t launch_row_blend_t(const RowBlendParams&, int, const Twiddles&, hipStream_t);
 template <typename R> hipError_t launch_row_feat_t(const RowFeatParams&, int, const Twiddles&, hipStream_t);
@@ -219,9 +201,8 @@ int row_rows_cap(int fp64, int nx, int var);
 
 hipError_t launch_row_fwd(int fp64, const RowFwdParams& p, int batch, const Twiddles& tw, hipStream_t s);
 hipError_t launch_row_inv(int fp64, const RowInvParams& p, int batch, const Twiddles& tw, hipStream_t s);
-hipError_t launch_row_setup(int fp64, const RowSetupParams& p, int batch, const Twiddles& tw, hipStream_t s);
 hipError_t launch_row_sweep(int fp64, const RowSweepParams& p, int batch, const Twiddles& tw, hipStream_t s);
-hipError_t launch_row_sa(int fp64, const RowSaParams& p, int batch, const Twiddles& tw, hipStream_t s);
+hipError_t launch_row_prod(int fp64, const RowProdParams& p, int batch, const Twiddles& tw, hipStream_t s);
 hipError_t launch_row_nphi(int fp64, const RowNphiParams& p, int batch, const Twiddles& tw, hipStream_t s);
 hipError_t launch_row_blend(int fp64, const RowBlendParams& p, int batch, const Twiddles& tw, hipStream_t s);
 hipError_t launch_row_feat(int fp64, const RowFeatParams& p, int batch, const Twiddles& tw, hipStream_t s);
