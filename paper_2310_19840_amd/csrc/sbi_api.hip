@@ -150,6 +150,7 @@ struct sbi_ctx {
     void* full_rs2 = nullptr;
     void* full_rhs = nullptr;
     void* full_lfl = nullptr;
+    void* full_rfl = nullptr;
     void* full_w = nullptr;
     void* full_part = nullptr;
     // two-boundary form of the fully nonlinear solve (variable beds)
@@ -307,7 +308,7 @@ static Layout layout(const sbi_grid* g, int batch) {
     // geometry (3 tables), its circulant, its right-hand side and two phi_b
     // iterates [batch][nx], and the per-member flags
     L.bytes_full = g->mode == SBI_MODE_FULL
-                       ? 16 * al((size_t)g->nx * 8 * batch) + al((size_t)full_slices(g->nx) * g->nx * 8 * batch) +
+                       ? 17 * al((size_t)g->nx * 8 * batch) + al((size_t)full_slices(g->nx) * g->nx * 8 * batch) +
                              al(sizeof(int) * batch)
                        : 0;
     // mixed precision: the FP32 context's workspace at the end
@@ -554,8 +555,9 @@ static sbi_status ctx_setup(sbi_ctx* c, const sbi_grid* g, int32_t batch, const 
         c->full_pb[1] = p + 13 * tb;
         c->full_s2a = p + 14 * tb;
         c->full_rs2 = p + 15 * tb;
-        c->full_part = p + 16 * tb;
-        c->full_bed = reinterpret_cast<int*>(p + 16 * tb + al((size_t)full_slices(g->nx) * g->nx * 8 * batch));
+        c->full_rfl = p + 16 * tb;
+        c->full_part = p + 17 * tb;
+        c->full_bed = reinterpret_cast<int*>(p + 17 * tb + al((size_t)full_slices(g->nx) * g->nx * 8 * batch));
     }
     gd.col_C = L.C;
     gd.href = c->href_dev;
@@ -1633,6 +1635,7 @@ static FullParams full_params(sbi_ctx* c) {
     p.exx = PHYS(PF_EXX);
     p.rhs = c->full_rhs;
     p.lfl = c->full_lfl;
+    p.rfl = c->full_rfl;
     p.w = c->full_w;
     p.vbuf[0] = PHYS(PF_B0);
     p.vbuf[1] = PHYS(PF_B1);

@@ -62,6 +62,12 @@ __device__ __forceinline__ bool full_deep(const FullParams& p, int m) {
     return (2.0 * M_PI / p.lx) * p.href[m] > kDeepK1H;
 }
 
+__device__ __forceinline__ bool full_bed(const FullParams& p, int m) { return p.bed && p.bed[m]; }
+// scaled distance of the flat geometry: surface to image 2 pi h / L, surface to bed pi h / L
+__device__ __forceinline__ double full_flat(const FullParams& p, int m) {
+    return (full_bed(p, m) ? 1.0 : 2.0) * M_PI * p.href[m] / p.lx;
+}
+
 // --- tables: S0^-1 (per member: its depth), eta_x and eta_xx circulants,
 // sin^2(pi j / n), and the circulant cm of S0^-1 (S0 - S_flat) (multiplier
 // exp(-2|k|h) / (1 + exp(-2|k|h))).  c[j] = (1/n) sum_m s(k_m) cos(2 pi m j / n) with
@@ -97,9 +103,13 @@ __global__ void __launch_bounds__(kFullThreads) k_full_tables(const FullParams p
     static_cast<double*>(p.c0)[(long long)m * n + j] = c / n;
     if (p.cm) static_cast<double*>(p.cm)[(long long)m * n + j] = cm / n;
     {
-        // the flat image's single-layer term 1/2 ln(sin^2(pi j / n) + sinh^2(2 pi h / L)) of this member
-        const double sn = sinpi((double)j / n), sh = deep ? 0.0 : sinh(2.0 * M_PI * h / p.lx);
-        static_cast<double*>(p.lfl)[(long long)m * n + j] = deep ? 0.0 : 0.5 * log(sn * sn + sh * sh);
+        // the flat geometry a pair kernel's logarithm is taken against: between
+        // the surface and its image, or (two-boundary members) surface and bed;
+        // 1/2 ln(sin^2(pi j / n) + sinh^2) and 1 / (sin^2 + sinh^2)
+        const double sn = sinpi((double)j / n), sh = deep && !full_bed(p, m) ? 0.0 : sinh(full_flat(p, m));
+        const bool none = deep && !full_bed(p, m);
+        static_cast<double*>(p.lfl)[(long long)m * n + j] = none ? 0.0 : 0.5 * log(sn * sn + sh * sh);
+        static_cast<double*>(p.rfl)[(long long)m * n + j] = none ? 0.0 : 1.0 / (sn * sn + sh * sh);
     }
     if (m == 0) {
         static_cast<double*>(p.d1)[j] = d1 / n;
@@ -148,8 +158,6 @@ __global__ void __launch_bounds__(kFullThreads) k_full_bedgeom(const FullParams 
         static_cast<double*>(p.bxx)[(long long)m * n + i] = a2;
     }
 }
-
-__device__ __forceinline__ bool full_bed(const FullParams& p, int m) { return p.bed && p.bed[m]; }
 
 // Decision of launch `sweep` from the residual of the previous one (the
 // iteration mode's rules); every workgroup decides alike, the leader records.
@@ -208,11 +216,79 @@ template <typename R> __device__ __forceinline__ R sinh_cosh_series(R x, R* ch) 
     return sinh_series(x);
 }
 
+// a / b for a positive, normal b: the reciprocal's two Newton steps and a
+// correction of the quotient, without the scaling of the general division
+__device__ __forceinline__ double pair_div(double a, double b) {
+    double r = __builtin_amdgcn_rcp(b);
+    r = fma(fma(-b, r, 1.0), r, r);
+    r = fma(fma(-b, r, 1.0), r, r);
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+}
+__device__ __forceinline__ float pair_div(float a, float b) { return a / b; }
+
+// log(1 + x).  The pair kernels' arguments are the height differences' effect
+// on a squared distance, small except for the nearest points: below, as
+// 2 atanh(s), s = x / (2 + x), by its series to s^21 (the next term is below
+// 2e-18 of the value for |s| <= 0.177); the library function elsewhere.
+__device__ __forceinline__ double pair_log1p(double x) {
+    if (!(x > -0.3 && x < 0.42)) return log1p(x);
+    const double s = pair_div(x, 2.0 + x), z = s * s;
+    double q = 1.0 / 21.0;
+    q = fma(q, z, 1.0 / 19.0);
+    q = fma(q, z, 1.0 / 17.0);
+    q = fma(q, z, 1.0 / 15.0);
+    q = fma(q, z, 1.0 / 13.0);
+    q = fma(q, z, 1.0 / 11.0);
+    q = fma(q, z, 1.0 / 9.0);
+    q = fma(q, z, 1.0 / 7.0);
+    q = fma(q, z, 1.0 / 5.0);
+    q = fma(q, z, 1.0 / 3.0);
+    return fma(2.0 * s * z, q, 2.0 * s);
+}
+__device__ __forceinline__ float pair_log1p(float x) { return log1p(x); }
+
+// A pair pass: kFullThreads evaluation points per workgroup, each served by
+// kPairLanes threads over a part of every staged block of sources (one thread
+// per point leaves one wavefront per SIMD, and its chains of dependent FP64
+// operations then wait on themselves); the lanes' sums are added in order.
+// Bound by the issue of FP64 operations, 60 to 75 a pair.  FP64, 4096 points,
+// per pass: the bed pass 83 us, the surface pass 55, the double layer 52 (148,
+// 174 and 114 with one thread per point, the library's logarithms, the general
+// division and a sinh of each pair's height difference).
+constexpr int kPairLanes = 4;
+constexpr int kPairThreads = kFullThreads * kPairLanes;
+// sum over the lanes of a point; red holds (kPairLanes - 1) * kFullThreads values
+__device__ __forceinline__ double pair_fold(double acc, double* red, int lane, int il) {
+    if (lane > 0) red[(lane - 1) * kFullThreads + il] = acc;
+    __syncthreads();
+    if (lane == 0)
+#pragma unroll
+        for (int l = 1; l < kPairLanes; ++l) acc += red[(l - 1) * kFullThreads + il];
+    return acc;
+}
+// Source block j0 .. of a slice: lane's points [jl0, jl1) within the block
+struct PairBlock {
+    int jl0, jl1;
+};
+__device__ __forceinline__ PairBlock pair_block(int j0, int jend, int lane) {
+    const int jn = min(kFullThreads, jend - j0);
+    const int per = (jn + kPairLanes - 1) / kPairLanes;
+    return {min(jn, lane * per), min(jn, (lane + 1) * per)};
+}
+
+// The sinh and cosh of the distance between two boundaries, pi (y - y') / L =
+// a + b with a >= 0 from the lower one and b from the upper (the image, the
+// bed), come from per-point tables: sinh a cosh b + cosh a sinh b.  The
+// boundaries do not touch, so the sum does not cancel beyond what the
+// difference of the heights does.
 template <typename R, int KIND>
-__global__ void __launch_bounds__(kFullThreads) k_full_pairs(const FullParams p) {
-    __shared__ R te[kFullThreads], tex[kFullThreads], tsrc[kFullThreads];
+__global__ void __launch_bounds__(kPairThreads) k_full_pairs(const FullParams p) {
+    __shared__ R te[kFullThreads], tex[kFullThreads], tsrc[kFullThreads], tsj[kFullThreads], tcj[kFullThreads];
+    __shared__ double red[(kPairLanes - 1) * kFullThreads];
     const int t = threadIdx.x;
-    const int i = blockIdx.x * kFullThreads + t;
+    const int il = t % kFullThreads, lane = __builtin_amdgcn_readfirstlane(t / kFullThreads);
+    const int i = blockIdx.x * kFullThreads + il;
     const int split = blockIdx.y;
     const int m = blockIdx.z;
     const int n = p.n;
@@ -229,70 +305,75 @@ __global__ void __launch_bounds__(kFullThreads) k_full_pairs(const FullParams p)
     const double* s2 = static_cast<const double*>(p.s2);
     const double* rs2 = static_cast<const double*>(p.rs2);
     const double* s2at = static_cast<const double*>(p.s2a);
-    const double* lfl = static_cast<const double*>(p.lfl) + (long long)m * n;
+    const double* rfl = static_cast<const double*>(p.rfl) + (long long)m * n;
     const R pl = R(M_PI / p.lx);
-    const bool deep = full_deep(p, m);
-    const bool img = !deep && !full_bed(p, m);       // the image form keeps the bed's image
-    const R b2h = R(2.0 * M_PI * p.href[m] / p.lx);  // 2 pi h / L
+    const bool img = !full_deep(p, m) && !full_bed(p, m);  // the image form keeps the bed's image
+    const R b2h = R(2.0 * M_PI * p.href[m] / p.lx);        // 2 pi h / L
+    const R sh0 = img ? sinh(b2h) : R(0);
     // this point's values
     const bool on = i < n;
     const R etai = on ? eta[i] : R(0);
     const R exi = on ? ex[i] : R(0);
+    R sbi = R(0), cbi = R(1);
+    if (img) {
+        const R b = pl * etai + b2h;
+        sbi = sinh(b);
+        cbi = cosh(b);
+    }
     double acc = 0.0;
     const int chunk = (n + gridDim.y - 1) / gridDim.y;
     const int jbeg = split * chunk, jend = min(n, jbeg + chunk);
     for (int j0 = jbeg; j0 < jend; j0 += kFullThreads) {
         __syncthreads();
-        const int jl = j0 + t;
-        if (jl < jend) {
-            te[t] = eta[jl];
-            tex[t] = ex[jl];
-            tsrc[t] = src[jl];
+        if (t < kFullThreads && j0 + t < jend) {
+            te[t] = eta[j0 + t];
+            tex[t] = ex[j0 + t];
+            tsrc[t] = src[j0 + t];
+            if (img) {
+                tsj[t] = sinh(pl * te[t]);
+                tcj[t] = cosh(pl * te[t]);
+            }
         }
         __syncthreads();
-        const int jn = min(kFullThreads, jend - j0);
         if (!on) continue;
-        for (int jj = 0; jj < jn; ++jj) {
+        const PairBlock pb = pair_block(j0, jend, lane);
+        for (int jj = pb.jl0; jj < pb.jl1; ++jj) {
             const int j = j0 + jj;
             const int d = (j - i + n) & (n - 1);
-            const R sa2 = R(s2[d]);                       // sin^2(pi (x_j - x_i) / L)
-            // sinh of the scaled elevation difference, formed from the difference
-            // itself (from exponentials of each point it would lose all relative
-            // accuracy for nearby points)
-            R chb;
-            const R shb = sinh_cosh_series(pl * (te[jj] - etai), &chb);  // sinh(pi (eta_j - eta_i) / L)
             R kv;
             if (KIND == 1) {
-                // -1/2 ln(1 + sinh^2 / sin^2); its limit -1/2 ln(1 + eta_x^2) at j = i
-                kv = j == i ? R(-0.5) * log1p(exi * exi) : R(-0.5) * log1p(shb * shb * R(rs2[d]));
+                // direct part -1/2 ln(1 + sinh^2 / sin^2) (its limit -1/2 ln(1 + eta_x^2) at j = i) and
+                // image minus flat image, -1/2 ln((sin^2 + sinh^2(pi (eta_i + eta_j + 2h) / L)) / (sin^2 +
+                // sinh^2(2 pi h / L))), as one logarithm
+                const R shb = sinh_series(pl * (te[jj] - etai));
+                R x = j == i ? exi * exi : shb * shb * R(rs2[d]);
                 if (img) {
-                    // image minus flat image: -1/2 ln(sin^2 + sinh^2(pi (eta_i + eta_j + 2h) / L))
-                    // + 1/2 ln(sin^2 + sinh^2(2 pi h / L))
-                    const R shp = sinh_series(pl * (te[jj] + etai) + b2h);
-                    kv += R(-0.5) * log(sa2 + shp * shp) + R(lfl[d]);
+                    const R shp = tsj[jj] * cbi + tcj[jj] * sbi;
+                    const R y = (shp - sh0) * (shp + sh0) * R(rfl[d]);
+                    x = x + y + x * y;
                 }
+                kv = R(-0.5) * pair_log1p(x);
             } else {
                 // Im[(pi/L) cot(a + i b) (1 + i eta_x,j)], a = pi (x_j - x_i)/L, b = pi (eta_j - eta_i)/L:
                 // cot(a + i b) = (sin 2a - i sinh 2b) / (2 (sin^2 a + sinh^2 b))
+                const R sa2 = R(s2[d]);  // sin^2 a
                 const R s2a = R(s2at[d]);  // sin 2a
-                if (j == i) {
-                    kv = R(0);  // the curvature limit is added below
-                } else {
-                    const R den = R(2) * (sa2 + shb * shb);
-                    kv = pl * (R(-2) * shb * chb + s2a * tex[jj]) / den;
-                }
+                R chb;
+                const R shb = sinh_cosh_series(pl * (te[jj] - etai), &chb);
+                // the curvature limit at j = i is added below
+                kv = j == i ? R(0) : pair_div(R(-2) * shb * chb + s2a * tex[jj], sa2 + shb * shb);
                 if (img) {
                     // the image partner: b' = pi (eta_i + eta_j + 2h) / L
-                    R chp;
-                    const R shp = sinh_cosh_series(pl * (te[jj] + etai) + b2h, &chp);
-                    const R den = R(2) * (sa2 + shp * shp);
-                    kv += pl * (R(-2) * shp * chp + s2a * tex[jj]) / den;
+                    const R shp = tsj[jj] * cbi + tcj[jj] * sbi, chp = tcj[jj] * cbi + tsj[jj] * sbi;
+                    kv += pair_div(R(-2) * shp * chp + s2a * tex[jj], sa2 + shp * shp);
                 }
+                kv *= R(0.5) * pl;
             }
             acc += (double)kv * (double)tsrc[jj];
         }
     }
-    if (!on) return;
+    acc = pair_fold(acc, red, lane, il);
+    if (!on || lane > 0) return;
     const double dx = p.lx / n;
     double out = acc * dx;
     if (KIND == 0 && i >= jbeg && i < jend) {
@@ -308,20 +389,26 @@ __global__ void __launch_bounds__(kFullThreads) k_full_pairs(const FullParams p)
 // image depend on |eta_j - eta_i|, eta_i + eta_j and sin^2(pi (x_j - x_i)/L)).
 // The n x n pairs split into tiles of kSymT x kSymT points; a workgroup takes
 // tile (I, J), I <= J, evaluates each of its pairs once and adds K V_j to the
-// row sums of its points i in block I and K V_i (reduced over a wavefront's
-// rows) to the column sums of its points j in block J.  Row sums go to slice J
-// of the points of block I, column sums to slice I of those of block J, so
-// every point receives n / kSymT slices, one from each block, each written
-// once; a diagonal tile (I = I) evaluates all its pairs and writes rows only.
+// row sums of its points i in block I and K V_i to the column sums of its
+// points j in block J.  Row sums go to slice J of the points of block I, column
+// sums to slice I of those of block J, so every point receives n / kSymT slices,
+// one from each block, each written once; a diagonal tile (I = J) evaluates all
+// its pairs and writes rows only.
+//
+// Bound by the issue of FP64 operations (about 50 a pair).  A tile's 64 columns
+// are the lanes of a wavefront and its four wavefronts take a quarter of the
+// tile's diagonals each: at 4096 points 2080 workgroups, eight to nine per CU
+// (tiles of 128 leave two or three, a third of the chip idle at the end).  FP64,
+// 4096 points: 39 us per pass, against 109 with tiles of 128 and two library
+// logarithms a pair.
 constexpr int kSymT = kFullSymTile;
-constexpr int kSymThreads = 2 * kSymT;  // two threads per row, each over half the tile's columns
-static_assert(kSymT / 2 == 64, "a half tile's columns are the lanes of one wavefront");
+constexpr int kSymWaves = 4;
+static_assert(kSymT == 64, "a tile's columns are the lanes of one wavefront");
 
 template <typename R>
-__global__ void __launch_bounds__(kSymThreads) k_full_sympairs(const FullParams p) {
+__global__ void __launch_bounds__(64 * kSymWaves) k_full_sympairs(const FullParams p) {
     __shared__ R tej[kSymT], tvj[kSymT], tsj[kSymT], tcj[kSymT];
-    __shared__ double colp[kSymThreads / 64][kSymT / 2];
-    __shared__ double rowp[2][kSymT];
+    __shared__ double colp[kSymWaves][kSymT], rowp[kSymWaves][kSymT];
     const int t = threadIdx.x;
     const int m = blockIdx.z;
     const int n = p.n;
@@ -344,21 +431,16 @@ __global__ void __launch_bounds__(kSymThreads) k_full_sympairs(const FullParams 
     const R* eta = static_cast<const R*>(p.eta) + mo;
     const R* ex = static_cast<const R*>(p.ex) + mo;
     const R* v = static_cast<const R*>(p.vin) + mo;
-    const double* s2 = static_cast<const double*>(p.s2);
     const double* rs2 = static_cast<const double*>(p.rs2);
-    const double* lfl = static_cast<const double*>(p.lfl) + (long long)m * n;
+    const double* rfl = static_cast<const double*>(p.rfl) + (long long)m * n;
     const R pl = R(M_PI / p.lx);
     const bool img = !full_deep(p, m);
     const R b2h = R(2.0 * M_PI * p.href[m] / p.lx);
-    const int il = t % kSymT, hf = t / kSymT;
-    const int i = I * kSymT + il;
+    const R sh0 = img ? sinh(b2h) : R(0);
+    const int wv = t / 64, ln = t & 63;
+    const int i = I * kSymT + ln;
     const R etai = eta[i], exi = ex[i];
     const double vi = (double)v[i];
-    // the image's sinh(pi (eta_j + eta_i + 2h) / L) as sinh(a_j + b_i) =
-    // sinh a_j cosh b_i + cosh a_j sinh b_i, a_j = pi eta_j / L, b_i = pi eta_i
-    // / L + 2 pi h / L: one sinh and cosh per point instead of a sinh per pair
-    // (with the bed below the surface b_i > |a_j|, so the second term
-    // dominates the first and the sum does not cancel)
     R sbi = R(0), cbi = R(1);
     if (img) {
         const R b = pl * etai + b2h;
@@ -375,43 +457,50 @@ __global__ void __launch_bounds__(kSymThreads) k_full_sympairs(const FullParams 
         }
     }
     __syncthreads();
-    const int wv = t / 64, ln = t & 63;
     const int from = (ln + 1) & 63;
+    constexpr int kSteps = kSymT / kSymWaves;
     double acc = 0.0, cacc = 0.0;
-    for (int jj = 0; jj < kSymT / 2; ++jj) {
-        // lane ln takes the columns of its half in the order ln, ln + 1, ...
-        // (mod 64): at each step the lanes of a wavefront hold 64 different
-        // columns, and the running column sum moves one lane down with its column
-        const int jl = hf * (kSymT / 2) + ((ln + jj) & (kSymT / 2 - 1));
+#pragma unroll 2
+    for (int s = 0; s < kSteps; ++s) {
+        // lane ln takes the columns ln + kSteps wv, + 1, ... (mod 64): at each
+        // step the lanes of a wavefront hold 64 different columns, and the
+        // running column sum moves one lane down with its column
+        const int jl = (ln + wv * kSteps + s) & 63;
         const int j = J * kSymT + jl;
         const int d = (j - i + n) & (n - 1);
-        const R sa2 = R(s2[d]);
         const R shb = sinh_series(pl * (tej[jl] - etai));
-        R kv = j == i ? R(-0.5) * log1p(exi * exi) : R(-0.5) * log1p(shb * shb * R(rs2[d]));
+        R x = j == i ? exi * exi : shb * shb * R(rs2[d]);
         if (img) {
             const R shp = tsj[jl] * cbi + tcj[jl] * sbi;
-            kv += R(-0.5) * log(sa2 + shp * shp) + R(lfl[d]);
+            const R y = (shp - sh0) * (shp + sh0) * R(rfl[d]);
+            x = x + y + x * y;
         }
-        acc += (double)kv * (double)tvj[jl];
+        const double kv = (double)(R(-0.5) * pair_log1p(x));
+        acc += kv * (double)tvj[jl];
         if (!diag) {
             // the pair seen from j: K V_i added to column jl's sum over this
             // wavefront's rows, which lane ln - 1 continues at the next step
-            cacc += (double)kv * vi;
+            cacc += kv * vi;
             cacc = __shfl(cacc, from, 64);
         }
     }
-    rowp[hf][il] = acc;
-    if (!diag) colp[wv][ln] = cacc;  // after 64 steps lane ln holds column ln of its half
+    rowp[wv][ln] = acc;
+    if (!diag) colp[wv][(ln + (wv + 1) * kSteps) & 63] = cacc;
     __syncthreads();
     if (t < kSymT) {
         const double dx = p.lx / n;
         double* part = static_cast<double*>(p.part);
+        double a = 0.0;
+#pragma unroll
+        for (int w = 0; w < kSymWaves; ++w) a += rowp[w][t];
         // rows of block I: slice J
-        part[((long long)J * p.batch + m) * n + I * kSymT + t] = (rowp[0][t] + rowp[1][t]) * dx;
+        part[((long long)J * p.batch + m) * n + I * kSymT + t] = a * dx;
         if (!diag) {
-            // columns of block J: slice I; column jl collects the two wavefronts of its half
-            const int h2 = t / (kSymT / 2), q = t % (kSymT / 2);
-            part[((long long)I * p.batch + m) * n + J * kSymT + t] = (colp[2 * h2][q] + colp[2 * h2 + 1][q]) * dx;
+            // columns of block J: slice I
+            double c = 0.0;
+#pragma unroll
+            for (int w = 0; w < kSymWaves; ++w) c += colp[w][t];
+            part[((long long)I * p.batch + m) * n + J * kSymT + t] = c * dx;
         }
     }
 }
@@ -420,11 +509,13 @@ __global__ void __launch_bounds__(kSymThreads) k_full_sympairs(const FullParams 
 // image; V_n absent at the first sweep) minus D_SB[phi_b] with the phi_b of
 // this sweep, at the surface points over a slice of the source points
 template <typename R>
-__global__ void __launch_bounds__(kFullThreads) k_full_spairs(const FullParams p) {
-    __shared__ R te[kFullThreads], tsrc[kFullThreads];
-    __shared__ double tbz[kFullThreads], tbx[kFullThreads], tpb[kFullThreads];
+__global__ void __launch_bounds__(kPairThreads) k_full_spairs(const FullParams p) {
+    __shared__ R te[kFullThreads], tsrc[kFullThreads], tsj[kFullThreads], tcj[kFullThreads], tbx[kFullThreads];
+    __shared__ double tpb[kFullThreads];
+    __shared__ double red[(kPairLanes - 1) * kFullThreads];
     const int t = threadIdx.x;
-    const int i = blockIdx.x * kFullThreads + t;
+    const int il = t % kFullThreads, lane = __builtin_amdgcn_readfirstlane(t / kFullThreads);
+    const int i = blockIdx.x * kFullThreads + il;
     const int split = blockIdx.y;
     const int m = blockIdx.z;
     const int n = p.n;
@@ -450,41 +541,44 @@ __global__ void __launch_bounds__(kFullThreads) k_full_spairs(const FullParams p
     const bool on = i < n;
     const R etai = on ? eta[i] : R(0);
     const R exi = on ? ex[i] : R(0);
-    double acc = 0.0;
+    const R sei = sinh(pl * etai), cei = cosh(pl * etai);
+    double accb = 0.0, accs = 0.0;
     const int chunk = (n + gridDim.y - 1) / gridDim.y;
     const int jbeg = split * chunk, jend = min(n, jbeg + chunk);
     for (int j0 = jbeg; j0 < jend; j0 += kFullThreads) {
         __syncthreads();
         const int jl = j0 + t;
-        if (jl < jend) {
+        if (t < kFullThreads && jl < jend) {
             te[t] = eta[jl];
             tsrc[t] = hasv ? src[jl] : R(0);
-            tbz[t] = bz[jl];
-            tbx[t] = bxs[jl];
+            const double b = -pld * bz[jl];  // the bed's depth below z = 0
+            tsj[t] = R(sinh(b));
+            tcj[t] = R(cosh(b));
+            tbx[t] = R(bxs[jl]);
             tpb[t] = pbs[jl];
         }
         __syncthreads();
-        const int jn = min(kFullThreads, jend - j0);
         if (!on) continue;
-        for (int jj = 0; jj < jn; ++jj) {
+        const PairBlock pb = pair_block(j0, jend, lane);
+#pragma unroll 2
+        for (int jj = pb.jl0; jj < pb.jl1; ++jj) {
             const int j = j0 + jj;
             const int d = (j - i + n) & (n - 1);
             const R sa2 = R(s2[d]);
             const R s2a = R(s2at[d]);
             // the bed source (x_j, b_j): -D_SB = Im[(pi/L) cot(a + i b) (1 + i b_x,j)],
-            // b = pi (b_j - eta_i) / L (the bed lies below every surface point)
-            R ch;
-            const R sh = sinh_cosh_series(R(pld * (tbz[jj] - (double)etai)), &ch);
-            acc += (double)(pl * (R(-2) * sh * ch + s2a * R(tbx[jj])) / (R(2) * (sa2 + sh * sh))) * tpb[jj];
+            // b = pi (b_j - eta_i) / L (the bed lies below every surface point): -b from the tables
+            const R sh = tsj[jj] * cei + tcj[jj] * sei, ch = tcj[jj] * cei + tsj[jj] * sei;
+            accb += (double)pair_div(R(2) * sh * ch + s2a * tbx[jj], sa2 + sh * sh) * tpb[jj];
             if (hasv) {
                 // the direct single layer minus the flat one, as in the image form
                 const R shb = sinh_series(pl * (te[jj] - etai));
-                const R kv = j == i ? R(-0.5) * log1p(exi * exi) : R(-0.5) * log1p(shb * shb * R(rs2[d]));
-                acc += (double)kv * (double)tsrc[jj];
+                accs += (double)pair_log1p(j == i ? exi * exi : shb * shb * R(rs2[d])) * (double)tsrc[jj];
             }
         }
     }
-    if (!on) return;
+    const double acc = pair_fold(0.5 * (double)pl * accb - 0.5 * accs, red, lane, il);
+    if (!on || lane > 0) return;
     static_cast<double*>(p.part)[((long long)split * p.batch + m) * n + i] = acc * (p.lx / n);
 }
 
@@ -493,16 +587,18 @@ __global__ void __launch_bounds__(kFullThreads) k_full_spairs(const FullParams p
 // S_BS[V_n] - D_BB[phi_b] (surface and bed sources, phi_b of this sweep),
 // which also decides the sweep.  With a = pi (x_j - x_i) / L and b the scaled
 // height difference pi (y_j - y_i) / L of source and evaluation point:
-// G = -1/2 ln(4 (sin^2 a + sinh^2 b)); the double layer of a surface source is
-// Im[(pi/L) cot(a + i b) (1 + i eta_x,j)], that of a bed source
-// -Im[(pi/L) cot(a + i b) (1 + i b_x,j)], with the curvature limit
-// -b_xx / (2 (1 + b_x^2)) at coincident bed points.
+// G = -1/2 ln(4 (sin^2 a + sinh^2 b)), taken against the flat geometry's table;
+// the double layer of a surface source is Im[(pi/L) cot(a + i b) (1 + i eta_x,j)],
+// that of a bed source -Im[(pi/L) cot(a + i b) (1 + i b_x,j)], with the curvature
+// limit -b_xx / (2 (1 + b_x^2)) at coincident bed points.
 template <typename R, int KIND>
-__global__ void __launch_bounds__(kFullThreads) k_full_bpairs(const FullParams p) {
-    __shared__ R te[kFullThreads], tex[kFullThreads], tsrc[kFullThreads];
+__global__ void __launch_bounds__(kPairThreads) k_full_bpairs(const FullParams p) {
+    __shared__ R tex[kFullThreads], tsrc[kFullThreads], tsj[kFullThreads], tcj[kFullThreads];
     __shared__ double tbz[kFullThreads], tbx[kFullThreads], tpb[kFullThreads];
+    __shared__ double red[(kPairLanes - 1) * kFullThreads];
     const int t = threadIdx.x;
-    const int i = blockIdx.x * kFullThreads + t;
+    const int il = t % kFullThreads, lane = __builtin_amdgcn_readfirstlane(t / kFullThreads);
+    const int i = blockIdx.x * kFullThreads + il;
     const int split = blockIdx.y;
     const int m = blockIdx.z;
     const int n = p.n;
@@ -521,18 +617,24 @@ __global__ void __launch_bounds__(kFullThreads) k_full_bpairs(const FullParams p
     const double* pbs = KIND == 3 ? static_cast<const double*>(p.pbin) + mb : nullptr;
     const double* s2 = static_cast<const double*>(p.s2);
     const double* s2at = static_cast<const double*>(p.s2a);
+    const double* lfl = static_cast<const double*>(p.lfl) + mb;
+    const double* rfl = static_cast<const double*>(p.rfl) + mb;
     const R pl = R(M_PI / p.lx);
     const double pld = M_PI / p.lx;
+    const R sh0 = R(sinh(full_flat(p, m)));
     const bool on = i < n;
     const double bzi = on ? bz[i] : 0.0;
-    double acc = 0.0;
+    const R sbi = R(sinh(-pld * bzi)), cbi = R(cosh(pld * bzi));  // the bed point's depth below z = 0
+    double acc = 0.0, accb = 0.0;
     const int chunk = (n + gridDim.y - 1) / gridDim.y;
     const int jbeg = split * chunk, jend = min(n, jbeg + chunk);
     for (int j0 = jbeg; j0 < jend; j0 += kFullThreads) {
         __syncthreads();
         const int jl = j0 + t;
-        if (jl < jend) {
-            te[t] = eta[jl];
+        if (t < kFullThreads && jl < jend) {
+            const R e = pl * eta[jl];
+            tsj[t] = sinh(e);
+            tcj[t] = cosh(e);
             tex[t] = ex[jl];
             tsrc[t] = src[jl];
             if (KIND == 3) {
@@ -542,32 +644,34 @@ __global__ void __launch_bounds__(kFullThreads) k_full_bpairs(const FullParams p
             }
         }
         __syncthreads();
-        const int jn = min(kFullThreads, jend - j0);
         if (!on) continue;
-        for (int jj = 0; jj < jn; ++jj) {
+        const PairBlock pb = pair_block(j0, jend, lane);
+#pragma unroll 2
+        for (int jj = pb.jl0; jj < pb.jl1; ++jj) {
             const int j = j0 + jj;
             const int d = (j - i + n) & (n - 1);
-            const R sa2 = R(s2[d]);
             const R s2a = R(s2at[d]);
+            const R sa2 = R(s2[d]);
             // the surface source (x_j, eta_j) seen from the bed point (x_i, b_i)
-            R ch;
-            const R sh = sinh_cosh_series(R(pld * ((double)te[jj] - bzi)), &ch);
-            const R den = R(2) * (sa2 + sh * sh);
+            const R sh = tsj[jj] * cbi + tcj[jj] * sbi;
             if (KIND == 2) {
-                acc += (double)(pl * (R(-2) * sh * ch + s2a * tex[jj]) / den) * (double)tsrc[jj];
+                const R ch = tcj[jj] * cbi + tsj[jj] * sbi;
+                acc += (double)pair_div(R(-2) * sh * ch + s2a * tex[jj], sa2 + sh * sh) * (double)tsrc[jj];
             } else {
-                acc += (double)(R(-0.5) * log(R(2) * den)) * (double)tsrc[jj];
+                const R y = (sh - sh0) * (sh + sh0) * R(rfl[d]);
+                acc += (lfl[d] + M_LN2 + 0.5 * (double)pair_log1p(y)) * (double)tsrc[jj];
                 if (j != i) {
                     // minus the bed's double layer at (x_j, b_j)
                     R chb;
                     const R shb = sinh_cosh_series(R(pld * (tbz[jj] - bzi)), &chb);
-                    const R denb = R(2) * (sa2 + shb * shb);
-                    acc += (double)(pl * (R(-2) * shb * chb + s2a * R(tbx[jj])) / denb) * tpb[jj];
+                    accb += (double)pair_div(R(-2) * shb * chb + s2a * R(tbx[jj]), sa2 + shb * shb) * tpb[jj];
                 }
             }
         }
     }
-    if (!on) return;
+    const double hpl = 0.5 * (double)pl;
+    acc = pair_fold(KIND == 2 ? hpl * acc : hpl * accb - acc, red, lane, il);
+    if (!on || lane > 0) return;
     const double dx = p.lx / n;
     double out = acc * dx;
     if (KIND == 3 && i >= jbeg && i < jend) {
@@ -619,19 +723,31 @@ __global__ void k_full_rhs(const FullParams p) {
 // --- w = rhs - (S - S0)[V_n], or rhs - (S - S_flat)[V_n] + D_SB[phi_b] (the
 // slices of the surface pass, in order; w = rhs at the first sweep of the
 // image form, from V_0 = 0)
+// The slices of 64 points are shared by kCombLanes wavefronts, whose sums are
+// added in order: one thread per point would wait for its loads slice by slice.
+constexpr int kCombLanes = 8;
 template <typename R>
-__global__ void k_full_combine(const FullParams p) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(64 * kCombLanes) k_full_combine(const FullParams p) {
+    __shared__ double red[kCombLanes][64];
+    const int t = threadIdx.x & 63, lane = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + t;
     const int m = blockIdx.z;
-    if (i >= p.n) return;
-    if (p.ctl[m].done) return;  // decided by this sweep's pair pass
+    if (p.ctl[m].done) return;  // decided by this sweep's pair pass (workgroup-uniform)
     const long long o = (long long)m * p.n + i;
-    double w = static_cast<const double*>(p.rhs)[o];
     // slices: those of the two-boundary surface pass, or of the image form's
     // single layer (nsym of the symmetric pass when it ran)
-    const int ns = full_bed(p, m) ? p.nsplit : (p.nsym > 0 ? p.nsym : p.nsplit);
-    if (p.vin || full_bed(p, m))
-        for (int s = 0; s < ns; ++s) w -= static_cast<const double*>(p.part)[((long long)s * p.batch + m) * p.n + i];
+    const int ns = !(p.vin || full_bed(p, m)) ? 0 : (full_bed(p, m) ? p.nsplit : (p.nsym > 0 ? p.nsym : p.nsplit));
+    double a = 0.0;
+    if (i < p.n) {
+#pragma unroll 4
+        for (int s = lane; s < ns; s += kCombLanes) a += static_cast<const double*>(p.part)[((long long)s * p.batch + m) * p.n + i];
+    }
+    red[lane][t] = a;
+    __syncthreads();
+    if (lane > 0 || i >= p.n) return;
+    double w = static_cast<const double*>(p.rhs)[o];
+#pragma unroll
+    for (int l = 0; l < kCombLanes; ++l) w -= red[l][t];
     static_cast<double*>(p.w)[o] = w;
 }
 
@@ -848,16 +964,16 @@ template <> hipError_t launch_full_t<Real>(const FullParams& p, int what, hipStr
             break;
         }
         case FULL_DOUBLE:
-            hipLaunchKernelGGL((k_full_pairs<Real, 0>), dim3(tiles, p.nsplit, p.batch), dim3(kFullThreads), 0, s, p);
+            hipLaunchKernelGGL((k_full_pairs<Real, 0>), dim3(tiles, p.nsplit, p.batch), dim3(kPairThreads), 0, s, p);
             break;
         case FULL_RHS:
             hipLaunchKernelGGL(k_full_rhs<Real>, dim3(tiles, 1, p.batch), dim3(kFullThreads), 0, s, p);
             break;
         case FULL_SINGLE:
-            hipLaunchKernelGGL((k_full_pairs<Real, 1>), dim3(tiles, p.nsplit, p.batch), dim3(kFullThreads), 0, s, p);
+            hipLaunchKernelGGL((k_full_pairs<Real, 1>), dim3(tiles, p.nsplit, p.batch), dim3(kPairThreads), 0, s, p);
             break;
         case FULL_COMBINE:
-            hipLaunchKernelGGL(k_full_combine<Real>, dim3(tiles, 1, p.batch), dim3(kFullThreads), 0, s, p);
+            hipLaunchKernelGGL(k_full_combine<Real>, dim3((n + 63) / 64, 1, p.batch), dim3(64 * kCombLanes), 0, s, p);
             break;
         case FULL_APPLY: {
             hipLaunchKernelGGL(k_full_apply<Real>, dim3((n + kApOuts - 1) / kApOuts, apply_slices(n), p.batch),
@@ -874,21 +990,21 @@ template <> hipError_t launch_full_t<Real>(const FullParams& p, int what, hipStr
             hipLaunchKernelGGL(k_full_bedgeom<Real>, dim3(outs, 1, p.batch), dim3(kFullThreads), 0, s, p);
             break;
         case FULL_RHSB:
-            hipLaunchKernelGGL((k_full_bpairs<Real, 2>), dim3(tiles, p.nsplit, p.batch), dim3(kFullThreads), 0, s, p);
+            hipLaunchKernelGGL((k_full_bpairs<Real, 2>), dim3(tiles, p.nsplit, p.batch), dim3(kPairThreads), 0, s, p);
             break;
         case FULL_RB:
             hipLaunchKernelGGL(k_full_rb<Real>, dim3(tiles, 1, p.batch), dim3(kFullThreads), 0, s, p);
             break;
         case FULL_BED:
-            hipLaunchKernelGGL((k_full_bpairs<Real, 3>), dim3(tiles, p.nsplit, p.batch), dim3(kFullThreads), 0, s, p);
+            hipLaunchKernelGGL((k_full_bpairs<Real, 3>), dim3(tiles, p.nsplit, p.batch), dim3(kPairThreads), 0, s, p);
             break;
         case FULL_SYM:
             if (n % kSymT != 0) return hipErrorInvalidValue;
             hipLaunchKernelGGL(k_full_sympairs<Real>, dim3((n / kSymT) * (n / kSymT + 1) / 2, 1, p.batch),
-                               dim3(kSymThreads), 0, s, p);
+                               dim3(64 * kSymWaves), 0, s, p);
             break;
         case FULL_SURF:
-            hipLaunchKernelGGL(k_full_spairs<Real>, dim3(tiles, p.nsplit, p.batch), dim3(kFullThreads), 0, s, p);
+            hipLaunchKernelGGL(k_full_spairs<Real>, dim3(tiles, p.nsplit, p.batch), dim3(kPairThreads), 0, s, p);
             break;
         case FULL_PB:
             hipLaunchKernelGGL(k_full_pb<Real>, dim3(tiles, 1, p.batch), dim3(kFullThreads), 0, s, p);

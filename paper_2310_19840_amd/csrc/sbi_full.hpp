@@ -33,7 +33,8 @@ struct FullParams {
     void* s2;
     void* s2a;            // [n] sin(2 pi j / n) of each index distance
     void* rs2;            // [n] 1 / sin^2(pi j / n) (0 at j = 0)
-    void* lfl;            // [batch][n] the flat image's single-layer term per member
+    void* lfl;            // [batch][n] 1/2 ln(sin^2 + sinh^2) of each member's flat geometry (image or bed)
+    void* rfl;            //   and 1 / (sin^2 + sinh^2)
     void* w;              // FP64 [batch][n]: rhs - (S - S0)[V_n]
     const void* vin;      // V_n (null: V_0 = 0)
     void* vout;           // V_(n+1)
@@ -56,7 +57,7 @@ enum {
     FULL_TABLES = 0, FULL_GEOM, FULL_DOUBLE, FULL_RHS, FULL_SINGLE, FULL_COMBINE, FULL_APPLY, FULL_SELECT,
     FULL_BEDGEOM, FULL_RHSB, FULL_RB, FULL_BED, FULL_PB, FULL_SURF, FULL_SYM
 };
-constexpr int kFullSymTile = 128;  // tile edge of FULL_SYM (n / kFullSymTile slices)
+constexpr int kFullSymTile = 64;  // tile edge of FULL_SYM (n / kFullSymTile slices)
 
 template <typename R> hipError_t launch_full_t(const FullParams&, int what, hipStream_t);
 hipError_t launch_full(int fp64, const FullParams& p, int what, hipStream_t s);
