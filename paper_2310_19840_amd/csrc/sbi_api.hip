@@ -243,9 +243,15 @@ static sbi_grid inner_grid(const sbi_grid* g) {
 }
 
 constexpr int kFullSplitMax = 16;  // source-point slices of a pair pass of the fully nonlinear solve
+// blocks a side of the symmetric single-layer pass: of one tile, or of two where
+// the points of all members fill the chip with a quarter of the workgroups too and
+// their slices would take 16 MiB and more (the allocation-free call has 64 in all)
+static int full_sym_blocks(int nx, int batch) {
+    return nx / kFullSymTile / ((long long)nx * batch <= 16384 ? 1 : 2);
+}
 // slices the pair passes of a fully nonlinear solve may write: the split passes'
-// and the symmetric single-layer pass's (one per tile block)
-static int full_slices(int nx) { return std::max(kFullSplitMax, nx / kFullSymTile); }
+// and the symmetric single-layer pass's (one per block)
+static int full_slices(int nx, int batch) { return std::max(kFullSplitMax, full_sym_blocks(nx, batch)); }
 
 static bool grid_valid(const sbi_grid* g) {
     if (!g) return false;
@@ -304,11 +310,11 @@ static Layout layout(const sbi_grid* g, int batch) {
                        : 0);
     // fully nonlinear solve (FP64 in both precisions): tables [batch + 5][nx]
     // and [batch][nx], right-hand side and source term [batch][nx], pair
-    // slices [full_slices(nx)][batch][nx]; for beds kept as a boundary, the bed
+    // slices [full_slices(nx, batch)][batch][nx]; for beds kept as a boundary, the bed
     // geometry (3 tables), its circulant, its right-hand side and two phi_b
     // iterates [batch][nx], and the per-member flags
     L.bytes_full = g->mode == SBI_MODE_FULL
-                       ? 17 * al((size_t)g->nx * 8 * batch) + al((size_t)full_slices(g->nx) * g->nx * 8 * batch) +
+                       ? 17 * al((size_t)g->nx * 8 * batch) + al((size_t)full_slices(g->nx, batch) * g->nx * 8 * batch) +
                              al(sizeof(int) * batch)
                        : 0;
     // mixed precision: the FP32 context's workspace at the end
@@ -557,7 +563,7 @@ static sbi_status ctx_setup(sbi_ctx* c, const sbi_grid* g, int32_t batch, const 
         c->full_rs2 = p + 15 * tb;
         c->full_rfl = p + 16 * tb;
         c->full_part = p + 17 * tb;
-        c->full_bed = reinterpret_cast<int*>(p + 17 * tb + al((size_t)full_slices(g->nx) * g->nx * 8 * batch));
+        c->full_bed = reinterpret_cast<int*>(p + 17 * tb + al((size_t)full_slices(g->nx, batch) * g->nx * 8 * batch));
     }
     gd.col_C = L.C;
     gd.href = c->href_dev;
@@ -1691,7 +1697,7 @@ static sbi_status full_solve(sbi_ctx* c, const void* eta_phys, double tol) {
     // the image form's single layer by its symmetric pass (each pair once) where
     // the grid holds two tiles or more
     const bool sym = p.n >= 2 * kFullSymTile;
-    p.nsym = sym ? p.n / kFullSymTile : 0;
+    p.nsym = sym ? full_sym_blocks(p.n, c->batch) : 0;
     if (bed) {
         // the bed's right-hand side -D_BS[phi_s] of the two-boundary members
         c->st.launches += 2;

@@ -387,39 +387,42 @@ __global__ void __launch_bounds__(kPairThreads) k_full_pairs(const FullParams p)
 // --- the single layer (S - S0)[V_n] of the image-form members from the
 // symmetry of its kernel: K(i, j) = K(j, i) (both the direct part and the
 // image depend on |eta_j - eta_i|, eta_i + eta_j and sin^2(pi (x_j - x_i)/L)).
-// The n x n pairs split into tiles of kSymT x kSymT points; a workgroup takes
-// tile (I, J), I <= J, evaluates each of its pairs once and adds K V_j to the
-// row sums of its points i in block I and K V_i to the column sums of its
-// points j in block J.  Row sums go to slice J of the points of block I, column
-// sums to slice I of those of block J, so every point receives n / kSymT slices,
-// one from each block, each written once; a diagonal tile (I = J) evaluates all
-// its pairs and writes rows only.
+// The n x n pairs split into blocks of Q kSymT x Q kSymT points; a workgroup
+// takes block (I, J), I <= J, tile by tile of kSymT x kSymT, evaluates each of
+// its pairs once and adds K V_j to the row sums of its points i in block I and
+// K V_i to the column sums of its points j in block J.  Row sums go to slice J
+// of the points of block I, column sums to slice I of those of block J, so every
+// point receives n / (Q kSymT) slices, one from each block, each written once; a
+// diagonal tile evaluates all its pairs and adds to the rows only, and the tiles
+// below the diagonal of a diagonal block are left out.
 //
 // Bound by the issue of FP64 operations (about 50 a pair).  A tile's 64 columns
 // are the lanes of a wavefront and its four wavefronts take a quarter of the
 // tile's diagonals each: at 4096 points 2080 workgroups, eight to nine per CU
-// (tiles of 128 leave two or three, a third of the chip idle at the end).  FP64,
-// 4096 points: 39 us per pass, against 109 with tiles of 128 and two library
-// logarithms a pair.
+// (blocks of two tiles a side leave two or three, a third of the chip idle at the
+// end: those are for where the slices of many members would fill memory instead).
+// FP64, 4096 points: 39 us per pass, against 109 with tiles of 128 and two
+// library logarithms a pair.
 constexpr int kSymT = kFullSymTile;
 constexpr int kSymWaves = 4;
 static_assert(kSymT == 64, "a tile's columns are the lanes of one wavefront");
 
-template <typename R>
+template <typename R, int Q>
 __global__ void __launch_bounds__(64 * kSymWaves) k_full_sympairs(const FullParams p) {
     __shared__ R tej[kSymT], tvj[kSymT], tsj[kSymT], tcj[kSymT];
     __shared__ double colp[kSymWaves][kSymT], rowp[kSymWaves][kSymT];
+    __shared__ double rsum[Q][kSymT], csum[Q][kSymT];
     const int t = threadIdx.x;
     const int m = blockIdx.z;
     const int n = p.n;
-    const int nb = n / kSymT;
+    const int nb = n / (Q * kSymT);
     {
         Ctl* ctl = p.ctl + m;
         const bool leader = blockIdx.x == 0 && t == 0;
         if (full_decided(p, ctl, leader)) return;  // workgroup-uniform
     }
     if (full_bed(p, m)) return;
-    // tile (I, J), I <= J, of this workgroup's linear index (row-major upper triangle)
+    // block (I, J), I <= J, of this workgroup's linear index (row-major upper triangle)
     int L = blockIdx.x, I = 0;
     while (L >= nb - I) {
         L -= nb - I;
@@ -438,69 +441,83 @@ __global__ void __launch_bounds__(64 * kSymWaves) k_full_sympairs(const FullPara
     const R b2h = R(2.0 * M_PI * p.href[m] / p.lx);
     const R sh0 = img ? sinh(b2h) : R(0);
     const int wv = t / 64, ln = t & 63;
-    const int i = I * kSymT + ln;
-    const R etai = eta[i], exi = ex[i];
-    const double vi = (double)v[i];
-    R sbi = R(0), cbi = R(1);
-    if (img) {
-        const R b = pl * etai + b2h;
-        sbi = sinh(b);
-        cbi = cosh(b);
-    }
     if (t < kSymT) {
-        const R ej = eta[J * kSymT + t];
-        tej[t] = ej;
-        tvj[t] = v[J * kSymT + t];
-        if (img) {
-            tsj[t] = sinh(pl * ej);
-            tcj[t] = cosh(pl * ej);
-        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) rsum[q][t] = csum[q][t] = 0.0;
     }
-    __syncthreads();
-    const int from = (ln + 1) & 63;
-    constexpr int kSteps = kSymT / kSymWaves;
-    double acc = 0.0, cacc = 0.0;
+#pragma unroll 1
+    for (int q = 0; q < Q * Q; ++q) {
+        const int qa = q / Q, qb = q % Q;
+        const bool own = diag && qa == qb;
+        if (diag && qa > qb) continue;
+        if (Q > 1) __syncthreads();  // the tile before is done with the shared columns
+        const int i = (I * Q + qa) * kSymT + ln;
+        const R etai = eta[i], exi = ex[i];
+        const double vi = (double)v[i];
+        R sbi = R(0), cbi = R(1);
+        if (img) {
+            const R b = pl * etai + b2h;
+            sbi = sinh(b);
+            cbi = cosh(b);
+        }
+        if (t < kSymT) {
+            const R ej = eta[(J * Q + qb) * kSymT + t];
+            tej[t] = ej;
+            tvj[t] = v[(J * Q + qb) * kSymT + t];
+            if (img) {
+                tsj[t] = sinh(pl * ej);
+                tcj[t] = cosh(pl * ej);
+            }
+        }
+        __syncthreads();
+        const int from = (ln + 1) & 63;
+        constexpr int kSteps = kSymT / kSymWaves;
+        double acc = 0.0, cacc = 0.0;
 #pragma unroll 2
-    for (int s = 0; s < kSteps; ++s) {
-        // lane ln takes the columns ln + kSteps wv, + 1, ... (mod 64): at each
-        // step the lanes of a wavefront hold 64 different columns, and the
-        // running column sum moves one lane down with its column
-        const int jl = (ln + wv * kSteps + s) & 63;
-        const int j = J * kSymT + jl;
-        const int d = (j - i + n) & (n - 1);
-        const R shb = sinh_series(pl * (tej[jl] - etai));
-        R x = j == i ? exi * exi : shb * shb * R(rs2[d]);
-        if (img) {
-            const R shp = tsj[jl] * cbi + tcj[jl] * sbi;
-            const R y = (shp - sh0) * (shp + sh0) * R(rfl[d]);
-            x = x + y + x * y;
+        for (int s = 0; s < kSteps; ++s) {
+            // lane ln takes the columns ln + kSteps wv, + 1, ... (mod 64): at each
+            // step the lanes of a wavefront hold 64 different columns, and the
+            // running column sum moves one lane down with its column
+            const int jl = (ln + wv * kSteps + s) & 63;
+            const int j = (J * Q + qb) * kSymT + jl;
+            const int d = (j - i + n) & (n - 1);
+            const R shb = sinh_series(pl * (tej[jl] - etai));
+            R x = j == i ? exi * exi : shb * shb * R(rs2[d]);
+            if (img) {
+                const R shp = tsj[jl] * cbi + tcj[jl] * sbi;
+                const R y = (shp - sh0) * (shp + sh0) * R(rfl[d]);
+                x = x + y + x * y;
+            }
+            const double kv = (double)(R(-0.5) * pair_log1p(x));
+            acc += kv * (double)tvj[jl];
+            if (!own) {
+                // the pair seen from j: K V_i added to column jl's sum over this
+                // wavefront's rows, which lane ln - 1 continues at the next step
+                cacc += kv * vi;
+                cacc = __shfl(cacc, from, 64);
+            }
         }
-        const double kv = (double)(R(-0.5) * pair_log1p(x));
-        acc += kv * (double)tvj[jl];
-        if (!diag) {
-            // the pair seen from j: K V_i added to column jl's sum over this
-            // wavefront's rows, which lane ln - 1 continues at the next step
-            cacc += kv * vi;
-            cacc = __shfl(cacc, from, 64);
+        rowp[wv][ln] = acc;
+        if (!own) colp[wv][(ln + (wv + 1) * kSteps) & 63] = cacc;
+        __syncthreads();
+        if (t < kSymT) {  // thread t adds to its own points' sums only
+#pragma unroll
+            for (int w = 0; w < kSymWaves; ++w) rsum[qa][t] += rowp[w][t];
+            if (!own) {
+                double* c = diag ? rsum[qb] : csum[qb];
+#pragma unroll
+                for (int w = 0; w < kSymWaves; ++w) c[t] += colp[w][t];
+            }
         }
     }
-    rowp[wv][ln] = acc;
-    if (!diag) colp[wv][(ln + (wv + 1) * kSteps) & 63] = cacc;
-    __syncthreads();
     if (t < kSymT) {
         const double dx = p.lx / n;
         double* part = static_cast<double*>(p.part);
-        double a = 0.0;
 #pragma unroll
-        for (int w = 0; w < kSymWaves; ++w) a += rowp[w][t];
-        // rows of block I: slice J
-        part[((long long)J * p.batch + m) * n + I * kSymT + t] = a * dx;
-        if (!diag) {
-            // columns of block J: slice I
-            double c = 0.0;
-#pragma unroll
-            for (int w = 0; w < kSymWaves; ++w) c += colp[w][t];
-            part[((long long)I * p.batch + m) * n + J * kSymT + t] = c * dx;
+        for (int q = 0; q < Q; ++q) {
+            // rows of block I: slice J; columns of block J: slice I
+            part[((long long)J * p.batch + m) * n + (I * Q + q) * kSymT + t] = rsum[q][t] * dx;
+            if (!diag) part[((long long)I * p.batch + m) * n + (J * Q + q) * kSymT + t] = csum[q][t] * dx;
         }
     }
 }
@@ -999,10 +1016,16 @@ template <> hipError_t launch_full_t<Real>(const FullParams& p, int what, hipStr
             hipLaunchKernelGGL((k_full_bpairs<Real, 3>), dim3(tiles, p.nsplit, p.batch), dim3(kPairThreads), 0, s, p);
             break;
         case FULL_SYM:
-            if (n % kSymT != 0) return hipErrorInvalidValue;
-            hipLaunchKernelGGL(k_full_sympairs<Real>, dim3((n / kSymT) * (n / kSymT + 1) / 2, 1, p.batch),
-                               dim3(64 * kSymWaves), 0, s, p);
+        {
+            const int nb = p.nsym;
+            if (n == nb * kSymT)
+                hipLaunchKernelGGL((k_full_sympairs<Real, 1>), dim3(nb * (nb + 1) / 2, 1, p.batch), dim3(64 * kSymWaves), 0, s, p);
+            else if (n == nb * 2 * kSymT)
+                hipLaunchKernelGGL((k_full_sympairs<Real, 2>), dim3(nb * (nb + 1) / 2, 1, p.batch), dim3(64 * kSymWaves), 0, s, p);
+            else
+                return hipErrorInvalidValue;
             break;
+        }
         case FULL_SURF:
             hipLaunchKernelGGL(k_full_spairs<Real>, dim3(tiles, p.nsplit, p.batch), dim3(kPairThreads), 0, s, p);
             break;

@@ -57,7 +57,7 @@ enum {
     FULL_TABLES = 0, FULL_GEOM, FULL_DOUBLE, FULL_RHS, FULL_SINGLE, FULL_COMBINE, FULL_APPLY, FULL_SELECT,
     FULL_BEDGEOM, FULL_RHSB, FULL_RB, FULL_BED, FULL_PB, FULL_SURF, FULL_SYM
 };
-constexpr int kFullSymTile = 64;  // tile edge of FULL_SYM (n / kFullSymTile slices)
+constexpr int kFullSymTile = 64;  // tile edge of FULL_SYM (n / kFullSymTile slices, or half as many)
 
 template <typename R> hipError_t launch_full_t(const FullParams&, int what, hipStream_t);
 hipError_t launch_full(int fp64, const FullParams& p, int what, hipStream_t s);
