@@ -29,6 +29,7 @@
 #include "../../include/sbi_net.h"
 #include "sbi_full.hpp"
 #include "sbi_kernels.hpp"
+#include "sbi_line.hpp"
 #include "sbi_net.hpp"
 
 using namespace sbi;
@@ -74,8 +75,12 @@ enum {
 enum {
     P_ETA, P_DELTA,
     P_WORK0,              // work fields of the learned seed and of the fully nonlinear solve
-    P_COUNT = P_WORK0 + 6
+    P_LINE0 = P_WORK0 + 6,   // 1D grids: fields of the orders in the one-kernel solve
+    P_COUNT = P_LINE0 + 10   // (P_WORK0 .. P_COUNT: its 16 fields)
 };
+
+// physical buffers a grid needs
+static int phys_count(int nx, int ny) { return ny == 1 && line_threads(nx) > 0 ? P_COUNT : P_LINE0; }
 
 struct Stats {
     double launches = 0, syncs = 0, sweeps = 0;
@@ -298,7 +303,7 @@ static Layout layout(const sbi_grid* g, int batch) {
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     L.bytes_comp = al((size_t)L.s_cmp * L.csz * batch) * C_COUNT;
     L.bytes_half = al((size_t)L.s_half * L.csz * batch) * H_COUNT;
-    L.bytes_phys = al((size_t)L.s_phys * L.rsz * batch) * P_COUNT;
+    L.bytes_phys = al((size_t)L.s_phys * L.rsz * batch) * phys_count(g->nx, g->ny);
     L.bytes_tw = al((size_t)g->nx * L.csz) + al((size_t)(g->nx / 2) * L.csz) + al((size_t)g->ny * L.csz);
     L.bytes_misc = al(sizeof(double) * batch) + al(sizeof(Ctl) * batch) + al(sizeof(CtlSlots) * batch) +
                    al(sizeof(double) * 2 * 64 * batch) + al(sizeof(double) * kAASlots * (size_t)(L.Kxp / L.C) * batch);
@@ -511,7 +516,7 @@ static sbi_status ctx_setup(sbi_ctx* c, const sbi_grid* g, int32_t batch, const 
         c->half[i] = p;
         p += al((size_t)L.s_half * L.csz * batch);
     }
-    for (int i = 0; i < P_COUNT; ++i) {
+    for (int i = 0; i < phys_count(g->nx, g->ny); ++i) {
         c->phys[i] = p;
         p += al((size_t)L.s_phys * L.rsz * batch);
     }
@@ -1828,6 +1833,90 @@ static sbi_status solve_stage(sbi_ctx* c, const void* eta_user, double tol, bool
     return SBI_OK;
 }
 
+// ---------------------------------------------------------------------------
+// one-dimensional grids: solves and steps in one kernel
+// ---------------------------------------------------------------------------
+// The kernel takes rows of up to 1024 points (line_threads), bands below half the
+// transform (dealias <= 1/2) and solves from the linear guess; a profiled context
+// keeps the separate passes, which its kernel classes name.  Both sides measured,
+// us a call, the kernel against the separate passes:
+//     256 points FP64, one W solve iterated to 1e-9     237     613
+//    1024 points FP64, the same                         371     598
+//    1024 points FP64, four SA steps                   1160    1891
+//     256 points FP64, four SA steps of 1024 members   2707    3975
+//      16 points FP32, four SA steps                    663    1628
+// At 2048 and 4096 points a transform spans wavefronts and the registers spill:
+// four tank steps of 4096 points took 4958 against 2486.
+static bool line_ok(const sbi_ctx* c) {
+    const GridDev& g = c->gd;
+    const int T = g.ny == 1 ? line_threads(g.nx) : 0;
+    return T > 0 && (c->grid.mode == SBI_MODE_SA || c->grid.mode == SBI_MODE_ITER) &&
+           c->grid.seed == SBI_SEED_LINEAR && !c->inner && !c->prof.on && (g.Kx + 63) / 64 * 64 <= T &&
+           2 * g.Mx < g.nx / 2;
+}
+
+static LineParams line_params(sbi_ctx* c, double tol) {
+    LineParams p{};
+    p.g = c->gd;
+    p.sa = c->grid.mode == SBI_MODE_SA;
+    p.vd = c->vd;
+    p.aa = c->grid.accel == SBI_ACCEL_ANDERSON;
+    p.max_sweeps = c->grid.max_sweeps;
+    p.tol = tol;
+    RkParams& rp = p.rk;
+    rp.g = c->gd;
+    rp.eh = CMP(C_EH);
+    rp.ph = CMP(C_PH);
+    rp.es = CMP(C_ES);
+    rp.ps = CMP(C_PS);
+    rp.ae = CMP(C_AE);
+    rp.ap = CMP(C_AP);
+    p.vh = CMP(p.sa ? C_VH : C_VP);
+    p.np = CMP(C_NP);
+    p.pd = CMP(C_PD);
+    rp.Vh = p.vh;
+    rp.Nph = p.np;
+    rp.Pdiv = c->dmp_w > 0.0 ? p.pd : nullptr;
+    rp.fb1 = c->grid.filter_beta1;
+    rp.fb2 = c->grid.filter_beta2;
+    p.vn = CMP(C_VN);
+    p.bn = CMP(C_BN);
+    p.bv = CMP(C_BV);
+    p.bb = CMP(C_BB);
+    for (int i = 0; i < kAASlots; ++i) {
+        p.ring[0][i] = CMP(C_AFV0 + i);
+        p.ring[1][i] = CMP(C_AFB0 + i);
+        p.ring[2][i] = CMP(C_AGV0 + i);
+        p.ring[3][i] = CMP(C_AGB0 + i);
+    }
+    p.gv = HALF(H_GV);
+    p.gd = HALF(H_GD);
+    p.gt = HALF(H_GT);
+    p.f[LF_ETA] = PHYS(P_ETA);
+    p.f[LF_DELTA] = PHYS(P_DELTA);
+    for (int i = 0; i < 16; ++i) p.f[LF_EX + i] = PHYS(P_WORK0 + i);  // P_WORK0 .., then P_LINE0 ..
+    p.ctl = c->ctl;
+    p.wm_n = c->wm_n;
+    std::memcpy(p.wm, c->wm, sizeof(p.wm));
+    p.wm_h = c->wm_h;
+    p.dmp_x0 = c->dmp_x0;
+    p.dmp_w = c->dmp_w;
+    p.rz_on = c->relax_on;
+    std::memcpy(p.rz, c->rz, sizeof(p.rz));
+    return p;
+}
+
+// steps per launch: a launch stays under a tenth of a second at the default limit of sweeps
+static int line_steps(const sbi_ctx* c) { return c->grid.mode == SBI_MODE_SA ? 64 : 8; }
+
+// n steps of the spectral state (steps of the ensembles: keep going after a
+// failed solve, as their separate passes do)
+static sbi_status line_enqueue(sbi_ctx* c, LineParams& p, int steps) {
+    p.steps = steps;
+    c->st.launches += 1;
+    return hip_ok(launch_line(c->fp64, p, c->batch, tw_of(c), c->stream));
+}
+
 static sbi_status solve_status(sbi_ctx* c, sbi_solve_info* info, bool fresh) {
     if (!fresh) SBI_TRY(read_heads(c));
     sbi_status worst = SBI_OK;
@@ -1936,10 +2025,19 @@ static sbi_status vertical_velocity(sbi_ctx* c, const void* eta, const void* phi
     const bool net = c->grid.seed == SBI_SEED_NET && c->grid.mode == SBI_MODE_ITER && !c->have_prev &&
                      c->net_loaded;
     c->fallbacks = 0;
-    SBI_TRY(to_spectral(c, net ? eta : nullptr, phi_s, false));
-    int vh = 0;
-    SBI_TRY(solve_stage(c, eta, tol, false, &vh,
-                        (c->grid.seed == SBI_SEED_USER && c->grid.mode == SBI_MODE_ITER) ? w_seed : nullptr));
+    if (line_ok(c)) {
+        LineParams lp = line_params(c, tol);
+        lp.load = 1;
+        lp.eta_in = eta;
+        lp.f[LF_ETA] = const_cast<void*>(eta);
+        lp.phi_in = phi_s;
+        SBI_TRY(line_enqueue(c, lp, 0));
+    } else {
+        SBI_TRY(to_spectral(c, net ? eta : nullptr, phi_s, false));
+        int vh = 0;
+        SBI_TRY(solve_stage(c, eta, tol, false, &vh,
+                            (c->grid.seed == SBI_SEED_USER && c->grid.mode == SBI_MODE_ITER) ? w_seed : nullptr));
+    }
     sbi_status st = solve_status(c, info, false);
     if (st < 0) return st;
     // W = T_V(V_n) of the deciding sweep: in half form for the mixed iteration,
@@ -2117,26 +2215,58 @@ extern "C" sbi_status sbi_step(sbi_ctx* c, sbi_state* state, double dt, int32_t 
     c->st = Stats();
     c->fallbacks = 0;
     sbi_step_info si{};
-    SBI_TRY(to_spectral(c, state->eta, state->phi_s, true));
     sbi_status worst = SBI_OK;
     double t = state->t;
-    for (int s = 0; s < n; ++s) {
-        for (int stage = 0; stage < 4; ++stage) {
-            int vh = 0;
-            SBI_TRY(solve_stage(c, nullptr, tol, true, &vh, nullptr, false, stage));
-            if (c->grid.mode != SBI_MODE_SA) {
-                // the iteration already read the control headers at its last poll
-                sbi_status st = solve_status(c, nullptr, true);
-                if (st < 0) return st;
-                if (st > worst) worst = st;
-                acc_info(c, &si);
-            } else {
-                si.solves += c->batch;
-            }
-            SBI_TRY(stage_update(c, stage, dt, vh, t));
+    if (n > 0 && line_ok(c)) {
+        LineParams lp = line_params(c, tol);
+        lp.rk.h = dt;
+        lp.load = lp.acc_reset = 1;
+        lp.eta_in = state->eta;
+        lp.phi_in = state->phi_s;
+        for (int s = 0; s < n; s += line_steps(c)) {
+            const int k = std::min(line_steps(c), n - s);
+            lp.t0 = t;
+            SBI_TRY(line_enqueue(c, lp, k));
+            lp.load = lp.acc_reset = 0;
+            for (int i = 0; i < k; ++i) t += dt;
+            if (c->grid.mode == SBI_MODE_SA) continue;
+            SBI_TRY(read_heads(c));
+            const sbi_status st = solve_status(c, nullptr, true);
+            if (st < 0) return st;
         }
-        t += dt;
-        if (c->relax_on) SBI_TRY(relax_zone(c, t));
+        if (c->grid.mode == SBI_MODE_SA) {
+            si.solves = 4ll * n * c->batch;
+        } else {
+            for (int b = 0; b < c->batch; ++b) {
+                const Ctl& h = c->head[b];
+                si.solves += h.acc_solves;
+                si.sweeps_total += h.acc_sweeps;
+                si.sweeps_max = std::max(si.sweeps_max, h.acc_sweeps_max);
+                si.max_residual = std::max(si.max_residual, h.acc_residual_max);
+                worst = std::max(worst, (sbi_status)h.acc_worst);
+            }
+            c->st.sweeps = (double)si.sweeps_total;
+        }
+    } else {
+        SBI_TRY(to_spectral(c, state->eta, state->phi_s, true));
+        for (int s = 0; s < n; ++s) {
+            for (int stage = 0; stage < 4; ++stage) {
+                int vh = 0;
+                SBI_TRY(solve_stage(c, nullptr, tol, true, &vh, nullptr, false, stage));
+                if (c->grid.mode != SBI_MODE_SA) {
+                    // the iteration already read the control headers at its last poll
+                    sbi_status st = solve_status(c, nullptr, true);
+                    if (st < 0) return st;
+                    if (st > worst) worst = st;
+                    acc_info(c, &si);
+                } else {
+                    si.solves += c->batch;
+                }
+                SBI_TRY(stage_update(c, stage, dt, vh, t));
+            }
+            t += dt;
+            if (c->relax_on) SBI_TRY(relax_zone(c, t));
+        }
     }
     if (c->grid.mode == SBI_MODE_SA) {
         // SA mode has no residual; non-finite values surface through the last setup
@@ -3079,7 +3209,14 @@ static sbi_status batch_enqueue_part(sbi_batch* b, sbi_state* states, int part, 
             SBI_TRY(to_spectral(c, gr.st_eta, gr.st_phi, true));
         } else if (part == PART_STEPS) {
             double t = states[gr.members[0]].t + toff;
-            for (int step = 0; step < n; ++step) {
+            if (line_ok(c)) {
+                LineParams lp = line_params(c, tol);
+                lp.rk.h = dt;
+                lp.t0 = t;
+                lp.keep = 1;
+                SBI_TRY(line_enqueue(c, lp, n));
+            }
+            for (int step = 0; step < n && !line_ok(c); ++step) {
                 for (int stage = 0; stage < 4; ++stage) {
                     int vh = 0;
                     SBI_TRY(solve_stage(c, nullptr, tol, true, &vh, nullptr, true, stage));
