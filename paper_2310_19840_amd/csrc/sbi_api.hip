@@ -1106,13 +1106,14 @@ static void sweep_col_terms(sbi_ctx* c, ColBuilder& b, bool products) {
     const int J = c->grid.order - 1;
     std::vector<int> se(J + 1), sbx(J + 1), sby(J + 1);
     if (products) {
-        int idx = 0;
-        for (int j = 1; j <= J; ++j) se[j] = b.prod(HALF(H_PROD0 + idx++));
-        if (c->vd) {
-            for (int j = 1; j <= J; ++j) sbx[j] = b.prod(HALF(H_PROD0 + idx++));
-            if (two_d)
-                for (int j = 1; j <= J; ++j) sby[j] = b.prod(HALF(H_PROD0 + idx++));
+        for (int j = 1; j <= J; ++j) {
+            se[j] = b.prod(HALF(H_PROD0 + j - 1));
+            if (c->vd) {
+                sbx[j] = b.prod(HALF(H_PROD0 + J + j - 1));
+                if (two_d) sby[j] = b.prod(HALF(H_PROD0 + 2 * J + j - 1));
+            }
         }
+        b.p.nfam = 1 + (c->vd ? (two_d ? 2 : 1) : 0);
     }
     b.term(b.cin(CMP(C_BV)), 0, 1.0, FN_ONE, 0, DV_NONE);
     if (c->vd) b.term(b.cin(CMP(C_BB)), 1, 1.0, FN_ONE, 0, DV_NONE);

@@ -138,6 +138,10 @@ struct ColParams {
     GridDev g;
     int nacc, nsub;
     int hyper;                         // some term uses tanh(kh) or sech(kh)
+    // > 0: the products are those of a sweep of the iteration, order by order: eta^j V, then with
+    // nfam 2 or 3 delta^j d_x phi_b, delta^j d_y phi_b; j = 1, 2, ..  Their terms, which the
+    // sources give as well, follow from j and the family alone.
+    int nfam;
     ColSub sub[kMaxSub];
     ColSrc src[kMaxProd + kMaxCin];    // products (half forms), then from kMaxProd on compact inputs
     // Anderson weights formed in the pass itself: when aa_partial is set, each

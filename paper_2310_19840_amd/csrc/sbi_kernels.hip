@@ -738,7 +738,7 @@ __device__ __forceinline__ bool col_control(const ColParams& p, Ctl* ctl, bool l
 
 // geometry of one kept mode
 template <typename R> struct ColGeo {
-    R k, T, S, kx, ky;
+    R k, ik, T, S, kx, ky;   // ik: 1 / k, 0 at k = 0
 };
 // (mx, r): column and compact row; T = tanh(kh) and S = sech(kh) only when
 // the pass uses them
@@ -751,6 +751,7 @@ __device__ __forceinline__ ColGeo<R> col_geo(const ColParams& p, int mx, int r, 
     const double k = sqrt(kx * kx + ky * ky);
     ColGeo<R> o;
     o.k = R(k);
+    o.ik = k > 0.0 ? R(1) / R(k) : R(0);
     o.T = o.S = R(1);
     if (p.hyper) {
         o.T = R(tanh(k * href));
@@ -801,14 +802,49 @@ __device__ __forceinline__ void col_add(const ColSrc& s, V val, V (&acc)[NACC], 
         if (s.fn[t] == FN_T) m *= q.T;
         else if (s.fn[t] == FN_S) m *= q.S;
         const int pw = s.pw[t];
-        if (pw >= 0) {
-            for (int e = 0; e < pw; ++e) m *= q.k;
+        if (pw < 0) {
+            m *= q.ik;
         } else {
-            m = q.k > R(0) ? m / q.k : R(0);
+            if (pw & 1) m *= q.k;
+            if (pw & 2) m *= q.k * q.k;
+            if (pw & 4) m *= (q.k * q.k) * (q.k * q.k);
         }
 #pragma unroll
         for (int a = 0; a < NACC; ++a)
             if (a == s.acc[t]) acc[a] = cx<V>(acc[a].x + val.x * m, acc[a].y + val.y * m);
+    }
+}
+
+// The products of a sweep (ColParams::nfam), value F of order j and family f, the
+// same in every thread:
+//     eta^j V:                  V -= <odd: T> k^j / j! F,          phi_b -= <odd> S k^(j-1) / j! F
+//     delta^j d_x,y phi_b:      D = i k_x,y F;  V += <odd> S k^(j-1) / j! D,
+//                               phi_b -= <odd: T, even: -1> k^(j-2) / j! D
+// kq: k^(j-2), carried from order to order.  Read from the sources' descriptions,
+// a term is a chain of branches and LDS reads: the sums of a sweep (FP64, the
+// waits for the slowest transform included) took 8.0 us at 128 x 64 and 13.4 us at
+// 1024 x 1024; this way 4.9 and 10.4.
+static __constant__ double kSweepFact[7] = {1.0, 1.0, 1.0 / 2.0, 1.0 / 6.0, 1.0 / 24.0, 1.0 / 120.0, 1.0 / 720.0};
+template <typename R, typename V, int NACC>
+__device__ __forceinline__ void col_sweep_add(int j, int f, R fact, V F, V (&acc)[NACC], R& kq, const ColGeo<R>& g) {
+    const bool odd = j & 1;
+    if (f == 0) kq = j == 1 ? g.ik : (j == 2 ? R(1) : kq * g.k);
+    const R kp = (j == 1 ? R(1) : kq * g.k) * fact;  // k^(j-1) / j!
+    if (f == 0) {
+        const R m = kp * g.k * (odd ? g.T : R(1));
+        acc[0] = cx<V>(acc[0].x - F.x * m, acc[0].y - F.y * m);
+        if (NACC > 1 && odd) {
+            const R s = kp * g.S;
+            acc[NACC - 1] = cx<V>(acc[NACC - 1].x - F.x * s, acc[NACC - 1].y - F.y * s);
+        }
+    } else {
+        const V D = mul_i(cscale(F, f == 1 ? g.kx : g.ky));
+        if (odd) {
+            const R s = kp * g.S;
+            acc[0] = cx<V>(acc[0].x + D.x * s, acc[0].y + D.y * s);
+        }
+        const R m = kq * fact * (odd ? -g.T : R(1));
+        if (NACC > 1) acc[NACC - 1] = cx<V>(acc[NACC - 1].x + D.x * m, acc[NACC - 1].y + D.y * m);
     }
 }
 
@@ -827,57 +863,33 @@ __device__ __forceinline__ V col_source(int src, const V (&acc)[NACC], const V (
     return src >= SRC_DIFF0 ? d : cadd(pq, cscale(d, omega));
 }
 
-// the weights inside a column-pass workgroup: the partials of the member are
-// added in a fixed order (strided per thread, then across the wavefront, then
-// wavefront by wavefront), so every workgroup forms the same weights; s_red
-// holds kAASlots reals per wavefront (<= 16), s_w receives the weights
-static __device__ void aa_block_weights(const ColParams& p, Ctl* ctl, int mem, bool commit, double* s_red, double* s_w) {
-    double d[kAASlots];
-#pragma unroll
-    for (int i = 0; i < kAASlots; ++i) d[i] = 0.0;
-    const double* part = p.aa_partial + (long long)mem * p.aa_nblk * kAASlots;
-    for (int b = threadIdx.x; b < p.aa_nblk; b += blockDim.x)
-#pragma unroll
-        for (int i = 0; i < kAASlots; ++i) d[i] += part[b * kAASlots + i];
-#pragma unroll
-    for (int i = 0; i < kAASlots; ++i)
-        for (int off = 32; off > 0; off >>= 1) d[i] += __shfl_xor(d[i], off, 64);
-    const int wv = threadIdx.x / 64;
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-        for (int i = 0; i < kAASlots; ++i) s_red[wv * kAASlots + i] = d[i];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double tot[kAASlots], w[kAASlots];
-#pragma unroll
-        for (int i = 0; i < kAASlots; ++i) tot[i] = 0.0;
-        const int nw = (blockDim.x + 63) / 64;
-        for (int v = 0; v < nw; ++v)
-#pragma unroll
-            for (int i = 0; i < kAASlots; ++i) tot[i] += s_red[v * kAASlots + i];
-        aa_weights(ctl, p.aa_sweep, tot, w, commit);
-#pragma unroll
-        for (int i = 0; i < kAASlots; ++i) s_w[i] = w[i];
-    }
-    __syncthreads();
-}
-
 // inner products of the residual history for the Anderson mixing, formed by
 // the sweep's own owners: d[i] += wt <F_i, f_n> of one mode over the ring slots
-// of sweep n (f: f_n's V and phi_b parts; the older ones are read back)
+// of sweep n (f: f_n's V and phi_b parts, old: those of the two sweeps before)
 template <typename V>
-__device__ __forceinline__ void col_aa_dots(const ColParams& p, const V (&f)[2], long long o, double wt,
+__device__ __forceinline__ void col_aa_old(const ColParams& p, long long o, V (&old)[kAADepth][2]) {
+#pragma unroll
+    for (int j = 1; j <= kAADepth; ++j)
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+            old[j - 1][part] = cx<V>(0, 0);
+            if (j <= p.sweep && p.aa_f[part][0])
+                old[j - 1][part] = static_cast<const V*>(p.aa_f[part][(p.sweep - j) % kAASlots])[o];
+        }
+}
+template <typename V>
+__device__ __forceinline__ void col_aa_dots(const ColParams& p, const V (&f)[2], const V (&old)[kAADepth][2], double wt,
                                             double (&d)[kAASlots]) {
-    const int n = p.sweep, k = n < kAADepth ? n : kAADepth;
+    const int n = p.sweep;
 #pragma unroll
     for (int part = 0; part < 2; ++part) {
         if (part == 1 && !p.aa_f[1][0]) break;
         const V f0 = f[part];
 #pragma unroll
         for (int j = 0; j <= kAADepth; ++j) {
-            if (j > k) break;
+            if (j > n) break;
             const int si = (n - j) % kAASlots;
-            const V fj = j == 0 ? f0 : static_cast<const V*>(p.aa_f[part][si])[o];
+            const V fj = j == 0 ? f0 : old[j - 1][part];
             const double v = wt * ((double)fj.x * (double)f0.x + (double)fj.y * (double)f0.y);
 #pragma unroll
             for (int i = 0; i < kAASlots; ++i)
@@ -930,6 +942,16 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
         }
     };
     if (wv < njob) request(wv);
+    // compact inputs an owner of one mode loads ahead of their use, into the
+    // columns' registers: in a pass without products before everything else
+    constexpr bool EARLY = IT == 1 && AHEAD;
+    constexpr int kPre = !EARLY ? 0 : (S * E < 6 ? S * E : 6);
+    const int nc = sub.c1 - sub.c0;
+    auto preload = [&](long long o, bool on) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < kPre; ++s)
+            raw[s / E][s % E] = s < nc && on ? static_cast<const V*>(p.src[kMaxProd + sub.c0 + s].ptr)[o] : cx<V>(R(0), R(0));
+    };
     Twid<V, NH, E> twc;
     twc.load(twY, j, S);                                       // the NH-point twiddles: every S-th entry
     V wn = cx<V>(R(1), R(0)), wq = wn;                         // W^(h j), W^(h P)
@@ -953,6 +975,7 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
         geo[it] = col_geo<R>(p, x0 + c2, r, href);
     }
     const long long cb = mem * g.s_cmp + (long long)x0 * g.Ky;  // compact base of the workgroup
+    if (njob == 0) preload(cb + co[0], co[0] >= 0);
     double omega = 1.0;
     // the decision is the same in every thread (the leader's header updates
     // cannot change it), so the workgroup returns as a whole
@@ -964,12 +987,11 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
     for (int it = 0; it < IT; ++it)
 #pragma unroll
         for (int a = 0; a < NACC; ++a) acc[it][a] = cx<V>(R(0), R(0));
-    V pv[IT][2];
+    R kq[IT];              // power of k carried over a sweep's products
+    int sj = 1, sf = 0;    // their order and family
+    const int nfam = p.nfam;
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-            pv[it][a] = (p.prev[a] && co[it] >= 0) ? static_cast<const V*>(p.prev[a])[cb + co[it]] : cx<V>(R(0), R(0));
+    for (int it = 0; it < IT; ++it) kq[it] = R(0);
 
     V* const area = areas + wv * AREA;
     lds_sync();  // the staged parameters: every wavefront's part of them is written
@@ -1023,6 +1045,27 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
         if (jb + W < njob) request(jb + W);
         lds_sync();
         const int s0 = rd * per, s1 = min(np, s0 + per);
+        if (NACC <= 2 && nfam > 0) {
+            V F[IT];
+#pragma unroll
+            for (int it = 0; it < IT; ++it) F[it] = areas[slot[it]];
+            for (int s = s0; s < s1; ++s) {
+                V nx[IT];  // the next product's values, on their way over this one's sums
+#pragma unroll
+                for (int it = 0; it < IT; ++it) nx[it] = areas[(min(s + 1, s1 - 1) - s0) * S * AREA + slot[it]];
+                const R fact = R(kSweepFact[sj]);
+#pragma unroll
+                for (int it = 0; it < IT; ++it) col_sweep_add<R, V, NACC>(sj, sf, fact, F[it], acc[it], kq[it], geo[it]);
+                if (++sf == nfam) {
+                    sf = 0;
+                    ++sj;
+                }
+#pragma unroll
+                for (int it = 0; it < IT; ++it) F[it] = nx[it];
+            }
+            lds_sync();
+            continue;
+        }
 #pragma unroll 2
         for (int s = s0; s < s1; ++s) {
             const ColSrc src = col_src(&sp.src[sub.p0 + s]);
@@ -1032,8 +1075,25 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
         }
         lds_sync();
     }
+    // what the owners read from here on, requested at once
+    if (njob > 0) preload(cb + co[0], co[0] >= 0);
+    V pv[IT][2], old[IT][kAADepth][2];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+            pv[it][a] = (p.prev[a] && co[it] >= 0) ? static_cast<const V*>(p.prev[a])[cb + co[it]] : cx<V>(R(0), R(0));
+        if (EARLY && p.aa_dots && co[it] >= 0) col_aa_old<V>(p, cb + co[it], old[it]);
+    }
+#pragma unroll
+    for (int s = 0; s < kPre; ++s) {
+        if (s >= nc) break;
+        const ColSrc src = col_src(&sp.src[kMaxProd + sub.c0 + s]);
+        const R cw = src.widx >= 0 ? R(s_aa[16 * kAASlots + src.widx]) : R(1);
+        if (co[0] >= 0) col_add<R, V, NACC>(src, cscale(raw[s / E][s % E], cw), acc[0], geo[0]);
+    }
 #pragma unroll 2
-    for (int s = sub.c0; s < sub.c1; ++s) {
+    for (int s = sub.c0 + kPre; s < sub.c1; ++s) {
         const ColSrc src = col_src(&sp.src[kMaxProd + s]);
         const R cw = src.widx >= 0 ? R(s_aa[16 * kAASlots + src.widx]) : R(1);
 #pragma unroll
@@ -1132,7 +1192,8 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
             const V f[2] = {col_source<V, NACC>(SRC_DIFF0, acc[it], pv[it], R(1)),
                             col_source<V, NACC>(SRC_DIFF1, acc[it], pv[it], R(1))};
             const int mx = x0 + co[it] / g.Ky;
-            col_aa_dots<V>(p, f, cb + co[it], mx == 0 ? 1.0 : 2.0, d);
+            if (!EARLY) col_aa_old<V>(p, cb + co[it], old[it]);
+            col_aa_dots<V>(p, f, old[it], mx == 0 ? 1.0 : 2.0, d);
         }
         col_aa_reduce(d, s_aa, p.aa_dots + ((long long)mem * gridDim.x + blockIdx.x) * kAASlots);
     }
@@ -1208,7 +1269,9 @@ __global__ void __launch_bounds__(64 * kCol1Waves) k_col1(const ColParams p) {
         for (int i = 0; i < kAASlots; ++i) d[i] = 0.0;
         if (wv == 0 && on) {
             const V f[2] = {col_source<V, NACC>(SRC_DIFF0, acc, pv, R(1)), col_source<V, NACC>(SRC_DIFF1, acc, pv, R(1))};
-            col_aa_dots<V>(p, f, cb, mx == 0 ? 1.0 : 2.0, d);
+            V old[kAADepth][2];
+            col_aa_old<V>(p, cb, old);
+            col_aa_dots<V>(p, f, old, mx == 0 ? 1.0 : 2.0, d);
         }
         col_aa_reduce(d, s_aa, p.aa_dots + ((long long)mem * gridDim.x + blockIdx.x) * kAASlots);
     }

@@ -67,7 +67,7 @@ static __device__ __attribute__((noinline)) void line_weights(Ctl* ctl, int n, c
     double tot[kAASlots], w[kAASlots];
 #pragma unroll
     for (int i = 0; i < kAASlots; ++i) tot[i] = s_tot[i];
-    aa_weights(ctl, n, tot, w, true);
+    aa_weights(ctl, &ctl->aa_gram[0][0], n, tot, w, true);
 #pragma unroll
     for (int i = 0; i < kAASlots; ++i) s_w[i] = w[i];
 }

@@ -132,14 +132,15 @@ static __device__ __forceinline__ double aa_sel(const double (&v)[kAASlots], int
 // dF_a = F_(a+1) - F_a over the history in sweep order (regularised by
 // 1e-12 trace / k; gamma = 0 when they fail), and write to w the weights of
 // x_(n+1) = g_n - sum_a gamma_a (G_(a+1) - G_a) on the history slots.
-// commit: store the new Gram entries (row and column of slot n) in the
-// control block.  The entries read here that are not in that row and column
+// commit: store the new Gram entries (row and column of slot n) in the control
+// block, whose entries (or a copy) gram gives.  Those read here are not in that
+// row and column: they
 // were stored by earlier sweeps, so workgroups of one pass that solve
 // side by side while one of them commits read the same values.
 // dots and w are indexed with compile-time indices only (registers); the
 // history slots in sweep order are H_a = (n - k + a) mod kAASlots, a <= k
-static __device__ void aa_weights(Ctl* ctl, int n, const double (&dots)[kAASlots], double (&w)[kAASlots],
-                                  bool commit) {
+static __device__ void aa_weights(Ctl* ctl, const double* gram, int n, const double (&dots)[kAASlots],
+                                  double (&w)[kAASlots], bool commit) {
     static_assert(kAADepth == 2, "the elimination below is written out for two residual differences");
     const int s = n % kAASlots, k = n < kAADepth ? n : kAADepth;
     const int H0 = (n - k) % kAASlots, H1 = (n - k + 1) % kAASlots, H2 = (n - k + 2) % kAASlots;
@@ -159,7 +160,7 @@ static __device__ void aa_weights(Ctl* ctl, int n, const double (&dots)[kAASlots
         const int r = a == 0 ? H0 : (a == 1 ? H1 : H2), c = b == 0 ? H0 : (b == 1 ? H1 : H2);
         if (r == s) return aa_sel(dots, c);
         if (c == s) return aa_sel(dots, r);
-        return ctl->aa_gram[r][c];
+        return gram[r * kAASlots + c];
     };
     double gam0 = 0.0, gam1 = 0.0;
     if (k == 1) {
@@ -226,6 +227,37 @@ __device__ __forceinline__ void col_aa_reduce(double (&d)[kAASlots], double* s_r
         for (int w = 0; w < nw; ++w) v += s_red[w * kAASlots + threadIdx.x];
         out[threadIdx.x] = v;
     }
+}
+
+// the weights inside a column-pass workgroup: its first wavefront adds the
+// member's partials in a fixed order (strided per lane, then across the lanes),
+// so every workgroup forms the same weights; s_w receives them
+static __device__ __forceinline__ void aa_block_weights(const ColParams& p, Ctl* ctl, int mem, bool commit, double* s_gram,
+                                                        double* s_w) {
+    if (threadIdx.x < 64) {
+        double d[kAASlots], w[kAASlots];
+        if (threadIdx.x < kAASlots * kAASlots) s_gram[threadIdx.x] = (&ctl->aa_gram[0][0])[threadIdx.x];
+#pragma unroll
+        for (int i = 0; i < kAASlots; ++i) d[i] = 0.0;
+        const double* part = p.aa_partial + (long long)mem * p.aa_nblk * kAASlots;
+#pragma unroll 4
+        for (int b = threadIdx.x; b < p.aa_nblk; b += 64)
+#pragma unroll
+            for (int i = 0; i < kAASlots; ++i) d[i] += part[b * kAASlots + i];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            if (off >= p.aa_nblk) continue;  // the lanes from there on hold zeros
+#pragma unroll
+            for (int i = 0; i < kAASlots; ++i) d[i] += __shfl_xor(d[i], off, 64);
+        }
+        wave_lds_sync();
+        if (threadIdx.x == 0) {
+            aa_weights(ctl, s_gram, p.aa_sweep, d, w, commit);
+#pragma unroll
+            for (int i = 0; i < kAASlots; ++i) s_w[i] = w[i];
+        }
+    }
+    lds_sync();
 }
 
 }  // namespace sbi
