@@ -3186,6 +3186,34 @@ extern "C" sbi_status sbi_batch_init(sbi_batch** out, int32_t m, const sbi_grid*
 // their streams and joins them back to b->cap.
 enum { PART_PROLOGUE = 0, PART_STEPS = 1, PART_EPILOGUE = 2 };
 
+// copies of `bytes` each on a stream, in one launch per kCopyList of them;
+// where destinations overlap (a caller's tensor given for two members) or an
+// address is no multiple of four, as copy commands in their order
+static sbi_status copy_fields(const std::vector<std::pair<const void*, void*>>& list, size_t bytes, hipStream_t s) {
+    std::vector<size_t> dst;
+    bool plain = bytes % 4 == 0;
+    for (const auto& c : list) {
+        plain = plain && ((size_t)c.first | (size_t)c.second) % 4 == 0;
+        dst.push_back((size_t)c.second);
+    }
+    std::sort(dst.begin(), dst.end());
+    for (size_t i = 1; i < dst.size(); ++i) plain = plain && dst[i] - dst[i - 1] >= bytes;
+    for (size_t i = 0; i < list.size(); i += plain ? kCopyList : 1) {
+        if (!plain) {
+            SBI_HIP(hipMemcpyAsync(list[i].second, list[i].first, bytes, hipMemcpyDeviceToDevice, s));
+            continue;
+        }
+        CopyList c{};
+        const int n = (int)std::min(list.size() - i, (size_t)kCopyList);
+        for (int k = 0; k < n; ++k) {
+            c.src[k] = list[i + k].first;
+            c.dst[k] = list[i + k].second;
+        }
+        SBI_TRY(hip_ok(launch_copy_list(c, n, bytes, s)));
+    }
+    return SBI_OK;
+}
+
 static sbi_status batch_enqueue_part(sbi_batch* b, sbi_state* states, int part, double dt, int n, double tol,
                                      double toff) {
     // nothing enqueued here may depend on the state time: a captured graph is
@@ -3200,13 +3228,13 @@ static sbi_status batch_enqueue_part(sbi_batch* b, sbi_state* states, int part, 
         SBI_HIP(hipStreamWaitEvent(gr.s, b->fork, 0));
         if (part == PART_PROLOGUE) {
             SBI_TRY(hip_ok(launch_ctl_acc_reset(c->ctl, c->batch, gr.s)));
+            std::vector<std::pair<const void*, void*>> in;
             for (size_t k = 0; k < gr.members.size(); ++k) {
                 const sbi_state& s = states[gr.members[k]];
-                SBI_HIP(hipMemcpyAsync(gr.st_eta + k * gr.field_bytes, s.eta, gr.field_bytes,
-                                       hipMemcpyDeviceToDevice, gr.s));
-                SBI_HIP(hipMemcpyAsync(gr.st_phi + k * gr.field_bytes, s.phi_s, gr.field_bytes,
-                                       hipMemcpyDeviceToDevice, gr.s));
+                in.emplace_back(s.eta, gr.st_eta + k * gr.field_bytes);
+                in.emplace_back(s.phi_s, gr.st_phi + k * gr.field_bytes);
             }
+            SBI_TRY(copy_fields(in, gr.field_bytes, gr.s));
             SBI_TRY(to_spectral(c, gr.st_eta, gr.st_phi, true));
         } else if (part == PART_STEPS) {
             double t = states[gr.members[0]].t + toff;
@@ -3228,13 +3256,13 @@ static sbi_status batch_enqueue_part(sbi_batch* b, sbi_state* states, int part, 
             }
         } else {
             SBI_TRY(to_physical(c, gr.st_eta, gr.st_phi));
+            std::vector<std::pair<const void*, void*>> out;
             for (size_t k = 0; k < gr.members.size(); ++k) {
                 const sbi_state& s = states[gr.members[k]];
-                SBI_HIP(hipMemcpyAsync(s.eta, gr.st_eta + k * gr.field_bytes, gr.field_bytes,
-                                       hipMemcpyDeviceToDevice, gr.s));
-                SBI_HIP(hipMemcpyAsync(s.phi_s, gr.st_phi + k * gr.field_bytes, gr.field_bytes,
-                                       hipMemcpyDeviceToDevice, gr.s));
+                out.emplace_back(gr.st_eta + k * gr.field_bytes, s.eta);
+                out.emplace_back(gr.st_phi + k * gr.field_bytes, s.phi_s);
             }
+            SBI_TRY(copy_fields(out, gr.field_bytes, gr.s));
         }
         SBI_HIP(hipEventRecord(gr.done, gr.s));
         SBI_HIP(hipStreamWaitEvent(b->cap, gr.done, 0));
@@ -3248,15 +3276,15 @@ static sbi_status batch_enqueue_part(sbi_batch* b, sbi_state* states, int part, 
 static sbi_status batch_keep(sbi_batch* b, sbi_state* states, bool save) {
     for (auto& gr : b->g) {
         sbi_ctx* c = gr.c;
+        std::vector<std::pair<const void*, void*>> list;
         for (size_t k = 0; k < gr.members.size(); ++k) {
             const sbi_state& st = states[gr.members[k]];
-            char* be = gr.bk_state + (2 * k) * gr.field_bytes;
-            char* bp = gr.bk_state + (2 * k + 1) * gr.field_bytes;
-            SBI_HIP(hipMemcpyAsync(save ? be : st.eta, save ? st.eta : be, gr.field_bytes, hipMemcpyDeviceToDevice,
-                                   b->cap));
-            SBI_HIP(hipMemcpyAsync(save ? bp : st.phi_s, save ? st.phi_s : bp, gr.field_bytes,
-                                   hipMemcpyDeviceToDevice, b->cap));
+            void* be = gr.bk_state + (2 * k) * gr.field_bytes;
+            void* bp = gr.bk_state + (2 * k + 1) * gr.field_bytes;
+            list.emplace_back(save ? st.eta : be, save ? be : st.eta);
+            list.emplace_back(save ? st.phi_s : bp, save ? bp : st.phi_s);
         }
+        SBI_TRY(copy_fields(list, gr.field_bytes, b->cap));
         if (c->grid.seed == SBI_SEED_PREV || c->grid.seed == SBI_SEED_NET) {
             char* d0 = static_cast<char*>(c->comp[C_DV]);   // C_DV, C_DB
             char* h0 = static_cast<char*>(c->comp[C_HV0]);  // C_HV0 .. C_HB0 + kHistTaps - 1

@@ -218,6 +218,12 @@ hipError_t launch_hist_adam(const HistParams& p, hipStream_t s);
 hipError_t launch_hist_newton(const HistParams& p, double lam, hipStream_t s);
 hipError_t launch_ctl_reset(Ctl* ctl, int batch, int slots, hipStream_t s);
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t s);
+constexpr int kCopyList = 120;  // copies of one launch (its arguments hold the pointers)
+struct CopyList {
+    const void* src[kCopyList];
+    void* dst[kCopyList];
+};
+hipError_t launch_copy_list(const CopyList& c, int n, size_t bytes, hipStream_t s);
 hipError_t launch_ctl_acc_reset(Ctl* ctl, int batch, hipStream_t s);
 // mixed precision: decision of an FP64 refinement sweep, the hand-over of its
 // residual to the FP32 correction solve (rv, rb FP64 compact -> bv, vn, bb, bn
