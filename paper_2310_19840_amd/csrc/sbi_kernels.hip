@@ -65,6 +65,25 @@ template <typename R, int NX, int EM = 8, bool TWC = false> struct Row {
     // exchanges need only wave-level ordering
     static constexpr bool WAVE = P <= 64;
 
+    // A thread's modes come in batches whose reads are issued together, the index
+    // clamped to the last one: a loop that tests each mode before its read waits out
+    // the latency once a mode.  128 x 64, FP64: sweeps 9.8 -> 8.3 us, N_phi 16.5 -> 13.8;
+    // 512 x 512, FP32: products of an order 8.0 -> 7.3 us, N_phi 16.9 -> 13.5; 1024 x 1024,
+    // FP32: sweeps 27.1 -> 25.3 us (in FP64 unchanged at 35.5).
+    static constexpr int kBatch = 4;
+    static __device__ __forceinline__ void fetch(V (&f)[kBatch], const V* __restrict__ Gr, const V* __restrict__ G2r, R c2,
+                                                 int k0, int kstep, int K, int ldh) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) f[u] = Gr[min(k0 + u * kstep, K - 1) * ldh];
+        if (G2r) {
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const V f2 = G2r[min(k0 + u * kstep, K - 1) * ldh];
+                f[u] = cx<V>(f[u].x + c2 * f2.x, f[u].y + c2 * f2.y);
+            }
+        }
+    }
+
     // v <- z = inverse row transform of (G + c2 G2) for the thread's row.
     // G, G2: member base of a half form [m_x][ny]; all rows of the workgroup
     // stage their kept spectra through LDS with coalesced column segments.
@@ -75,7 +94,6 @@ template <typename R, int NX, int EM = 8, bool TWC = false> struct Row {
                                                    R c2, const RowCtx& rc, V* lds_all,
                                                    const TW& twN, const V* __restrict__ twX, R scale) {
         V* lds = lds_all + rc.rl * LS;
-        lds_sync();  // other rows' transforms are done with the area the staging loop writes
         // a thread stages modes k0, k0 + kstep, ... of row r2 of the workgroup
         // (the block is a whole number of rows, and ny a multiple of rpw)
         const int r2 = rc.t & (rc.rpw - 1);
@@ -83,23 +101,26 @@ template <typename R, int NX, int EM = 8, bool TWC = false> struct Row {
         V* const zr = lds_all + r2 * LS;
         const V* const Gr = G + rc.y0 + r2;
         const V* const G2r = G2 ? G2 + rc.y0 + r2 : nullptr;
+        const int K = rc.Mx + 1;
+        V f[kBatch];
+        fetch(f, Gr, G2r, c2, k0, kstep, K, rc.ldh);
+        lds_sync();  // other rows' transforms are done with the area the staging loop writes
         if (2 * rc.Mx < N) {
             // kept band below N/2: F[k] alone gives Z[k] and Z[N-k], Z is zero
             // between them; the staging loop writes Z directly
-            const int K = rc.Mx + 1;
-#pragma unroll 4
-            for (int k = k0; k < K; k += kstep) {
-                V f = Gr[k * rc.ldh];
-                if (G2r) {
-                    const V f2 = G2r[k * rc.ldh];
-                    f = cx<V>(f.x + c2 * f2.x, f.y + c2 * f2.y);
-                }
-                const V h = cscale(f, R(0.5));
-                zr[k] = cadd(h, mul_i(cmul(h, cconj(twX[k]))));
-                if (k > 0) {
-                    const V hc = cconj(h);
-                    const V w = mul_i(cmul(hc, cconj(twX[N - k])));
-                    zr[N - k] = cx<V>(hc.x - w.x, hc.y - w.y);
+            for (int kb = k0; kb < K; kb += kBatch * kstep) {
+                if (kb > k0) fetch(f, Gr, G2r, c2, kb, kstep, K, rc.ldh);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    const int k = kb + u * kstep;
+                    if (k >= K) break;
+                    const V h = cscale(f[u], R(0.5));
+                    zr[k] = cadd(h, mul_i(cmul(h, cconj(twX[k]))));
+                    if (k > 0) {
+                        const V hc = cconj(h);
+                        const V w = mul_i(cmul(hc, cconj(twX[N - k])));
+                        zr[N - k] = cx<V>(hc.x - w.x, hc.y - w.y);
+                    }
                 }
             }
             for (int k = K + k0; k <= N - K; k += kstep) zr[k] = cx<V>(R(0), R(0));
@@ -107,17 +128,13 @@ template <typename R, int NX, int EM = 8, bool TWC = false> struct Row {
 #pragma unroll
             for (int q = 0; q < E; ++q) v[q] = lds[rc.j + q * P];
         } else {
-#pragma unroll 4
-            for (int m = k0; m < N; m += kstep) {
-                V f = cx<V>(R(0), R(0));
-                if (m <= rc.Mx) {
-                    f = Gr[m * rc.ldh];
-                    if (G2r) {
-                        const V f2 = G2r[m * rc.ldh];
-                        f = cx<V>(f.x + c2 * f2.x, f.y + c2 * f2.y);
-                    }
+            for (int mb = k0; mb < N; mb += kBatch * kstep) {
+                if (mb > k0) fetch(f, Gr, G2r, c2, mb, kstep, K, rc.ldh);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    const int m = mb + u * kstep;
+                    if (m < N) zr[m] = m <= rc.Mx ? f[u] : cx<V>(R(0), R(0));
                 }
-                zr[m] = f;
             }
             lds_sync();
 #pragma unroll
@@ -155,13 +172,24 @@ template <typename R, int NX, int EM = 8, bool TWC = false> struct Row {
         const V* const zr = lds_all + r2 * LS;
         V* const Hr = H + rc.y0 + r2;
         const int mstep = rc.nthr >> rc.rsh;
-#pragma unroll 4
-        for (int m = rc.t >> rc.rsh; m <= rc.Mx; m += mstep) {
-            const V zm = zr[m];
-            const V zc = cconj(zr[(N - m) & (N - 1)]);
-            const V ev = cx<V>(R(0.5) * (zm.x + zc.x), R(0.5) * (zm.y + zc.y));
-            const V od = mul_mi<false>(cx<V>(R(0.5) * (zm.x - zc.x), R(0.5) * (zm.y - zc.y)));
-            Hr[m * rc.ldh] = cadd(ev, cmul(twX[m], od));
+        for (int mb = rc.t >> rc.rsh; mb <= rc.Mx; mb += kBatch * mstep) {
+            V zm[kBatch], zc[kBatch], tw[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int m = min(mb + u * mstep, rc.Mx);
+                zm[u] = zr[m];
+                zc[u] = zr[(N - m) & (N - 1)];
+                tw[u] = twX[m];
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int m = mb + u * mstep;
+                const V c = cconj(zc[u]);
+                const V ev = cx<V>(R(0.5) * (zm[u].x + c.x), R(0.5) * (zm[u].y + c.y));
+                const V od = mul_mi<false>(cx<V>(R(0.5) * (zm[u].x - c.x), R(0.5) * (zm[u].y - c.y)));
+                const V F = cadd(ev, cmul(tw[u], od));
+                if (m <= rc.Mx) Hr[m * rc.ldh] = F;
+            }
         }
         lds_sync();
     }
