@@ -63,8 +63,9 @@ def algorithmic_bytes(kind: str, nx: int, ny: int, Kx: int, Ky: int, csz: int, r
 
     half-form array: ny*Kx complex; compact array: Ky*Kx complex; physical: nx*ny real.
     aa: the Anderson-mixed iteration, whose row pass also reads T(V_(n-1)) and
-    whose column pass writes T_V(x_n), f_n and g_n (compact) and the residual's
-    half forms, not the next iterate.
+    whose column pass reads the two older residuals (for the inner products) and
+    writes T_V(x_n), f_n and g_n (compact) and the residual's half forms, not the
+    next iterate.
     """
     half = ny * Kx * csz
     comp = Ky * Kx * csz
@@ -81,6 +82,7 @@ def algorithmic_bytes(kind: str, nx: int, ny: int, Kx: int, Ky: int, csz: int, r
         if aa:
             # write T_V(x_n), the residual f_n and relaxed sweep g_n (compact, V and phi_b parts) and the half
             # forms of f_n and T_V(x_n)
+            nin_c += 2 * (1 + (1 if vd else 0))
             return nprod * half + nin_c * comp + 2 * half + (1 + 2 * (1 + (1 if vd else 0))) * comp
         nout_c = 2 + (1 if vd else 0)
         return nprod * half + nin_c * comp + (2 + ncomp) * half + nout_c * comp
@@ -89,7 +91,7 @@ def algorithmic_bytes(kind: str, nx: int, ny: int, Kx: int, Ky: int, csz: int, r
 
 KERNEL_SOURCES = ["paper_2310_19840_amd/csrc/sbi_kernels.hip", "paper_2310_19840_amd/csrc/sbi_fft.hpp",
                   "paper_2310_19840_amd/csrc/sbi_internal.hpp", "paper_2310_19840_amd/csrc/sbi_kernels.hpp",
-                  "paper_2310_19840_amd/csrc/sbi_device.hpp"]
+                  "paper_2310_19840_amd/csrc/sbi_device.hpp", "paper_2310_19840_amd/csrc/sbi_stage.hpp"]
 TRAFFIC_RECORD = "profiles/sweep_kernels_traffic_c5_1024.txt"
 
 

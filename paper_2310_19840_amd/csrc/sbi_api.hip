@@ -1048,6 +1048,7 @@ static sbi_status anderson_mix(sbi_ctx* c, int n) {
     b.p.aa_partial = c->aa_partial;
     b.p.aa_nblk = c->gd.Kxp / c->gd.col_C;
     b.p.aa_sweep = n;
+    b.p.nmix = k + 1;
     b.cout(SRC_ACC0, CMP(C_VN));
     b.inv(SRC_ACC0, DV_NONE, HALF(H_GV));
     if (c->vd) {

@@ -150,6 +150,9 @@ struct ColParams {
     // slots; the first workgroup of a member stores the new Gram entries
     const double* aa_partial;
     int aa_nblk, aa_sweep;
+    // > 0: a mixing pass: the compact inputs are the V (and phi_b) parts of so many relaxed sweeps,
+    // oldest first, each scaled by its weight and added to its sum
+    int nmix;
     // inner products <F_i, f_n> of the residual history formed by a sweep's
     // pass (f_n the differences of its accumulators to prev, the older ones
     // the ring aa_f[V, phi_b part][slot]): one partial per workgroup

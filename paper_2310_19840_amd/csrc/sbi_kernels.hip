@@ -685,8 +685,8 @@ __global__ void __launch_bounds__(row_threads<NX>()) k_row_feat(const RowFeatPar
 // small grids the chain of dependent loads and barriers of one workgroup.
 // Measured per launch, against one whose transform threads also formed the sums
 // of the modes they held: FP64 1024 x 1024 sweep 36 us (37, and 5.6 for the
-// inner products in a kernel of their own), its inverse pass 16.6 (17.5); FP32
-// 512 x 512 SA order 8.5 (21.7); FP64 128 x 64 sweep 20 (31); a single product
+// inner products in a kernel of their own), its inverse pass 15.4 (17.5); FP32
+// 512 x 512 SA order 7.6 (21.7); FP64 128 x 64 sweep 14.6 (31); a single product
 // without inverse at 1024 rows 6.9 (11.8).
 //
 // S ("classes"): columns of more than 512 rows are split by decimation in
@@ -1004,11 +1004,13 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
     }
     const long long cb = mem * g.s_cmp + (long long)x0 * g.Ky;  // compact base of the workgroup
     if (njob == 0) preload(cb + co[0], co[0] >= 0);
+    double head[kAASlots] = {};
+    if (p.aa_partial) aa_head(p, mem, head);
     double omega = 1.0;
     // the decision is the same in every thread (the leader's header updates
     // cannot change it), so the workgroup returns as a whole
     if (!col_control(p, ctl, blockIdx.x == 0 && blockIdx.y == 0 && t == 0, &omega)) return;
-    if (p.aa_partial) aa_block_weights(p, ctl, mem, blockIdx.x == 0, s_aa, s_aa + 16 * kAASlots);
+    if (p.aa_partial) aa_block_weights(p, ctl, mem, blockIdx.x == 0, head, s_aa, s_aa + 16 * kAASlots);
 
     V acc[IT][NACC];
 #pragma unroll
@@ -1113,9 +1115,32 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
             pv[it][a] = (p.prev[a] && co[it] >= 0) ? static_cast<const V*>(p.prev[a])[cb + co[it]] : cx<V>(R(0), R(0));
         if (EARLY && p.aa_dots && co[it] >= 0) col_aa_old<V>(p, cb + co[it], old[it]);
     }
+    // a mixing pass's sums and a sweep's forcing need no descriptions (decoded, an
+    // input costs some 0.4 us; a mixing pass of 128 x 64 FP64 took 10.6 us, now 8.8,
+    // of 1024 x 1024 17.8, now 15.4)
+    const int kmix = kPre >= 2 * kAASlots && NACC <= 2 ? p.nmix : 0;
+    const bool forced = kPre >= 2 && NACC <= 2 && nfam > 0;
+    if constexpr (kPre >= 2) {
+        if (kmix > 0) {
+#pragma unroll
+            for (int a = 0; a < (kPre >= 2 * kAASlots ? kAASlots : 0); ++a) {
+                if (a >= kmix) break;
+                const R w = R(s_aa[16 * kAASlots + (p.aa_sweep - kmix + 1 + a) % kAASlots]);
+                if (NACC == 1) {
+                    acc[0][0] = cadd(acc[0][0], cscale(raw[a / E][a % E], w));
+                } else {
+                    acc[0][0] = cadd(acc[0][0], cscale(raw[2 * a / E][2 * a % E], w));
+                    acc[0][NACC - 1] = cadd(acc[0][NACC - 1], cscale(raw[(2 * a + 1) / E][(2 * a + 1) % E], w));
+                }
+            }
+        } else if (forced) {
+            acc[0][0] = cadd(acc[0][0], raw[0][0]);
+            if (NACC > 1) acc[0][NACC - 1] = cadd(acc[0][NACC - 1], raw[1 / E][1 % E]);
+        }
+    }
 #pragma unroll
     for (int s = 0; s < kPre; ++s) {
-        if (s >= nc) break;
+        if (s >= nc || kmix > 0 || forced) break;
         const ColSrc src = col_src(&sp.src[kMaxProd + sub.c0 + s]);
         const R cw = src.widx >= 0 ? R(s_aa[16 * kAASlots + src.widx]) : R(1);
         if (co[0] >= 0) col_add<R, V, NACC>(src, cscale(raw[s / E][s % E], cw), acc[0], geo[0]);
@@ -1255,8 +1280,10 @@ __global__ void __launch_bounds__(64 * kCol1Waves) k_col1(const ColParams p) {
     for (int a = 0; a < 2; ++a) pv[a] = (p.prev[a] && on) ? static_cast<const V*>(p.prev[a])[cb] : zero;
     const ColGeo<R> geo = col_geo<R>(p, mx, 0, g.href[mem]);
     double omega = 1.0;
+    double head[kAASlots] = {};
+    if (p.aa_partial) aa_head(p, mem, head);
     if (!col_control(p, ctl, blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0, &omega)) return;
-    if (p.aa_partial) aa_block_weights(p, ctl, mem, blockIdx.x == 0, s_aa, s_aa + 16 * kAASlots);
+    if (p.aa_partial) aa_block_weights(p, ctl, mem, blockIdx.x == 0, head, s_aa, s_aa + 16 * kAASlots);
     lds_sync();
     V acc[NACC];
 #pragma unroll

@@ -231,17 +231,23 @@ __device__ __forceinline__ void col_aa_reduce(double (&d)[kAASlots], double* s_r
 
 // the weights inside a column-pass workgroup: its first wavefront adds the
 // member's partials in a fixed order (strided per lane, then across the lanes),
-// so every workgroup forms the same weights; s_w receives them
-static __device__ __forceinline__ void aa_block_weights(const ColParams& p, Ctl* ctl, int mem, bool commit, double* s_gram,
-                                                        double* s_w) {
+// so every workgroup forms the same weights; s_w receives them.  head: the first
+// 64 partials, read ahead by aa_head.
+__device__ __forceinline__ void aa_head(const ColParams& p, int mem, double (&head)[kAASlots]) {
+#pragma unroll
+    for (int i = 0; i < kAASlots; ++i)
+        head[i] = (int)threadIdx.x < min(64, p.aa_nblk) ? p.aa_partial[((long long)mem * p.aa_nblk + threadIdx.x) * kAASlots + i] : 0.0;
+}
+static __device__ __forceinline__ void aa_block_weights(const ColParams& p, Ctl* ctl, int mem, bool commit,
+                                                        const double (&head)[kAASlots], double* s_gram, double* s_w) {
     if (threadIdx.x < 64) {
         double d[kAASlots], w[kAASlots];
         if (threadIdx.x < kAASlots * kAASlots) s_gram[threadIdx.x] = (&ctl->aa_gram[0][0])[threadIdx.x];
 #pragma unroll
-        for (int i = 0; i < kAASlots; ++i) d[i] = 0.0;
+        for (int i = 0; i < kAASlots; ++i) d[i] = head[i];
         const double* part = p.aa_partial + (long long)mem * p.aa_nblk * kAASlots;
 #pragma unroll 4
-        for (int b = threadIdx.x; b < p.aa_nblk; b += 64)
+        for (int b = threadIdx.x + 64; b < p.aa_nblk; b += 64)
 #pragma unroll
             for (int i = 0; i < kAASlots; ++i) d[i] += part[b * kAASlots + i];
 #pragma unroll
