@@ -15,7 +15,7 @@
  * tol, state pointers, seeds and sweep budgets); up to 8 instantiated graphs
  * are kept, least recently used first out.  With SBI_BATCH_AUTOTUNE each
  * group's launch plan (row-transform radix and twiddle mode, rows per row
- * workgroup, column-pass product split; sbi.h, sbi_plan) is chosen at init:
+ * workgroup; sbi.h, sbi_plan) is chosen at init:
  * one group is tuned like a context (sbi_autotune); with several, each
  * group's candidates are timed while every group runs its unit of work
  * concurrently (group by group, from the default plans), since the fastest
@@ -87,7 +87,7 @@ sbi_status sbi_batch_net_load(sbi_batch* b, const void* weights, size_t bytes);
 sbi_status sbi_batch_net_hist_load(sbi_batch* b, int32_t taps, int32_t bins, double dk, const float* w);
 
 /* Number of member groups and, per group (g < groups), its member count and
-   the column-pass split of its plan (0: none). */
+   the col_split kept with its plan (0: none). */
 int32_t sbi_batch_groups(const sbi_batch* b, int32_t* members_out, int32_t* split_out, int32_t n);
 
 /* Launch plan of group g (sbi.h, sbi_plan; us and cached are 0). */
