@@ -2219,7 +2219,8 @@ extern "C" sbi_status sbi_step(sbi_ctx* c, sbi_state* state, double dt, int32_t 
     sbi_step_info si{};
     sbi_status worst = SBI_OK;
     double t = state->t;
-    if (n > 0 && line_ok(c)) {
+    bool line = n > 0 && line_ok(c);
+    if (line) {
         LineParams lp = line_params(c, tol);
         lp.rk.h = dt;
         lp.load = lp.acc_reset = 1;
@@ -2234,9 +2235,17 @@ extern "C" sbi_status sbi_step(sbi_ctx* c, sbi_state* state, double dt, int32_t 
             if (c->grid.mode == SBI_MODE_SA) continue;
             SBI_TRY(read_heads(c));
             const sbi_status st = solve_status(c, nullptr, true);
-            if (st < 0) return st;
+            if (st < 0 && c->batch == 1) return st;
+            if (st < 0) {
+                // each member ran until its own failure; the call reports the first
+                // one to happen, which the separate passes find (the state is as given)
+                line = false;
+                t = state->t;
+                break;
+            }
         }
-        if (c->grid.mode == SBI_MODE_SA) {
+        if (!line) {
+        } else if (c->grid.mode == SBI_MODE_SA) {
             si.solves = 4ll * n * c->batch;
         } else {
             for (int b = 0; b < c->batch; ++b) {
@@ -2249,7 +2258,9 @@ extern "C" sbi_status sbi_step(sbi_ctx* c, sbi_state* state, double dt, int32_t 
             }
             c->st.sweeps = (double)si.sweeps_total;
         }
-    } else {
+    }
+    if (!line) {
+        c->st = Stats();
         SBI_TRY(to_spectral(c, state->eta, state->phi_s, true));
         for (int s = 0; s < n; ++s) {
             for (int stage = 0; stage < 4; ++stage) {

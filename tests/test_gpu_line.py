@@ -80,3 +80,23 @@ def test_nonfinite_member(gpu, nx, mode):
                 call()
             assert err.value.code == -5
         assert torch.equal(e.nan_to_num(), keep[0].nan_to_num()) and torch.equal(p, keep[1])
+
+
+@pytest.mark.parametrize("amp", [0.12, 0.2, 0.3, 0.6])
+def test_first_failure_is_reported(gpu, amp):
+    # member 1 is non-finite at once; member 0, at the steeper amplitudes, fails some steps later with another code
+    import torch
+    from paper_2310_19840_amd import SBIError, Solver
+    lx, depth, eta, phi = _case(128, 2, 1)
+    eta[0] *= amp / 0.04
+    phi[0] *= amp / 0.04
+    eta[1, 0, 7] = np.inf
+    codes = []
+    for separate in (False, True):
+        s = Solver(128, 1, lx, 1.0, depth, h_ref=1.5, batch=2, device=gpu, mode="iter", max_sweeps=100)
+        if separate:
+            s.profile()
+        with pytest.raises(SBIError) as err:
+            s.step(*(torch.tensor(a, device=gpu) for a in (eta, phi)), 0.1, 7, tol=1e-10)
+        codes.append(err.value.code)
+    assert codes[0] == codes[1]
