@@ -990,7 +990,8 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
     // the owner's mode(s): entry i = t + it T of the workgroup's compact modes
     const double href = g.href[mem];
     ColGeo<R> geo[IT];
-    int slot[IT];          // element of the areas holding the mode: class area, column, transform index
+    int slot[IT];          // element of the areas holding the mode: class area, column, transform index (0: no mode,
+                           // so that a thread without one reads inside the areas too)
     int co[IT];            // compact offset from the workgroup's first column, -1: no mode
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
@@ -999,7 +1000,7 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
         const bool on = c2 < CW && x0 + c2 < g.Kx;
         const int n = r <= g.My ? r : r + NY - g.Ky;
         co[it] = on ? i : -1;
-        slot[it] = (n % S) * AREA + c2 * REG + n / S;
+        slot[it] = on ? (n % S) * AREA + c2 * REG + n / S : 0;
         geo[it] = col_geo<R>(p, x0 + c2, r, href);
     }
     const long long cb = mem * g.s_cmp + (long long)x0 * g.Ky;  // compact base of the workgroup
