@@ -228,11 +228,11 @@ __device__ __forceinline__ double pair_div(double a, double b) {
 __device__ __forceinline__ float pair_div(float a, float b) { return a / b; }
 
 // log(1 + x).  The pair kernels' arguments are the height differences' effect
-// on a squared distance, small except for the nearest points: below, as
+// on a squared distance, small except for the nearest points: pair_small, as
 // 2 atanh(s), s = x / (2 + x), by its series to s^21 (the next term is below
 // 2e-18 of the value for |s| <= 0.177); the library function elsewhere.
-__device__ __forceinline__ double pair_log1p(double x) {
-    if (!(x > -0.3 && x < 0.42)) return log1p(x);
+__device__ __forceinline__ bool pair_is_small(double x) { return x > -0.3 && x < 0.42; }
+__device__ __forceinline__ double pair_small(double x) {
     const double s = pair_div(x, 2.0 + x), z = s * s;
     double q = 1.0 / 21.0;
     q = fma(q, z, 1.0 / 19.0);
@@ -246,6 +246,8 @@ __device__ __forceinline__ double pair_log1p(double x) {
     q = fma(q, z, 1.0 / 3.0);
     return fma(2.0 * s * z, q, 2.0 * s);
 }
+__device__ __forceinline__ double pair_log1p(double x) { return pair_is_small(x) ? pair_small(x) : log1p(x); }
+__device__ __forceinline__ float pair_small(float x) { return log1p(x); }
 __device__ __forceinline__ float pair_log1p(float x) { return log1p(x); }
 
 // A pair pass: kFullThreads evaluation points per workgroup, each served by
@@ -604,7 +606,8 @@ __global__ void __launch_bounds__(kPairThreads) k_full_spairs(const FullParams p
 // S_BS[V_n] - D_BB[phi_b] (surface and bed sources, phi_b of this sweep),
 // which also decides the sweep.  With a = pi (x_j - x_i) / L and b the scaled
 // height difference pi (y_j - y_i) / L of source and evaluation point:
-// G = -1/2 ln(4 (sin^2 a + sinh^2 b)), taken against the flat geometry's table;
+// G = -1/2 ln(4 (sin^2 a + sinh^2 b)), taken against the flat geometry's table
+// where the distances are alike;
 // the double layer of a surface source is Im[(pi/L) cot(a + i b) (1 + i eta_x,j)],
 // that of a bed source -Im[(pi/L) cot(a + i b) (1 + i b_x,j)], with the curvature
 // limit -b_xx / (2 (1 + b_x^2)) at coincident bed points.
@@ -675,8 +678,12 @@ __global__ void __launch_bounds__(kPairThreads) k_full_bpairs(const FullParams p
                 const R ch = tcj[jj] * cbi + tsj[jj] * sbi;
                 acc += (double)pair_div(R(-2) * sh * ch + s2a * tex[jj], sa2 + sh * sh) * (double)tsrc[jj];
             } else {
+                // 1/2 ln(4 (sin^2 a + sinh^2 b)).  Against the flat geometry only near it: where
+                // the bed rises far above the reference depth y tends to -1, 1 + y would cancel
+                // (and the flat distance may overflow), and the logarithm is that of the distance
                 const R y = (sh - sh0) * (sh + sh0) * R(rfl[d]);
-                acc += (lfl[d] + M_LN2 + 0.5 * (double)pair_log1p(y)) * (double)tsrc[jj];
+                const double l = pair_is_small(y) ? lfl[d] + 0.5 * (double)pair_small(y) : 0.5 * (double)log(sa2 + sh * sh);
+                acc += (l + M_LN2) * (double)tsrc[jj];
                 if (j != i) {
                     // minus the bed's double layer at (x_j, b_j)
                     R chb;
