@@ -280,10 +280,15 @@ __device__ __forceinline__ PairBlock pair_block(int j0, int jend, int lane) {
 }
 
 // The sinh and cosh of the distance between two boundaries, pi (y - y') / L =
-// a + b with a >= 0 from the lower one and b from the upper (the image, the
-// bed), come from per-point tables: sinh a cosh b + cosh a sinh b.  The
-// boundaries do not touch, so the sum does not cancel beyond what the
-// difference of the heights does.
+// a + b, come from per-point tables: sinh a cosh b + cosh a sinh b.  Between
+// surface and bed, a is the surface's height above a level and b the bed's depth
+// below it; the level is the surface's lowest point (the solve's set-up left it in
+// the control header), so that a >= 0, b >= 0 wherever the bed lies below every
+// trough, and the sums add terms of one sign: against z = 0 a surface far below it
+// would lose exp(2 pi |eta| / L) in relative accuracy.  The tables and sums are FP64
+// in both precisions and rounded once, as the difference of the heights would be.
+__device__ __forceinline__ double full_lowest(const FullParams& p, int m) { return unord_bits(p.ctl[m].eta_min); }
+
 template <typename R, int KIND>
 __global__ void __launch_bounds__(kPairThreads) k_full_pairs(const FullParams p) {
     __shared__ R te[kFullThreads], tex[kFullThreads], tsrc[kFullThreads], tsj[kFullThreads], tcj[kFullThreads];
@@ -529,8 +534,8 @@ __global__ void __launch_bounds__(64 * kSymWaves) k_full_sympairs(const FullPara
 // this sweep, at the surface points over a slice of the source points
 template <typename R>
 __global__ void __launch_bounds__(kPairThreads) k_full_spairs(const FullParams p) {
-    __shared__ R te[kFullThreads], tsrc[kFullThreads], tsj[kFullThreads], tcj[kFullThreads], tbx[kFullThreads];
-    __shared__ double tpb[kFullThreads];
+    __shared__ R te[kFullThreads], tsrc[kFullThreads], tbx[kFullThreads];
+    __shared__ double tpb[kFullThreads], tsj[kFullThreads], tcj[kFullThreads];
     __shared__ double red[(kPairLanes - 1) * kFullThreads];
     const int t = threadIdx.x;
     const int il = t % kFullThreads, lane = __builtin_amdgcn_readfirstlane(t / kFullThreads);
@@ -560,7 +565,8 @@ __global__ void __launch_bounds__(kPairThreads) k_full_spairs(const FullParams p
     const bool on = i < n;
     const R etai = on ? eta[i] : R(0);
     const R exi = on ? ex[i] : R(0);
-    const R sei = sinh(pl * etai), cei = cosh(pl * etai);
+    const double low = full_lowest(p, m), hi = pld * ((double)etai - low);  // the surface point above the level
+    const double sei = sinh(hi), cei = cosh(hi);
     double accb = 0.0, accs = 0.0;
     const int chunk = (n + gridDim.y - 1) / gridDim.y;
     const int jbeg = split * chunk, jend = min(n, jbeg + chunk);
@@ -570,9 +576,9 @@ __global__ void __launch_bounds__(kPairThreads) k_full_spairs(const FullParams p
         if (t < kFullThreads && jl < jend) {
             te[t] = eta[jl];
             tsrc[t] = hasv ? src[jl] : R(0);
-            const double b = -pld * bz[jl];  // the bed's depth below z = 0
-            tsj[t] = R(sinh(b));
-            tcj[t] = R(cosh(b));
+            const double b = pld * (low - bz[jl]);  // the bed's depth below the level
+            tsj[t] = sinh(b);
+            tcj[t] = cosh(b);
             tbx[t] = R(bxs[jl]);
             tpb[t] = pbs[jl];
         }
@@ -587,7 +593,7 @@ __global__ void __launch_bounds__(kPairThreads) k_full_spairs(const FullParams p
             const R s2a = R(s2at[d]);
             // the bed source (x_j, b_j): -D_SB = Im[(pi/L) cot(a + i b) (1 + i b_x,j)],
             // b = pi (b_j - eta_i) / L (the bed lies below every surface point): -b from the tables
-            const R sh = tsj[jj] * cei + tcj[jj] * sei, ch = tcj[jj] * cei + tsj[jj] * sei;
+            const R sh = R(tsj[jj] * cei + tcj[jj] * sei), ch = R(tcj[jj] * cei + tsj[jj] * sei);
             accb += (double)pair_div(R(2) * sh * ch + s2a * tbx[jj], sa2 + sh * sh) * tpb[jj];
             if (hasv) {
                 // the direct single layer minus the flat one, as in the image form
@@ -613,7 +619,8 @@ __global__ void __launch_bounds__(kPairThreads) k_full_spairs(const FullParams p
 // limit -b_xx / (2 (1 + b_x^2)) at coincident bed points.
 template <typename R, int KIND>
 __global__ void __launch_bounds__(kPairThreads) k_full_bpairs(const FullParams p) {
-    __shared__ R tex[kFullThreads], tsrc[kFullThreads], tsj[kFullThreads], tcj[kFullThreads];
+    __shared__ R tex[kFullThreads], tsrc[kFullThreads];
+    __shared__ double tsj[kFullThreads], tcj[kFullThreads];
     __shared__ double tbz[kFullThreads], tbx[kFullThreads], tpb[kFullThreads];
     __shared__ double red[(kPairLanes - 1) * kFullThreads];
     const int t = threadIdx.x;
@@ -641,10 +648,11 @@ __global__ void __launch_bounds__(kPairThreads) k_full_bpairs(const FullParams p
     const double* rfl = static_cast<const double*>(p.rfl) + mb;
     const R pl = R(M_PI / p.lx);
     const double pld = M_PI / p.lx;
-    const R sh0 = R(sinh(full_flat(p, m)));
+    const double sh0 = sinh(full_flat(p, m));
     const bool on = i < n;
     const double bzi = on ? bz[i] : 0.0;
-    const R sbi = R(sinh(-pld * bzi)), cbi = R(cosh(pld * bzi));  // the bed point's depth below z = 0
+    const double low = full_lowest(p, m), bi = pld * (low - bzi);  // the bed point's depth below the level
+    const double sbi = sinh(bi), cbi = cosh(bi);
     double acc = 0.0, accb = 0.0;
     const int chunk = (n + gridDim.y - 1) / gridDim.y;
     const int jbeg = split * chunk, jend = min(n, jbeg + chunk);
@@ -652,7 +660,7 @@ __global__ void __launch_bounds__(kPairThreads) k_full_bpairs(const FullParams p
         __syncthreads();
         const int jl = j0 + t;
         if (t < kFullThreads && jl < jend) {
-            const R e = pl * eta[jl];
+            const double e = pld * ((double)eta[jl] - low);  // the surface above the level
             tsj[t] = sinh(e);
             tcj[t] = cosh(e);
             tex[t] = ex[jl];
@@ -673,16 +681,17 @@ __global__ void __launch_bounds__(kPairThreads) k_full_bpairs(const FullParams p
             const R s2a = R(s2at[d]);
             const R sa2 = R(s2[d]);
             // the surface source (x_j, eta_j) seen from the bed point (x_i, b_i)
-            const R sh = tsj[jj] * cbi + tcj[jj] * sbi;
+            const double shd = tsj[jj] * cbi + tcj[jj] * sbi;
+            const R sh = R(shd);
             if (KIND == 2) {
-                const R ch = tcj[jj] * cbi + tsj[jj] * sbi;
+                const R ch = R(tcj[jj] * cbi + tsj[jj] * sbi);
                 acc += (double)pair_div(R(-2) * sh * ch + s2a * tex[jj], sa2 + sh * sh) * (double)tsrc[jj];
             } else {
                 // 1/2 ln(4 (sin^2 a + sinh^2 b)).  Against the flat geometry only near it: where
                 // the bed rises far above the reference depth y tends to -1, 1 + y would cancel
                 // (and the flat distance may overflow), and the logarithm is that of the distance
-                const R y = (sh - sh0) * (sh + sh0) * R(rfl[d]);
-                const double l = pair_is_small(y) ? lfl[d] + 0.5 * (double)pair_small(y) : 0.5 * (double)log(sa2 + sh * sh);
+                const double y = (shd - sh0) * (shd + sh0) * rfl[d];
+                const double l = pair_is_small(y) ? lfl[d] + 0.5 * (double)pair_small(R(y)) : 0.5 * (double)log(sa2 + sh * sh);
                 acc += (l + M_LN2) * (double)tsrc[jj];
                 if (j != i) {
                     // minus the bed's double layer at (x_j, b_j)
