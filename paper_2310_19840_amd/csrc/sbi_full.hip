@@ -289,9 +289,27 @@ __device__ __forceinline__ PairBlock pair_block(int j0, int jend, int lane) {
 // in both precisions and rounded once, as the difference of the heights would be.
 __device__ __forceinline__ double full_lowest(const FullParams& p, int m) { return unord_bits(p.ctl[m].eta_min); }
 
+// Between surface and image the level is the bed itself, halfway between them: a
+// and b are pi / L times the two points' heights above it.
+//
+// Single layer of the image form, direct part and image minus flat image,
+//     -1/2 ln(1 + x) - 1/2 ln((sin^2 + sinh^2(pi (eta_i + eta_j + 2 h) / L)) / (sin^2 + sinh^2(2 pi h / L))),
+// as one logarithm of (1 + x)(1 + y), y from the difference of the squares.  For a
+// surface far below z = 0 y tends to -1 and 1 + y would cancel: it is then the ratio
+// itself.  sh: sinh of the image's distance, sh0 of the flat one, s2, rfl: the flat
+// geometry's tables at the pair's index distance.
+template <typename R>
+__device__ __forceinline__ R pair_single(R x, double sh, double sh0, const double* s2, double rfl) {
+    const double y = (sh - sh0) * (sh + sh0) * rfl;
+    if (!(y > -0.3)) return R(-0.5) * log((R(1) + x) * R((*s2 + sh * sh) * rfl));
+    const R yr = R(y);
+    return R(-0.5) * pair_log1p(x + yr + x * yr);
+}
+
 template <typename R, int KIND>
 __global__ void __launch_bounds__(kPairThreads) k_full_pairs(const FullParams p) {
-    __shared__ R te[kFullThreads], tex[kFullThreads], tsrc[kFullThreads], tsj[kFullThreads], tcj[kFullThreads];
+    __shared__ R te[kFullThreads], tex[kFullThreads], tsrc[kFullThreads];
+    __shared__ double tsj[kFullThreads], tcj[kFullThreads];
     __shared__ double red[(kPairLanes - 1) * kFullThreads];
     const int t = threadIdx.x;
     const int il = t % kFullThreads, lane = __builtin_amdgcn_readfirstlane(t / kFullThreads);
@@ -315,15 +333,15 @@ __global__ void __launch_bounds__(kPairThreads) k_full_pairs(const FullParams p)
     const double* rfl = static_cast<const double*>(p.rfl) + (long long)m * n;
     const R pl = R(M_PI / p.lx);
     const bool img = !full_deep(p, m) && !full_bed(p, m);  // the image form keeps the bed's image
-    const R b2h = R(2.0 * M_PI * p.href[m] / p.lx);        // 2 pi h / L
-    const R sh0 = img ? sinh(b2h) : R(0);
+    const double pld = M_PI / p.lx, h = p.href[m];
+    const double sh0 = img ? sinh(2.0 * pld * h) : 0.0;
     // this point's values
     const bool on = i < n;
     const R etai = on ? eta[i] : R(0);
     const R exi = on ? ex[i] : R(0);
-    R sbi = R(0), cbi = R(1);
+    double sbi = 0.0, cbi = 1.0;
     if (img) {
-        const R b = pl * etai + b2h;
+        const double b = pld * ((double)etai + h);
         sbi = sinh(b);
         cbi = cosh(b);
     }
@@ -337,8 +355,9 @@ __global__ void __launch_bounds__(kPairThreads) k_full_pairs(const FullParams p)
             tex[t] = ex[j0 + t];
             tsrc[t] = src[j0 + t];
             if (img) {
-                tsj[t] = sinh(pl * te[t]);
-                tcj[t] = cosh(pl * te[t]);
+                const double a = pld * ((double)te[t] + h);
+                tsj[t] = sinh(a);
+                tcj[t] = cosh(a);
             }
         }
         __syncthreads();
@@ -349,17 +368,10 @@ __global__ void __launch_bounds__(kPairThreads) k_full_pairs(const FullParams p)
             const int d = (j - i + n) & (n - 1);
             R kv;
             if (KIND == 1) {
-                // direct part -1/2 ln(1 + sinh^2 / sin^2) (its limit -1/2 ln(1 + eta_x^2) at j = i) and
-                // image minus flat image, -1/2 ln((sin^2 + sinh^2(pi (eta_i + eta_j + 2h) / L)) / (sin^2 +
-                // sinh^2(2 pi h / L))), as one logarithm
+                // direct part -1/2 ln(1 + sinh^2 / sin^2) (its limit -1/2 ln(1 + eta_x^2) at j = i), and the image's
                 const R shb = sinh_series(pl * (te[jj] - etai));
-                R x = j == i ? exi * exi : shb * shb * R(rs2[d]);
-                if (img) {
-                    const R shp = tsj[jj] * cbi + tcj[jj] * sbi;
-                    const R y = (shp - sh0) * (shp + sh0) * R(rfl[d]);
-                    x = x + y + x * y;
-                }
-                kv = R(-0.5) * pair_log1p(x);
+                const R x = j == i ? exi * exi : shb * shb * R(rs2[d]);
+                kv = img ? pair_single(x, tsj[jj] * cbi + tcj[jj] * sbi, sh0, s2 + d, rfl[d]) : R(-0.5) * pair_log1p(x);
             } else {
                 // Im[(pi/L) cot(a + i b) (1 + i eta_x,j)], a = pi (x_j - x_i)/L, b = pi (eta_j - eta_i)/L:
                 // cot(a + i b) = (sin 2a - i sinh 2b) / (2 (sin^2 a + sinh^2 b))
@@ -371,7 +383,7 @@ __global__ void __launch_bounds__(kPairThreads) k_full_pairs(const FullParams p)
                 kv = j == i ? R(0) : pair_div(R(-2) * shb * chb + s2a * tex[jj], sa2 + shb * shb);
                 if (img) {
                     // the image partner: b' = pi (eta_i + eta_j + 2h) / L
-                    const R shp = tsj[jj] * cbi + tcj[jj] * sbi, chp = tcj[jj] * cbi + tsj[jj] * sbi;
+                    const R shp = R(tsj[jj] * cbi + tcj[jj] * sbi), chp = R(tcj[jj] * cbi + tsj[jj] * sbi);
                     kv += pair_div(R(-2) * shp * chp + s2a * tex[jj], sa2 + shp * shp);
                 }
                 kv *= R(0.5) * pl;
@@ -416,7 +428,8 @@ static_assert(kSymT == 64, "a tile's columns are the lanes of one wavefront");
 
 template <typename R, int Q>
 __global__ void __launch_bounds__(64 * kSymWaves) k_full_sympairs(const FullParams p) {
-    __shared__ R tej[kSymT], tvj[kSymT], tsj[kSymT], tcj[kSymT];
+    __shared__ R tej[kSymT], tvj[kSymT];
+    __shared__ double tsj[kSymT], tcj[kSymT];
     __shared__ double colp[kSymWaves][kSymT], rowp[kSymWaves][kSymT];
     __shared__ double rsum[Q][kSymT], csum[Q][kSymT];
     const int t = threadIdx.x;
@@ -441,12 +454,13 @@ __global__ void __launch_bounds__(64 * kSymWaves) k_full_sympairs(const FullPara
     const R* eta = static_cast<const R*>(p.eta) + mo;
     const R* ex = static_cast<const R*>(p.ex) + mo;
     const R* v = static_cast<const R*>(p.vin) + mo;
+    const double* s2 = static_cast<const double*>(p.s2);
     const double* rs2 = static_cast<const double*>(p.rs2);
     const double* rfl = static_cast<const double*>(p.rfl) + (long long)m * n;
     const R pl = R(M_PI / p.lx);
     const bool img = !full_deep(p, m);
-    const R b2h = R(2.0 * M_PI * p.href[m] / p.lx);
-    const R sh0 = img ? sinh(b2h) : R(0);
+    const double pld = M_PI / p.lx, h = p.href[m];
+    const double sh0 = img ? sinh(2.0 * pld * h) : 0.0;
     const int wv = t / 64, ln = t & 63;
     if (t < kSymT) {
 #pragma unroll
@@ -461,9 +475,9 @@ __global__ void __launch_bounds__(64 * kSymWaves) k_full_sympairs(const FullPara
         const int i = (I * Q + qa) * kSymT + ln;
         const R etai = eta[i], exi = ex[i];
         const double vi = (double)v[i];
-        R sbi = R(0), cbi = R(1);
+        double sbi = 0.0, cbi = 1.0;
         if (img) {
-            const R b = pl * etai + b2h;
+            const double b = pld * ((double)etai + h);
             sbi = sinh(b);
             cbi = cosh(b);
         }
@@ -472,8 +486,9 @@ __global__ void __launch_bounds__(64 * kSymWaves) k_full_sympairs(const FullPara
             tej[t] = ej;
             tvj[t] = v[(J * Q + qb) * kSymT + t];
             if (img) {
-                tsj[t] = sinh(pl * ej);
-                tcj[t] = cosh(pl * ej);
+                const double a = pld * ((double)ej + h);
+                tsj[t] = sinh(a);
+                tcj[t] = cosh(a);
             }
         }
         __syncthreads();
@@ -489,13 +504,9 @@ __global__ void __launch_bounds__(64 * kSymWaves) k_full_sympairs(const FullPara
             const int j = (J * Q + qb) * kSymT + jl;
             const int d = (j - i + n) & (n - 1);
             const R shb = sinh_series(pl * (tej[jl] - etai));
-            R x = j == i ? exi * exi : shb * shb * R(rs2[d]);
-            if (img) {
-                const R shp = tsj[jl] * cbi + tcj[jl] * sbi;
-                const R y = (shp - sh0) * (shp + sh0) * R(rfl[d]);
-                x = x + y + x * y;
-            }
-            const double kv = (double)(R(-0.5) * pair_log1p(x));
+            const R x = j == i ? exi * exi : shb * shb * R(rs2[d]);
+            const double kv = (double)(img ? pair_single(x, tsj[jl] * cbi + tcj[jl] * sbi, sh0, s2 + d, rfl[d])
+                                           : R(-0.5) * pair_log1p(x));
             acc += kv * (double)tvj[jl];
             if (!own) {
                 // the pair seen from j: K V_i added to column jl's sum over this

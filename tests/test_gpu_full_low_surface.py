@@ -41,3 +41,9 @@ def _check(gpu, nx, h, depth, level):
 def test_over_a_variable_bed(gpu, nx, h, depth_min, level):
     x = np.arange(nx) * 2 * math.pi / nx
     _check(gpu, nx, h, (h - (h - depth_min) * np.exp(np.cos(x - 2.0) - 1.0))[None, :], level)
+
+
+@pytest.mark.parametrize("nx", [64, 256])
+@pytest.mark.parametrize("h,level", [(2.0, -1.5), (5.0, -4.0), (9.0, -8.5), (17.0, -8.0), (17.0, -15.0), (17.0, 10.0)])
+def test_over_a_flat_bed(gpu, nx, h, level):
+    _check(gpu, nx, h, np.full((1, nx), h), level)
