@@ -3247,7 +3247,16 @@ static sbi_status batch_enqueue_part(sbi_batch* b, sbi_state* states, int part, 
                 in.emplace_back(s.phi_s, gr.st_phi + k * gr.field_bytes);
             }
             SBI_TRY(copy_fields(in, gr.field_bytes, gr.s));
-            SBI_TRY(to_spectral(c, gr.st_eta, gr.st_phi, true));
+            if (line_ok(c)) {
+                // by the kernel that steps, as a context of the member's own: the same state bit for bit
+                LineParams lp = line_params(c, tol);
+                lp.load = 2;
+                lp.eta_in = gr.st_eta;
+                lp.phi_in = gr.st_phi;
+                SBI_TRY(line_enqueue(c, lp, 1));
+            } else {
+                SBI_TRY(to_spectral(c, gr.st_eta, gr.st_phi, true));
+            }
         } else if (part == PART_STEPS) {
             double t = states[gr.members[0]].t + toff;
             if (line_ok(c)) {
