@@ -34,6 +34,9 @@
  * doubled, until every solve is decided, so results equal those of the full
  * max_sweeps budget while the launches scale with the sweeps the solves need.
  * A learned seed (SBI_SEED_NET) that fails is reported, not redone.
+ * Groups whose steps run in one kernel (one-dimensional grids of up to 1024
+ * points with a kept band of at most half and seeds from the linear guess)
+ * decide their sweeps on the device: they enqueue none ahead and have no budget.
  *
  * Nothing a batch step computes depends on the state time t (each member's
  * t is only advanced by n*dt): time-dependent forcing -- the wave tank's
@@ -94,8 +97,8 @@ int32_t sbi_batch_groups(const sbi_batch* b, int32_t* members_out, int32_t* spli
 sbi_status sbi_batch_plan(const sbi_batch* b, int32_t g, sbi_plan* out);
 
 /* Current sweep budget of each group (host int32 [n]; max_sweeps when none is
-   set); returns the number of step calls redone with a larger budget since
-   init. */
+   set, as for the one-kernel groups); returns the number of step calls redone
+   with a larger budget since init. */
 int32_t sbi_batch_budgets(const sbi_batch* b, int32_t* budget_out, int32_t n);
 
 sbi_status sbi_batch_destroy(sbi_batch* b);

@@ -3490,8 +3490,9 @@ extern "C" sbi_status sbi_batch_step(sbi_batch* b, sbi_state* states, double dt,
         }
         // next budget: the largest sweep count of this call plus a margin;
         // changed only when it moves by more than the margin (each change is
-        // a new capture)
-        if (iter && n > 0) {
+        // a new capture).  One-kernel groups decide their sweeps on the device
+        // and launch none ahead: no budget, and no inputs saved for one
+        if (iter && n > 0 && !line_ok(c)) {
             const int want = std::min(c->grid.max_sweeps, smax + kBudgetMargin);
             if (c->budget <= 0 || want > c->budget || want + kBudgetMargin < c->budget) c->budget = want;
         }

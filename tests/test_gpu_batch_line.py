@@ -2,7 +2,7 @@
 and statistics equal a context of the member's own bit for bit, over several
 calls, calls longer than a captured part (4 steps) and longer than a context's
 launch (8), captured and not, beside groups that take the separate passes.
-A member that fails ends the call with its
+Such groups have no sweep budget.  A member that fails ends the call with its
 code; the others' states are those of their own runs.
 """
 import math
@@ -57,6 +57,8 @@ def test_members_equal_single_contexts(gpu, mode, accel, precision, graph):
             _, d = s.step(e1[i], p1[i], 0.05, n, tol=tol)
             assert torch.equal(e[i], e1[i]) and torch.equal(p[i], p1[i]), (n, i)
             assert [info[i][k] for k in ("solves", "sweeps_total", "sweeps_max")] == [d[k] for k in ("solves", "sweeps_total", "sweeps_max")]
+    budgets, redos = b.budgets()
+    assert budgets == [200] * len(b.groups()) and redos == 0
 
 
 def test_beside_separate_passes(gpu):
@@ -72,6 +74,8 @@ def test_beside_separate_passes(gpu):
         for i, (m, _, _) in enumerate(mems):
             _solver(m, gpu).step(e1[i], p1[i], 0.05, n, tol=1e-10)
             assert torch.equal(e[i], e1[i]) and torch.equal(p[i], p1[i]), (n, i)
+    budgets, _ = b.budgets()
+    assert budgets[0] == budgets[3] == 200 and max(budgets[1:3]) < 200
 
 
 @pytest.mark.parametrize("graph", [True, False])
