@@ -342,7 +342,9 @@ const char* sbi_status_string(sbi_status s);
  * device time in ms and launch count since the last enable, and returns the
  * number of classes.  In SBI_MIXED contexts the FP32 correction sweeps count
  * as "row_sweep_fp32" and "col_sweep_fp32", the FP64 refinement sweeps as
- * "row_sweep" and "col_sweep".
+ * "row_sweep" and "col_sweep".  A profiled context takes the separate passes
+ * also where others run one-dimensional solves and steps in one kernel (see
+ * the launch plans below): the same results to rounding, other times.
  */
 enum { SBI_PROFILE_OFF = 0, SBI_PROFILE_ALL = 1, SBI_PROFILE_SWEEPS = 2 };
 sbi_status sbi_profile_enable(sbi_ctx* ctx, int32_t enable);
@@ -371,6 +373,11 @@ int32_t sbi_last_stats(const sbi_ctx* ctx, double* out, int32_t n);
  *                sweep in iteration mode, one W solve in SA mode), 0 when the
  *                plan was set rather than measured.
  *   cached       1 when sbi_autotune took the plan from the plan cache.
+ * One-dimensional contexts of up to 1024 points with a kept band of at most half
+ * (dealias <= 1/2), in SA or iteration mode with seeds from the linear guess,
+ * FP64 or FP32, run W solves and fixed steps in one kernel without such choices:
+ * there a plan, and the time sbi_autotune reports, are those of the passes that
+ * adaptive steps, diagnostics and profiled calls take.
  */
 typedef struct sbi_plan {
     int32_t row_variant;
@@ -393,9 +400,9 @@ sbi_status sbi_plan_set(sbi_ctx* ctx, const sbi_plan* plan);
 
 /*
  * Autotuner: times every built row variant and rows per workgroup from the
- * launch bound down to a quarter of it, each on the context's own kernels and workspace (5 units
- * after 2 of warm-up, best of two rounds, HIP events on the context's
- * stream), and keeps the fastest.  The plan cache, a process-wide table keyed
+ * launch bound down to a quarter of it, each on the context's own kernels and
+ * workspace (5 units after 2 of warm-up, best of two rounds, HIP events on the
+ * context's stream), and keeps the fastest.  The plan cache, a process-wide table keyed
  * by device (name and architecture), grid size, batch, precision, mode,
  * acceleration, order and whether the bed varies, is consulted first: a hit
  * is applied without timing unless flags has SBI_TUNE_FORCE, and every search

@@ -3026,12 +3026,14 @@ extern "C" sbi_status sbi_tune_cache_save(const char* path, int32_t* count) {
 // timed with every group running (one unit of each on its own stream, forked
 // from and joined to the batch's stream), group by group (coordinate
 // descent from the default plans).  A single group is the context's own
-// tuning.  The plan cache keys an ensemble's plans by all its groups' keys.
+// tuning.  Groups whose steps run in one kernel have nothing that a plan changes
+// and keep the default.  The plan cache keys an ensemble's plans by all its groups' keys.
 static sbi_status ensemble_time(sbi_batch* b, hipEvent_t e0, hipEvent_t e1, float* us) {
     constexpr int kRounds = 2, kReps = 3;
     auto unit = [&]() -> sbi_status {
         SBI_HIP(hipEventRecord(b->fork, b->cap));
         for (auto& gr : b->g) {
+            if (line_ok(gr.c)) continue;
             SBI_HIP(hipStreamWaitEvent(gr.s, b->fork, 0));
             SBI_TRY(hip_ok(launch_ctl_reset(gr.c->ctl, gr.c->batch, gr.c->grid.max_sweeps + 2, gr.s)));
             SBI_TRY(tune_unit(gr.c));
@@ -3056,6 +3058,7 @@ static sbi_status ensemble_time(sbi_batch* b, hipEvent_t e0, hipEvent_t e1, floa
 }
 
 static sbi_status batch_autotune(sbi_batch* b) {
+    if (std::all_of(b->g.begin(), b->g.end(), [](const sbi_batch::Group& gr) { return line_ok(gr.c); })) return SBI_OK;
     if (b->g.size() == 1) return autotune(b->g[0].c, 0, nullptr);
     std::string ens = "ens";
     std::vector<std::string> keys;
@@ -3093,7 +3096,7 @@ static sbi_status batch_autotune(sbi_batch* b) {
     if (st == SBI_OK) st = ensemble_time(b, e0, e1, &cur);
     for (size_t i = 0; i < b->g.size() && st == SBI_OK; ++i) {
         sbi_ctx* c = b->g[i].c;
-        if (c->grid.mode == SBI_MODE_FULL) continue;
+        if (c->grid.mode == SBI_MODE_FULL || line_ok(c)) continue;
         for (const sbi_plan& cand : plan_candidates(c)) {
             st = plan_apply(c, cand);
             float us = 0.f;

@@ -101,3 +101,13 @@ def test_failing_member(gpu, mode, bad, graph):
     # the next call of the same ensemble with every member sound again
     e[1], p[1] = e[0].clone(), p[0].clone()
     assert b.step(e, p, 0.05, 2, tol=1e-10)[0] == 0
+
+
+def test_autotune_leaves_one_kernel_groups_alone(gpu):
+    from paper_2310_19840_amd import Batch
+    o = dict(mode="iter", accel="anderson")
+    line = [_member(64, 0, **o)[0], _member(256, 1, **o)[0]]
+    for mems, alone in ((line[:1], True), (line, True), (line + [_member(2048, 2, **o)[0]], False)):
+        plans = Batch(mems, device=gpu, autotune=True).plans()
+        for q in plans[:len(plans) if alone else 2]:
+            assert (q["row_variant"], q["row_rows"], q["col_split"]) == (0, 0, 0)
