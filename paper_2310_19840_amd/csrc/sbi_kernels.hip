@@ -689,13 +689,18 @@ __global__ void __launch_bounds__(row_threads<NX>()) k_row_feat(const RowFeatPar
 // 512 x 512 SA order 7.6 (21.7); FP64 128 x 64 sweep 14.6 (31); a single product
 // without inverse at 1024 rows 6.9 (11.8).
 //
-// S ("classes"): columns of more than 512 rows are split by decimation in
-// frequency into S = ny / 512 transforms of 512 points, one wavefront each:
-// wave h forms u_h[n] = sum_p x[n + 512 p] W_S^(h p) W^(h n), W = exp(-2 pi i /
-// ny), whose transform holds the modes S k + h.  All S waves read the whole
-// column (the repeated reads are served by the cache).  The inverse runs the
-// other way: each wave inverts its class of modes, multiplies by W^(-h n), and
-// the S waves form x[n + 512 p] = sum_h W_S^(-h p) e_h[n] through LDS.
+// S ("classes"): columns of more than 512 rows are split by decimation in frequency
+// into S = ny / 512 transforms of 512 points, one wavefront each: wave h forms u_h[n]
+// = sum_p x[n + 512 p] W_S^(h p) W^(h n), W = exp(-2 pi i / ny), whose transform holds
+// the modes S k + h. Both waves of S = 2 read the whole column (the second reads are
+// served by the cache). Four would read it four times and hold no next round's values:
+// there wave q loads the positions n of its quarter of the 512, forms u_0 .. u_3 from
+// them and leaves each in its class's area, so that a value is read once and requested
+// a round ahead (16 members of 16 x 2048, FP64: a sweep's pass 46 us, 103 with four
+// reads; FP32 28 against 61). The inverse runs the other way: each wave inverts its
+// class of modes, multiplies by W^(-h n), and the S waves form x[n + 512 p] = sum_h
+// W_S^(-h p) e_h[n] through LDS (four classes: wave q those of its quarter, for every
+// p).
 // ---------------------------------------------------------------------------
 template <typename R, int NY> struct ColShape {
     using V = typename cplx_of<R>::type;
@@ -954,14 +959,21 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
     const int rounds = (njob + W - 1) / W;
     const int per = W / S;                                     // products per round
     // column of job jb (product jb / S): the raw values of its thread
-    // (not for the largest columns in FP64: their registers hold a thread's several modes)
-    constexpr bool AHEAD = S == 1 || (S == 2 && IT == 1) || (S == 2 && sizeof(R) == 4);
-    V raw[AHEAD ? S : 1][E];
+    // (not for columns of several modes an owner in FP64: their registers hold those)
+    constexpr bool SPREAD = S > 2;   // each value read by one wavefront of the column, see above
+    static_assert(!SPREAD || (S == 4 && P == 64 && E % S == 0), "the radix-4 step of a spread column");
+    constexpr bool AHEAD = S == 1 || SPREAD || IT == 1 || sizeof(R) == 4;
+    constexpr int RAW = AHEAD ? (SPREAD ? 1 : S) : 1;
+    V raw[RAW][E];
     auto column = [&](int jb) __attribute__((always_inline)) {
         return static_cast<const V*>(jb < W ? p.src[sub.p0 + jb / S].ptr : col_uni(sp.src[sub.p0 + jb / S].ptr)) + mem * g.s_half + (long long)(x0 + c) * g.ldh + j;
     };
     auto request = [&](int jb) __attribute__((always_inline)) {
-        if constexpr (AHEAD) {
+        if constexpr (SPREAD) {
+            const V* H = column(jb) + h * (NH / S);
+#pragma unroll
+            for (int q = 0; q < E; ++q) raw[0][q] = H[(q / S) * P + (q % S) * NH];
+        } else if constexpr (AHEAD) {
             const V* H = column(jb);
 #pragma unroll
             for (int s = 0; s < S; ++s)
@@ -973,7 +985,7 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
     // compact inputs an owner of one mode loads ahead of their use, into the
     // columns' registers: in a pass without products before everything else
     constexpr bool EARLY = IT == 1 && AHEAD;
-    constexpr int kPre = !EARLY ? 0 : (S * E < 6 ? S * E : 6);
+    constexpr int kPre = !EARLY ? 0 : (RAW * E < 6 ? RAW * E : 6);
     const int nc = sub.c1 - sub.c0;
     auto preload = [&](long long o, bool on) __attribute__((always_inline)) {
 #pragma unroll
@@ -983,9 +995,14 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
     Twid<V, NH, E> twc;
     twc.load(twY, j, S);                                       // the NH-point twiddles: every S-th entry
     V wn = cx<V>(R(1), R(0)), wq = wn;                         // W^(h j), W^(h P)
-    if constexpr (S > 1) {
+    if constexpr (S == 2) {
         wn = twY[h * j];
         wq = twY[h * P];
+    }
+    V ws[SPREAD ? E / S : 1];                                  // W^n of the thread's positions of the radix-4 step
+    if constexpr (SPREAD) {
+#pragma unroll
+        for (int r = 0; r < E / S; ++r) ws[r] = twY[h * (NH / S) + j + r * P];
     }
     // the owner's mode(s): entry i = t + it T of the workgroup's compact modes
     const double href = g.href[mem];
@@ -1028,11 +1045,34 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
     lds_sync();  // the staged parameters: every wavefront's part of them is written
     for (int rd = 0; rd < rounds; ++rd) {
         const int jb = rd * W + wv;
+        if constexpr (SPREAD) {
+            if (jb < njob) {
+                V* const cls = areas + (wv - h) * AREA + h * (NH / S) + j;
+#pragma unroll
+                for (int r = 0; r < E / S; ++r) {
+                    const V* x = &raw[0][r * S];
+                    const V a = cadd(x[0], x[2]), b = csub(x[0], x[2]), e = cadd(x[1], x[3]);
+                    const V d = mul_mi<false>(csub(x[1], x[3]));
+                    V w = ws[r];
+                    asm volatile("" : "+v"(w.x), "+v"(w.y));  // powers formed here, not held across rounds
+                    const V w2 = cmul(w, w);
+                    cls[0 * AREA + r * P] = cadd(a, e);
+                    cls[1 * AREA + r * P] = cmul(cadd(b, d), w);
+                    cls[2 * AREA + r * P] = cmul(csub(a, e), w2);
+                    cls[3 * AREA + r * P] = cmul(csub(b, d), cmul(w2, w));
+                }
+            }
+            lds_sync();  // every part of the column's classes is written
+        }
         if (jb < njob) {
             V v[E];
             if constexpr (S == 1) {
 #pragma unroll
                 for (int q = 0; q < E; ++q) v[q] = raw[0][q];
+            } else if constexpr (SPREAD) {
+#pragma unroll
+                for (int q = 0; q < E; ++q) v[q] = area[j + q * P];
+                wave_lds_sync();
             } else {
                 if constexpr (AHEAD) {
                     if (h == 0) {
@@ -1046,16 +1086,10 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
                     const V* H = column(jb);
 #pragma unroll
                     for (int q = 0; q < E; ++q) v[q] = H[q * P];
-#pragma unroll 1
-                    for (int s = 1; s < S; ++s) {
-                        const int rot = S == 2 ? 2 * (h * s) : (h * s) & 3;  // times (-i)^(...)
 #pragma unroll
-                        for (int q = 0; q < E; ++q) {
-                            const V x = H[q * P + s * NH];
-                            const V y = rot == 0 ? x : (rot == 1 ? mul_mi<false>(x)
-                                                                 : (rot == 2 ? cx<V>(-x.x, -x.y) : mul_i(x)));
-                            v[q] = cadd(v[q], y);
-                        }
+                    for (int q = 0; q < E; ++q) {
+                        const V x = H[q * P + NH];
+                        v[q] = h == 0 ? cadd(v[q], x) : csub(v[q], x);
                     }
                 }
                 if (h > 0) {
@@ -1188,7 +1222,7 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
             wave_lds_sync();
             fft<V, NH, true, 1, E, true>(v, area + c * REG, 0, j, twc);
             if constexpr (S > 1) {
-                if (h > 0) {
+                if (!SPREAD && h > 0) {
                     V w = cconj(wn);
                     asm volatile("" : "+v"(w.x), "+v"(w.y));
                     const V wc = cconj(wq);
@@ -1203,28 +1237,40 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
                 for (int q = 0; q < E; ++q) area[j + q * P] = v[q];
             }
         }
-        if constexpr (S > 1) {
+        V* const G = o < on ? static_cast<V*>(col_uni(sp.inv[sub.i0 + o0 + o])) + mem * g.s_half + (long long)(x0 + c) * g.ldh : nullptr;
+        if constexpr (SPREAD) {
+            lds_sync();
+            if (o < on) {
+                const V* const e = areas + o * S * AREA + h * (NH / S) + j;
+                V* const x = G + h * (NH / S) + j;
+#pragma unroll
+                for (int r = 0; r < E / S; ++r) {
+                    V w = cconj(ws[r]);
+                    asm volatile("" : "+v"(w.x), "+v"(w.y));
+                    const V w2 = cmul(w, w);
+                    const V e0 = e[r * P], e1 = cmul(e[AREA + r * P], w), e2 = cmul(e[2 * AREA + r * P], w2);
+                    const V e3 = cmul(e[3 * AREA + r * P], cmul(w2, w));
+                    const V a = cadd(e0, e2), b = csub(e0, e2), d = cadd(e1, e3), f = mul_i(csub(e1, e3));
+                    x[r * P] = cadd(a, d);
+                    x[NH + r * P] = cadd(b, f);
+                    x[2 * NH + r * P] = csub(a, d);
+                    x[3 * NH + r * P] = csub(b, f);
+                }
+            }
+        } else if constexpr (S > 1) {
             lds_sync();
             if (o < on) {
                 const V* const e = areas + o * S * AREA;
 #pragma unroll
                 for (int q = 0; q < E; ++q) {
-                    const int n = j + q * P;
-                    V x = e[n];
-#pragma unroll
-                    for (int s = 1; s < S; ++s) {
-                        const int rot = S == 2 ? 2 * ((h * s) & 1) : (h * s) & 3;  // times i^(...)
-                        const V y = e[s * AREA + n];
-                        x = cadd(x, rot == 0 ? y : (rot == 1 ? mul_i(y) : (rot == 2 ? cx<V>(-y.x, -y.y) : mul_mi<false>(y))));
-                    }
-                    v[q] = x;
+                    const V a = e[j + q * P], b = e[AREA + j + q * P];
+                    v[q] = h == 0 ? cadd(a, b) : csub(a, b);
                 }
             }
         }
-        if (o < on) {
-            V* G = static_cast<V*>(col_uni(sp.inv[sub.i0 + o0 + o])) + mem * g.s_half + (long long)(x0 + c) * g.ldh + h * NH + j;
+        if (!SPREAD && o < on) {
 #pragma unroll
-            for (int q = 0; q < E; ++q) G[q * P] = v[q];
+            for (int q = 0; q < E; ++q) G[h * NH + j + q * P] = v[q];
         }
     }
     // compact outputs: a mode's inputs were all read by its owner, so an output
@@ -1610,6 +1656,11 @@ SBI_ROW_LAUNCH(k_row_nphi_tank, RowNphiParams)
 SBI_ROW_LAUNCH(k_row_blend, RowBlendParams)
 SBI_ROW_LAUNCH(k_row_feat, RowFeatParams)
 
+// kept modes of an owner thread: one where twelve wavefronts hold a column's, else two or three
+template <typename R, int NY> static int col_modes(const GridDev& g) {
+    using CS = ColShape<R, NY>;
+    return (CS::CW * g.Ky + 64 * CS::WMAX - 1) / (64 * CS::WMAX);
+}
 // Wavefronts of a column-pass workgroup: one per column transform of a round,
 // as few as the same number of rounds takes, and enough to own every kept
 // mode.  Few workgroups (up to one per CU) take up to twelve, so that a
@@ -1631,7 +1682,7 @@ template <typename R, int NY> static int col_waves(const ColParams& p, int batch
     const int rounds = (jobs + cap - 1) / cap;
     int w = rounds > 0 ? (jobs + rounds - 1) / rounds : 1;
     w = std::max(w, std::min(ni * CS::S, cap));
-    const int it = CS::CW * p.g.Ky <= 64 * CS::WMAX ? 1 : CS::ITMAX;
+    const int it = col_modes<R, NY>(p.g);
     w = std::max(w, (CS::CW * p.g.Ky + 64 * it - 1) / (64 * it));
     w = (w + CS::S - 1) / CS::S * CS::S;
     return std::min(w, CS::WMAX);
@@ -1659,8 +1710,11 @@ static hipError_t col_go(const ColParams& p, int batch, const Twiddles& tw, hipS
         using CS = ColShape<R, NY>;
         if (p.g.col_C != CS::CW) return hipErrorInvalidValue;  // the layout was made for another tile
         const int W = col_waves<R, NY>(p, batch);
+        const int it = col_modes<R, NY>(p.g);
+        if constexpr (CS::ITMAX > 2)
+            if (it > 2) return col_it<R, NY, NACC, CS::ITMAX>(p, W, batch, tw, s);
         if constexpr (CS::ITMAX > 1)
-            if (CS::CW * p.g.Ky > 64 * CS::WMAX) return col_it<R, NY, NACC, CS::ITMAX>(p, W, batch, tw, s);
+            if (it > 1) return col_it<R, NY, NACC, 2>(p, W, batch, tw, s);
         return col_it<R, NY, NACC, 1>(p, W, batch, tw, s);
     }
 }
