@@ -385,67 +385,60 @@ __device__ __forceinline__ void row_sweep_body(const RowSweepParams& p, const ty
     if (ctl->done) return;  // block-uniform: the member's solve is decided
     ROW_PROLOGUE_T(RowVar<R, NX, VAR>)
     // product family and chunk of this workgroup; with several chunks the
-    // residual test has a workgroup row of its own after them
+    // residual test has a workgroup row of its own after them.  The iterate and the
+    // products come from one piece of code however the chains are cut: copies of it may
+    // round apart, and a member's results must not depend on how many others there are
     const int fam = blockIdx.y / p.nch, ch = blockIdx.y % p.nch;
     const bool rest = fam == p.nfam;
-    if (rest || (fam == 0 && p.nch == 1)) {
-        V vv[E];
-        const bool products = p.products && !rest;
-        // the iterate: for its products, and for the residual's denominator
-        // of the relaxed update (a residual-only Anderson pass needs neither)
-        if (!AA || products)
-            RW::inverse(vv, static_cast<const V*>(p.gV) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
-        if (p.residual) {
-            V dd[E];
-            RW::inverse(dd, static_cast<const V*>(p.gD) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
-            const double c = 1.0 - ctl->omega;
-            unsigned long long nu = 0ull, de = 0ull;
+    const bool test = p.residual && (rest || (fam == 0 && p.nch == 1)), products = p.products && !rest;
+    V v[E];
+    // the iterate: for its products, and for the residual's denominator
+    // of the relaxed update (a residual-only Anderson pass needs neither)
+    if (products || (test && !AA))
+        RW::inverse(v, static_cast<const V*>(fam == 0 || rest ? p.gV : (fam == 1 ? p.gbx : p.gby)) + hb, nullptr, R(0), rc,
+                    lds_all, twN, twX, iscale);
+    if (test) {
+        V dd[E];
+        RW::inverse(dd, static_cast<const V*>(p.gD) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
+        const double c = 1.0 - ctl->omega;
+        unsigned long long nu = 0ull, de = 0ull;
+        if (ri.valid) {
+#pragma unroll
+            for (int q = 0; q < E; ++q) {
+                const double d0 = (double)dd[q].x, d1 = (double)dd[q].y;
+                unsigned long long a = abs_bits(d0), b = abs_bits(d1);
+                nu = a > nu ? a : nu;
+                nu = b > nu ? b : nu;
+                if constexpr (!AA) {
+                    // denominator T(V_(n-1)) = V_n + (1 - omega) D from the relaxed update
+                    a = abs_bits((double)v[q].x + c * d0);
+                    b = abs_bits((double)v[q].y + c * d1);
+                    de = a > de ? a : de;
+                    de = b > de ? b : de;
+                }
+            }
+        }
+        if constexpr (AA) {
+            // denominator T(V_(n-1)) given as its own half form (in D's registers)
+            RW::inverse(dd, static_cast<const V*>(p.gT) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
             if (ri.valid) {
 #pragma unroll
                 for (int q = 0; q < E; ++q) {
-                    const double d0 = (double)dd[q].x, d1 = (double)dd[q].y;
-                    unsigned long long a = abs_bits(d0), b = abs_bits(d1);
-                    nu = a > nu ? a : nu;
-                    nu = b > nu ? b : nu;
-                    if constexpr (!AA) {
-                        // denominator T(V_(n-1)) = V_n + (1 - omega) D from the relaxed update
-                        a = abs_bits((double)vv[q].x + c * d0);
-                        b = abs_bits((double)vv[q].y + c * d1);
-                        de = a > de ? a : de;
-                        de = b > de ? b : de;
-                    }
+                    const unsigned long long a = abs_bits((double)dd[q].x), b = abs_bits((double)dd[q].y);
+                    de = a > de ? a : de;
+                    de = b > de ? b : de;
                 }
-            }
-            if constexpr (AA) {
-                // denominator T(V_(n-1)) given as its own half form (in D's registers)
-                RW::inverse(dd, static_cast<const V*>(p.gT) + hb, nullptr, R(0), rc, lds_all, twN, twX, iscale);
-                if (ri.valid) {
-#pragma unroll
-                    for (int q = 0; q < E; ++q) {
-                        const unsigned long long a = abs_bits((double)dd[q].x), b = abs_bits((double)dd[q].y);
-                        de = a > de ? a : de;
-                        de = b > de ? b : de;
-                    }
-                }
-            }
-            block_reduce2_max_u64(nu, de);
-            if (threadIdx.x == 0) {
-                atomicMax(&ctl->slots->num[p.slot], nu);
-                atomicMax(&ctl->slots->den[p.slot], de);
             }
         }
-        if (!products) return;
-        // eta^j V as a running product
-        V ev[E];
-        RW::load(ev, static_cast<const R*>(p.eta) + po, ri.j, ri.valid);
-        row_chain<RW, V, E>(vv, ev, 0, p.J, p.h, hb, rc, lds_all, twN, twX);
-        return;
+        block_reduce2_max_u64(nu, de);
+        if (threadIdx.x == 0) {
+            atomicMax(&ctl->slots->num[p.slot], nu);
+            atomicMax(&ctl->slots->den[p.slot], de);
+        }
     }
+    if (!products) return;
     // eta^j V, delta^j d_x phi_b, delta^j d_y phi_b
-    if (!p.products) return;
-    V v[E], w[E];
-    RW::inverse(v, static_cast<const V*>(fam == 0 ? p.gV : (fam == 1 ? p.gbx : p.gby)) + hb, nullptr, R(0), rc, lds_all,
-                twN, twX, iscale);
+    V w[E];
     RW::load(w, static_cast<const R*>(fam == 0 ? p.eta : p.delta) + po, ri.j, ri.valid);
     row_chain<RW, V, E>(v, w, ch * p.pc, min(p.J, (ch + 1) * p.pc), p.h + fam * p.J, hb, rc, lds_all, twN, twX);
 }
