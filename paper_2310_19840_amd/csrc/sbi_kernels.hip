@@ -997,7 +997,10 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
 #pragma unroll
         for (int r = 0; r < E / S; ++r) ws[r] = twY[h * (NH / S) + j + r * P];
     }
-    // the owner's mode(s): entry i = t + it T of the workgroup's compact modes
+    // the owner's mode(s): entry i = t + it owners of the workgroup's compact modes.  The owners'
+    // number follows from the band alone, not from the wavefronts of the launch, which follow from
+    // the member count too: a member's inner products are to round alike among many and alone
+    const int owners = IT == 1 ? 0 : (CW * g.Ky + 64 * IT - 1) / (64 * IT) * 64;
     const double href = g.href[mem];
     ColGeo<R> geo[IT];
     int slot[IT];          // element of the areas holding the mode: class area, column, transform index (0: no mode,
@@ -1005,9 +1008,9 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
     int co[IT];            // compact offset from the workgroup's first column, -1: no mode
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const int i = t + it * (int)blockDim.x;
+        const int i = t + it * owners;
         const int c2 = i / g.Ky, r = i - c2 * g.Ky;
-        const bool on = c2 < CW && x0 + c2 < g.Kx;
+        const bool on = (IT == 1 || t < owners) && c2 < CW && x0 + c2 < g.Kx;
         const int n = r <= g.My ? r : r + NY - g.Ky;
         co[it] = on ? i : -1;
         slot[it] = on ? (n % S) * AREA + c2 * REG + n / S : 0;

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nx,ny,dealias,counts", [
-    (16, 2048, 0.5, (5,)), (16, 2048, 0.9, (40,)), (32, 1024, 0.5, (40,)),
+    (16, 2048, 0.5, (5, 150)), (16, 2048, 0.9, (40,)), (16, 1024, 0.9, (70, 200)), (32, 1024, 0.5, (40,)),
     (32, 64, 0.5, (3, 300, 1500)), (64, 16, 0.5, (700,)), (16, 512, 0.7, (130,)),
     (2048, 1, 0.5, (5, 60, 400)), (256, 1, 0.8, (3, 150, 1200))])
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
