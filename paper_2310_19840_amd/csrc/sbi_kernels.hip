@@ -1661,10 +1661,12 @@ template <typename R, int NY> static int col_modes(const GridDev& g) {
 // as few as the same number of rounds takes, and enough to own every kept
 // mode.  Few workgroups (up to one per CU) take up to twelve, so that a
 // workgroup's chain is short; more of them hide each other's barriers, and
-// smaller workgroups then pack the CU better.  Measured with at most 4 / 8 / 12
-// wavefronts: 96 ragged FP32 members (6656 workgroups a pass) 7.9 / 8.8 / 9.3 ms
-// per step; two 1024 x 1024 FP64 members (512) 5.9 / 5.7 / 6.0; one 512 x 512
-// member (128) 0.67 / 0.65 / 0.65.
+// smaller workgroups then pack the CU better.  Measured, us a sweep's pass with at
+// most 4 / 8 / 12 wavefronts: 128 x 128 FP64, 48 members (384 workgroups) 26 / 34 / 38,
+// 64 members (512) 27 / 36 / 41, 96 (768) 34 / 52 / 59; FP32 64 members 16.5 / 18.1 /
+// 25; 64 x 512 FP64, 64 members (1024) 46 / 65 / 76 and 57 for the pass before this
+// one.  One 512 x 512 member (128) 0.67 / 0.65 / 0.65 ms per step.  The usual half band
+// of 1024 rows takes eight at any rate, for its owners.
 template <typename R, int NY> static int col_waves(const ColParams& p, int batch) {
     using CS = ColShape<R, NY>;
     int np = 0, ni = 0;
@@ -1673,7 +1675,7 @@ template <typename R, int NY> static int col_waves(const ColParams& p, int batch
         ni = std::max(ni, (int)(p.sub[s].i1 - p.sub[s].i0));
     }
     const long long groups = (long long)(p.g.Kxp / CS::CW) * p.nsub * batch;
-    const int cap = groups <= 256 ? CS::WMAX : (groups <= 1024 ? 8 : 4);
+    const int cap = groups <= 256 ? CS::WMAX : 4;
     const int jobs = np * CS::S;
     const int rounds = (jobs + cap - 1) / cap;
     int w = rounds > 0 ? (jobs + rounds - 1) / rounds : 1;
