@@ -138,6 +138,7 @@ struct ColParams {
     GridDev g;
     int nacc, nsub;
     int hyper;                         // some term uses tanh(kh) or sech(kh)
+    int lanes;                         // one-dimensional grids: partial sums of the sources (set by the launcher)
     // > 0: the products are those of a sweep of the iteration, order by order: eta^j V, then with
     // nfam 2 or 3 delta^j d_x phi_b, delta^j d_y phi_b; j = 1, 2, ..  Their terms, which the
     // sources give as well, follow from j and the family alone.

@@ -1298,14 +1298,16 @@ __global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColP
 // Column pass of one-dimensional grids: a "column" is one mode, so a thread
 // reads its mode of a source itself.  Bound by the latency of one chain (control
 // header, parameters, loads, sums, store); the sources are shared by up to
-// eight wavefronts whose partial sums meet in LDS.
-constexpr int kCol1Waves = 8;
+// eight lanes whose partial sums meet in LDS, a lane taking every lanes-th
+// source.  A wavefront serves one lane or several in turn (col1_waves): the
+// lanes, and with them the rounding, do not depend on the number of members.
+constexpr int kCol1Lanes = 8;
 template <typename R, int NACC>
-__global__ void __launch_bounds__(64 * kCol1Waves) k_col1(const ColParams p) {
+__global__ void __launch_bounds__(64 * kCol1Lanes) k_col1(const ColParams p) {
     using V = typename cplx_of<R>::type;
     __shared__ double s_aa[(16 + 1) * kAASlots];
     __shared__ ColParams sp;
-    __shared__ V sums[kCol1Waves - 1][NACC][64];
+    __shared__ V sums[kCol1Lanes - 1][NACC][64];
     const int t = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
     const int mem = blockIdx.z;
@@ -1329,24 +1331,27 @@ __global__ void __launch_bounds__(64 * kCol1Waves) k_col1(const ColParams p) {
     if (p.aa_partial) aa_block_weights(p, ctl, mem, blockIdx.x == 0, head, s_aa, s_aa + 16 * kAASlots);
     lds_sync();
     V acc[NACC];
+    const int np = sub.p1 - sub.p0, ns = np + sub.c1 - sub.c0, lanes = p.lanes;
+    // the last lane first, so that the first wavefront ends with lane 0 in its sums
+    for (int lane = wv + (lanes - 1 - wv) / W * W; lane >= 0; lane -= W) {
 #pragma unroll
-    for (int a = 0; a < NACC; ++a) acc[a] = zero;
-    const int np = sub.p1 - sub.p0, ns = np + sub.c1 - sub.c0;
+        for (int a = 0; a < NACC; ++a) acc[a] = zero;
 #pragma unroll 2
-    for (int s = wv; s < ns; s += W) {
-        const bool prod = s < np;
-        const ColSrc src = col_src(&sp.src[prod ? sub.p0 + s : kMaxProd + sub.c0 + s - np]);
-        V val = on ? static_cast<const V*>(col_uni(src.ptr))[prod ? hb : cb] : zero;
-        if (src.widx >= 0) val = cscale(val, R(s_aa[16 * kAASlots + src.widx]));
-        col_add<R, V, NACC>(src, val, acc, geo);
-    }
-    if (W > 1) {
-        if (wv > 0)
+        for (int s = lane; s < ns; s += lanes) {
+            const bool prod = s < np;
+            const ColSrc src = col_src(&sp.src[prod ? sub.p0 + s : kMaxProd + sub.c0 + s - np]);
+            V val = on ? static_cast<const V*>(col_uni(src.ptr))[prod ? hb : cb] : zero;
+            if (src.widx >= 0) val = cscale(val, R(s_aa[16 * kAASlots + src.widx]));
+            col_add<R, V, NACC>(src, val, acc, geo);
+        }
+        if (lane > 0)
 #pragma unroll
-            for (int a = 0; a < NACC; ++a) sums[wv - 1][a][t] = acc[a];
+            for (int a = 0; a < NACC; ++a) sums[lane - 1][a][t] = acc[a];
+    }
+    if (lanes > 1) {
         lds_sync();
         if (wv == 0)
-            for (int w = 1; w < W; ++w)
+            for (int w = 1; w < lanes; ++w)
 #pragma unroll
                 for (int a = 0; a < NACC; ++a) acc[a] = cadd(acc[a], sums[w - 1][a][t]);
     }
@@ -1694,6 +1699,14 @@ static hipError_t col_it(const ColParams& p, int W, int batch, const Twiddles& t
                        (size_t)W * CS::AREA * sizeof(V), s, p, (const V*)tw.ty);
     return hipGetLastError();
 }
+// Wavefronts of a one-dimensional column pass's workgroup, for so many workgroups:
+// all lanes side by side while the chip has room, fewer where more wavefronts would
+// only wait for each other.  Measured, us a sweep's pass with 8 / 4 / 2 wavefronts:
+// 16 workgroups (4096 points) 7.5 / 7.9 / 9.0; 768 (512 points, 256 members) 14.2 /
+// 10.1 / 10.4; 8192 (8192 points, 256 members) 96 / 53 / 44.
+static int col1_waves(int lanes, long long groups) {
+    return (int)std::min<long long>(lanes, std::max<long long>(2, 3072 / groups));
+}
 template <typename R, int NY, int NACC>
 static hipError_t col_go(const ColParams& p, int batch, const Twiddles& tw, hipStream_t s) {
     if constexpr (NY == 1) {
@@ -1701,8 +1714,10 @@ static hipError_t col_go(const ColParams& p, int batch, const Twiddles& tw, hipS
         int ns = 0;
         for (int i = 0; i < p.nsub; ++i)
             ns = std::max(ns, p.sub[i].p1 - p.sub[i].p0 + p.sub[i].c1 - p.sub[i].c0);
-        const int W = std::min(kCol1Waves, std::max(1, (ns + 1) / 2));
-        hipLaunchKernelGGL((k_col1<R, NACC>), dim3(p.g.Kxp / 64, p.nsub, batch), dim3(64 * W), 0, s, p);
+        ColParams q = p;
+        q.lanes = std::min(kCol1Lanes, std::max(1, (ns + 1) / 2));
+        const int W = col1_waves(q.lanes, (long long)(p.g.Kxp / 64) * p.nsub * batch);
+        hipLaunchKernelGGL((k_col1<R, NACC>), dim3(p.g.Kxp / 64, p.nsub, batch), dim3(64 * W), 0, s, q);
         return hipGetLastError();
     } else {
         using CS = ColShape<R, NY>;
