@@ -953,16 +953,19 @@ static sbi_status stage_state_pass(sbi_ctx* c, bool need_eta, bool allow_prev = 
 // products); with fewer than two workgroups per CU the chip idles along it, so
 // the chains are cut, each piece repeating the inverse, until 512 workgroups
 // run or each holds one product.  Measured, uncut -> cut: 128 x 64 FP64
-// iteration 4160 -> 2870 us a step, 512 x 512 FP32 SA 642 -> 580, 1D 256-point
-// solve 1008 -> 770.  From 512 on the repeated transforms cost more: 1024 x 1024
-// (768 workgroups) 7.0 ms uncut, 7.5 in halves, 8.5 in single products.
+// iteration 4160 -> 2870 us a step, 512 x 512 FP32 SA 642 -> 580.  From 512 on
+// the repeated transforms cost more: 1024 x 1024 (768 workgroups) 7.0 ms uncut,
+// 7.5 in halves, 8.5 in single products.  A row of a one-dimensional grid of up to
+// 1024 points is a workgroup of one wavefront, a quarter of the others', and takes
+// four times as many: 64 points, band 0.8, FP32, a step of 256 members by SA 678 us
+// with 512 and 584 with 2048, iterated 1623 and 1261; of 512 members 2081 and 1441.
 static int row_chunk(const sbi_ctx* c, int nfam, int J) {
-    constexpr long long kWant = 512;
+    const long long want = c->grid.ny == 1 && c->grid.nx <= 1024 ? 2048 : 512;
     const int cap = std::min(row_rows_cap(c->fp64, c->grid.nx, c->gd.row_var), c->grid.ny);
     const int rpw = c->gd.row_rpw > 0 ? std::min(c->gd.row_rpw, cap) : cap;
     const long long groups = (long long)((c->grid.ny + rpw - 1) / rpw) * nfam * c->batch;
     int pc = std::max(J, 1);
-    for (int parts = 2; parts <= J && groups * ((J + pc - 1) / pc) < kWant; ++parts) pc = (J + parts - 1) / parts;
+    for (int parts = 2; parts <= J && groups * ((J + pc - 1) / pc) < want; ++parts) pc = (J + parts - 1) / parts;
     return pc;
 }
 
