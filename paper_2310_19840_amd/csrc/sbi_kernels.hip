@@ -551,8 +551,11 @@ __device__ __forceinline__ void row_nphi_body(const RowNphiParams& p, const type
     RW::forward(q, static_cast<V*>(p.h) + hb, rc, lds_all, twN, twX);
 }
 
+// (two wavefronts a SIMD: left to itself the compiler takes registers for one in FP64
+// at 256 and 2048 points, for the reads in batches; 2048 x 64, 16 members 51 -> 37 us,
+// 256 x 256, 32 members 38 -> 28)
 template <typename R, int NX>
-__global__ void __launch_bounds__(row_threads<NX>()) k_row_nphi(const RowNphiParams p, const typename cplx_of<R>::type* twN_tab,
+__global__ void __launch_bounds__(row_threads<NX>(), 2) k_row_nphi(const RowNphiParams p, const typename cplx_of<R>::type* twN_tab,
                            const typename cplx_of<R>::type* twX_tab) {
     row_nphi_body<R, NX, false>(p, twN_tab, twX_tab);
 }
