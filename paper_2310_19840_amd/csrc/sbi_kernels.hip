@@ -69,8 +69,9 @@ template <typename R, int NX, int EM = 8, bool TWC = false> struct Row {
     // clamped to the last one: a loop that tests each mode before its read waits out
     // the latency once a mode.  128 x 64, FP64: sweeps 9.8 -> 8.3 us, N_phi 16.5 -> 13.8;
     // 512 x 512, FP32: products of an order 8.0 -> 7.3 us, N_phi 16.9 -> 13.5; 1024 x 1024,
-    // FP32: sweeps 27.1 -> 25.3 us (in FP64 unchanged at 35.5).
-    static constexpr int kBatch = 4;
+    // FP32: sweeps 27.1 -> 25.3 us (in FP64 unchanged at 35.5).  Rows of 8192 points in FP64 read
+    // two at a time: with four the mixed sweeps spill (8192 x 16, 16 members 159 us, with two 138).
+    static constexpr int kBatch = sizeof(R) == 8 && NX >= 8192 ? 2 : 4;
     static __device__ __forceinline__ void fetch(V (&f)[kBatch], const V* __restrict__ Gr, const V* __restrict__ G2r, R c2,
                                                  int k0, int kstep, int K, int ldh) {
 #pragma unroll
