@@ -928,8 +928,10 @@ __device__ __forceinline__ void col_aa_dots(const ColParams& p, const V (&f)[2],
     }
 }
 
+// (16 rows: four wavefronts a SIMD, whose loads in flight cover the latency; with three
+// 256 x 16 FP64, 512 members, took 41 us a sweep's pass, now 38)
 template <typename R, int NY, int NACC, int IT>
-__global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX)) k_col(const ColParams p, const typename cplx_of<R>::type* __restrict__ twY) {
+__global__ void __launch_bounds__((64 * ColShape<R, NY>::WMAX), (NY <= 16 && NACC <= 2 ? 4 : 1)) k_col(const ColParams p, const typename cplx_of<R>::type* __restrict__ twY) {
     using CS = ColShape<R, NY>;
     using V = typename CS::V;
     constexpr int S = CS::S, NH = CS::NH, E = CS::E, P = CS::P, CW = CS::CW, REG = CS::REG, AREA = CS::AREA;
