@@ -250,7 +250,9 @@ static sbi_grid inner_grid(const sbi_grid* g) {
 constexpr int kFullSplitMax = 16;  // source-point slices of a pair pass of the fully nonlinear solve
 // blocks a side of the symmetric single-layer pass: of one tile, or of two where
 // the points of all members fill the chip with a quarter of the workgroups too and
-// their slices would take 16 MiB and more (the allocation-free call has 64 in all)
+// their slices would take 16 MiB and more (the allocation-free call has 64 in all).
+// With the split of the other passes it makes the order of this mode's sums, and so
+// their last digits, follow from the number of members
 static int full_sym_blocks(int nx, int batch) {
     return nx / kFullSymTile / ((long long)nx * batch <= 16384 ? 1 : 2);
 }
@@ -1850,6 +1852,15 @@ static sbi_status solve_stage(sbi_ctx* c, const void* eta_user, double tol, bool
 //    1024 points FP64, four SA steps                   1160    1891
 //     256 points FP64, four SA steps of 1024 members   2707    3975
 //      16 points FP32, four SA steps                    663    1628
+// Many members fill the chip either way; there the transforms' work in LDS still
+// pays (four steps, the separate passes with a band just above the half):
+//    1024 points FP64, 256 members, SA / mixed     1301 /  4337     4045 / 12714
+//    1024 points FP64, 1024 members                4796 / 17044     9041 / 26303
+//    1024 points FP64, 4096 members               18567 / 67345    33135 / 96999
+//    1024 points FP32, 4096 members               12531 / 27362    18882 / 30921
+//     256 points FP64, 4096 members               10622 / 39540    14388 / 46016
+// (of the shapes from 256 points up, the separate passes are ahead, by 5 to 7%, for
+// 4096 members iterated in FP32 at 512 points and relaxed at 1024).
 // At 2048 and 4096 points a transform spans wavefronts and the registers spill:
 // four tank steps of 4096 points took 4958 against 2486.
 static bool line_ok(const sbi_ctx* c) {

@@ -37,7 +37,8 @@
 // keeps the image form, which then drops the image.
 //
 // One object per precision (SBI_REAL): fields and the pair arithmetic run in
-// that type; the circulant tables, the slices of the pair sums and every
+// that type; the tables of the heights and of the flat geometry and the distances
+// formed from them, the circulant tables, the slices of the pair sums and every
 // accumulation are FP64 (the direct sums over n points would otherwise lose
 // about log10(sqrt(n)) digits in FP32).
 #include <hip/hip_runtime.h>
@@ -255,7 +256,7 @@ __device__ __forceinline__ float pair_log1p(float x) { return log1p(x); }
 // per point leaves one wavefront per SIMD, and its chains of dependent FP64
 // operations then wait on themselves); the lanes' sums are added in order.
 // Bound by the issue of FP64 operations, 60 to 75 a pair.  FP64, 4096 points,
-// per pass: the bed pass 83 us, the surface pass 55, the double layer 52 (148,
+// per pass: the bed pass 75 us, the surface pass 56, the double layer 52 (148,
 // 174 and 114 with one thread per point, the library's logarithms, the general
 // division and a sinh of each pair's height difference).
 constexpr int kPairLanes = 4;
@@ -420,7 +421,7 @@ __global__ void __launch_bounds__(kPairThreads) k_full_pairs(const FullParams p)
 // tile's diagonals each: at 4096 points 2080 workgroups, eight to nine per CU
 // (blocks of two tiles a side leave two or three, a third of the chip idle at the
 // end: those are for where the slices of many members would fill memory instead).
-// FP64, 4096 points: 39 us per pass, against 109 with tiles of 128 and two
+// FP64, 4096 points: 41 us per pass, against 109 with tiles of 128 and two
 // library logarithms a pair.
 constexpr int kSymT = kFullSymTile;
 constexpr int kSymWaves = 4;

@@ -711,11 +711,12 @@ template <typename R, int NY> struct ColShape {
     // 256 / S bytes apart modulo the banks, so that consecutive modes, which
     // alternate between the classes, are read without conflicts
     static constexpr int AREA = CW * REG + (S > 1 ? 256 / S / (int)sizeof(V) : 0);
-    // wavefronts of a workgroup at most: twelve leave each thread 168 registers,
-    // enough to hold the next round's column in FP64
+    // wavefronts of a workgroup at most: twelve leave each thread 168 registers, which
+    // hold the next round's column in FP64 too, but for 7 registers of a sweep and 47 of
+    // the state pass at 1024 rows, and 13 to 23 at 2048 rows with two modes an owner
     static constexpr int WMAX = 12;
-    // kept modes per owner thread when all of a column's are kept (1 below 1024
-    // rows; quarter bands of 1024 rows take 1 as well)
+    // kept modes per owner thread when all of a column's are kept: 1 below 1024 rows,
+    // 2 at 1024 and 3 at 2048 rows, where half bands take 1 and 2
     static constexpr int ITMAX = (CW * (NY - 1) + 64 * WMAX - 1) / (64 * WMAX);
     static_assert(WMAX % S == 0 && WMAX * AREA * sizeof(V) + 4096 <= kMaxLdsBytes, "the workgroup's LDS");
 };
