@@ -107,10 +107,9 @@ typedef struct sbi_grid {
                               sweeps per solve (then SBI_WARN_NOT_CONVERGED).
                               Not for ensembles (sbi_batch_init) or
                               sbi_vertical_velocity_noalloc (SBI_ERR_UNSUPPORTED) */
-    int32_t mode;          /* SBI_MODE_ITER (default), SBI_MODE_SA or SBI_MODE_FULL (1D).
-                              A member's results do not depend on the other members
-                              of its context; in SBI_MODE_FULL their last digits do
-                              (the order of the sums follows the number of members) */
+    int32_t mode;          /* SBI_MODE_ITER (default), SBI_MODE_SA or SBI_MODE_FULL (1D;
+                              the order of its sums, and so the last digits of a
+                              member's results, follow from the number of members) */
     int32_t seed;          /* SBI_SEED_* for the iteration; default SBI_SEED_LINEAR,
                               the initiation of Sec. 2.4.  SBI_SEED_PREV: the linear
                               guess plus the nonlinear part (V* - k tanh(kh) phi_hat,
