@@ -3213,7 +3213,10 @@ extern "C" sbi_status sbi_batch_init(sbi_batch** out, int32_t m, const sbi_grid*
 // transforms them, a steps part advances the spectral states n steps, the
 // epilogue transforms back and copies out.  Each part forks the groups onto
 // their streams and joins them back to b->cap.
-enum { PART_PROLOGUE = 0, PART_STEPS = 1, PART_EPILOGUE = 2 };
+// Groups whose steps run in one kernel load their states in the call's first
+// steps (PART_FIRST), as a context of the member's own does, so that both hold the
+// same state bit for bit; the prologue (n: 1 when steps follow, else 0) leaves them out.
+enum { PART_PROLOGUE = 0, PART_STEPS = 1, PART_EPILOGUE = 2, PART_FIRST = 3 };
 
 // copies of `bytes` each on a stream, in one launch per kCopyList of them;
 // where destinations overlap (a caller's tensor given for two members) or an
@@ -3264,23 +3267,19 @@ static sbi_status batch_enqueue_part(sbi_batch* b, sbi_state* states, int part, 
                 in.emplace_back(s.phi_s, gr.st_phi + k * gr.field_bytes);
             }
             SBI_TRY(copy_fields(in, gr.field_bytes, gr.s));
-            if (line_ok(c)) {
-                // by the kernel that steps, as a context of the member's own: the same state bit for bit
-                LineParams lp = line_params(c, tol);
-                lp.load = 2;
-                lp.eta_in = gr.st_eta;
-                lp.phi_in = gr.st_phi;
-                SBI_TRY(line_enqueue(c, lp, 1));
-            } else {
-                SBI_TRY(to_spectral(c, gr.st_eta, gr.st_phi, true));
-            }
-        } else if (part == PART_STEPS) {
+            if (n == 0 || !line_ok(c)) SBI_TRY(to_spectral(c, gr.st_eta, gr.st_phi, true));
+        } else if (part == PART_STEPS || part == PART_FIRST) {
             double t = states[gr.members[0]].t + toff;
             if (line_ok(c)) {
                 LineParams lp = line_params(c, tol);
                 lp.rk.h = dt;
                 lp.t0 = t;
                 lp.keep = 1;
+                if (part == PART_FIRST) {
+                    lp.load = 1;
+                    lp.eta_in = gr.st_eta;
+                    lp.phi_in = gr.st_phi;
+                }
                 SBI_TRY(line_enqueue(c, lp, n));
             }
             for (int step = 0; step < n && !line_ok(c); ++step) {
@@ -3356,25 +3355,25 @@ constexpr size_t kMaxGraphs = 8;
 // instantiated) or directly
 static sbi_status batch_part(sbi_batch* b, sbi_state* states, int part, double dt, int n, double tol, double toff) {
     if (!(b->flags & SBI_BATCH_GRAPH)) return batch_enqueue_part(b, states, part, dt, n, tol, toff);
+    const bool steps = part == PART_STEPS || part == PART_FIRST;
     std::vector<const void*> ptrs;
     std::vector<int> prev, budget;
-    if (part != PART_STEPS)
+    if (!steps)
         for (int i = 0; i < b->m; ++i) {
             ptrs.push_back(states[i].eta);
             ptrs.push_back(states[i].phi_s);
         }
     // what the captured solves are seeded from: the previous solve, and how
     // many history entries the learned layer holds; and the sweep budgets
-    if (part == PART_STEPS)
+    if (steps)
         for (auto& gr : b->g) {
             prev.push_back((gr.c->have_prev ? 1 : 0) + 2 * std::min(gr.c->hist_count, gr.c->hist_K));
             budget.push_back(gr.c->budget);
         }
-    const bool steps = part == PART_STEPS;
     sbi_batch::Graph* hit = nullptr;
     for (auto& gg : b->graphs)
-        if (gg.part == part && gg.ptrs == ptrs && (!steps || (gg.n == n && gg.dt == dt && gg.tol == tol &&
-                                                               gg.prev == prev && gg.budget == budget))) {
+        if (gg.part == part && gg.ptrs == ptrs && gg.n == n &&
+            (!steps || (gg.dt == dt && gg.tol == tol && gg.prev == prev && gg.budget == budget))) {
             hit = &gg;
             break;
         }
@@ -3407,7 +3406,7 @@ static sbi_status batch_part(sbi_batch* b, sbi_state* states, int part, double d
         (void)hipGraphDestroy(graph);
         if (e != hipSuccess) return SBI_ERR_HIP;
         gg.part = part;
-        gg.n = steps ? n : 0;
+        gg.n = n;
         gg.dt = steps ? dt : 0.0;
         gg.tol = steps ? tol : 0.0;
         gg.ptrs = ptrs;
@@ -3425,10 +3424,11 @@ static sbi_status batch_part(sbi_batch* b, sbi_state* states, int part, double d
 // epilogue (the spectral states stay in the workspace between parts, so the
 // result does not depend on the split)
 static sbi_status batch_launch(sbi_batch* b, sbi_state* states, double dt, int n, double tol) {
-    SBI_TRY(batch_part(b, states, PART_PROLOGUE, dt, 0, tol, 0.0));
+    const bool line = std::any_of(b->g.begin(), b->g.end(), [](const sbi_batch::Group& gr) { return line_ok(gr.c); });
+    SBI_TRY(batch_part(b, states, PART_PROLOGUE, dt, line && n > 0 ? 1 : 0, tol, 0.0));
     for (int done = 0; done < n; done += kGraphSteps) {
         const int k = std::min(kGraphSteps, n - done);
-        SBI_TRY(batch_part(b, states, PART_STEPS, dt, k, tol, done * dt));
+        SBI_TRY(batch_part(b, states, line && done == 0 ? PART_FIRST : PART_STEPS, dt, k, tol, done * dt));
     }
     return batch_part(b, states, PART_EPILOGUE, dt, 0, tol, 0.0);
 }

@@ -540,7 +540,6 @@ __global__ void __launch_bounds__((LineShape<R, NX>::T)) k_line(const LineParams
                     sv[2] = x;
                 }
             }
-            if (p.load == 2) return;
             phase = LINE_START;
         } else if (phase == LINE_START && !sa) {
             if (lead) {

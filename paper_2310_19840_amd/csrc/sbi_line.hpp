@@ -20,7 +20,7 @@ struct LineParams {
     // steps > 0: that many steps of rk.h from time t0 on the state (rk.eh, rk.ph);
     // 0: one solve at (eta_in, phi_in)
     int steps;
-    int load;            // 1: first transform the physical phi_in (and eta_in when stepping) to the state; 2: only that
+    int load;            // first transform the physical phi_in (and eta_in when stepping) to the state
     int acc_reset;       // clear the totals over solves first
     int keep;            // go on stepping after a failed solve (ensembles)
     double t0;

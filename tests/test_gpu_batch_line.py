@@ -50,7 +50,7 @@ def test_members_equal_single_contexts(gpu, mode, accel, precision, graph):
     b = Batch([m for m, _, _ in mems], device=gpu, graph=graph)
     tol = 1e-10 if precision == "fp64" else 1e-5
     single = [_solver(m, gpu) for m, _, _ in mems]
-    for n in (9, 1, 4, 9):
+    for n in (9, 1, 0, 4, 9):
         st, info = b.step(e, p, 0.05, n, tol=tol)
         assert st == 0
         for i, s in enumerate(single):
