@@ -302,9 +302,9 @@ __device__ __forceinline__ double full_lowest(const FullParams& p, int m) { retu
 template <typename R>
 __device__ __forceinline__ R pair_single(R x, double sh, double sh0, const double* s2, double rfl) {
     const double y = (sh - sh0) * (sh + sh0) * rfl;
-    if (!(y > -0.3)) return R(-0.5) * log((R(1) + x) * R((*s2 + sh * sh) * rfl));
-    const R yr = R(y);
-    return R(-0.5) * pair_log1p(x + yr + x * yr);
+    const R yr = R(y), z = x + yr + x * yr;
+    if (y > -0.3 && z < R(0.42)) return R(-0.5) * pair_small(z);  // z >= y, as x >= 0
+    return R(-0.5) * (y > -0.3 ? log1p(z) : log((R(1) + x) * R((*s2 + sh * sh) * rfl)));
 }
 
 template <typename R, int KIND>
