@@ -35,8 +35,9 @@
  * max_sweeps budget while the launches scale with the sweeps the solves need.
  * A learned seed (SBI_SEED_NET) that fails is reported, not redone.
  * Groups whose steps run in one kernel (one-dimensional grids of up to 1024
- * points with a kept band of at most half and seeds from the linear guess)
- * decide their sweeps on the device: they enqueue none ahead and have no budget.
+ * points with a kept band of at most half and seeds from the linear guess) go to
+ * spectral space with the call's first steps, and decide their sweeps on the
+ * device: they enqueue none ahead, have no budget and are not tuned.
  *
  * Nothing a batch step computes depends on the state time t (each member's
  * t is only advanced by n*dt): time-dependent forcing -- the wave tank's
